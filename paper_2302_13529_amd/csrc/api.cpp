@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 using imin::DecreaseArgs;
@@ -107,14 +108,106 @@ int alloc_ws(Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap
     return IMIN_OK;
 }
 
+void free_tree(imin::TreeWs &ws)
+{
+    dfree(ws.base);
+    ws = imin::TreeWs();
+}
+
+size_t carve_tree(imin::TreeWs &ws, unsigned char *base, int32_t slots, int64_t lcap,
+                  int64_t xcap, int64_t nclaim, int64_t words)
+{
+    size_t at = 0;
+    auto take = [&](auto *&p, int64_t per_slot) {
+        using T = typename std::remove_reference<decltype(*p)>::type;
+        at = (at + 255) & ~size_t(255);
+        p = base ? reinterpret_cast<T *>(base + at) : nullptr;
+        at += (size_t)slots * (size_t)std::max<int64_t>(per_slot, 1) * sizeof(T);
+    };
+    ws.slots = slots;
+    ws.lcap = lcap;
+    ws.xcap = xcap;
+    ws.nclaim = nclaim;
+    ws.words = words;
+    take(ws.rng, lcap);
+    take(ws.dom, lcap);
+    take(ws.rid, lcap);
+    take(ws.par, lcap);
+    take(ws.acc, lcap);
+    take(ws.lvl, lcap + 1);
+    take(ws.lid, nclaim);
+    take(ws.extra, xcap);
+    take(ws.planes, imin::kTreePlanes * words);
+    take(ws.used, 1);
+    return at;
+}
+
+int alloc_tree(imin::TreeWs &ws, int32_t slots, int64_t lcap, int64_t xcap, int64_t nclaim,
+               int64_t words, hipStream_t stream)
+{
+    if (ws.base && ws.slots == slots && ws.lcap == lcap && ws.xcap == xcap &&
+        ws.nclaim == nclaim && ws.words == words)
+        return IMIN_OK;
+    free_tree(ws);
+    imin::TreeWs w;
+    const size_t bytes = carve_tree(w, nullptr, slots, lcap, xcap, nclaim, words);
+    unsigned char *base = nullptr;
+    if (!ok(hipMalloc(&base, bytes))) {
+        (void)hipGetLastError();
+        return IMIN_ENOMEM;
+    }
+    carve_tree(w, base, slots, lcap, xcap, nclaim, words);
+    w.base = base;
+    w.bytes = bytes;
+    ws = w;
+    // the planes start at zero; every launch leaves them so once they are drained
+    if (!ok(hipMemsetAsync(ws.planes, 0, (size_t)slots * imin::kTreePlanes * (size_t)words * 4,
+                           stream))) {
+        free_tree(ws);
+        return IMIN_EDEVICE;
+    }
+    return IMIN_OK;
+}
+
 // Per-slot scratch: every local array holds all n vertices plus the root, so only the
 // extra-edge list can overflow. Its default capacity covers a quarter of the vertices; a
 // graph whose m is below that can never overflow and needs no spill path.
 bool small_enabled(const imin_graph *g);
 
 // max_slots > 0 caps a new allocation (an existing one of the right shape is kept).
-int size_workspaces(imin_graph *g, int32_t max_slots)
+int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach_only)
 {
+    if (g->tree) {
+        imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT, reach_only, theta, g->num_cus,
+                         g->shape);
+        // every reachable vertex and the root fit; only the extra-edge list can overflow
+        const int64_t lcap = (int64_t)g->nreach + 1, xmax = (int64_t)g->m + 1;
+        const int64_t words = ((int64_t)g->nreach + 31) / 32;
+        const bool lt = g->model == IMIN_LT;
+        const int64_t nclaim = lt ? 0 : g->nclaim;
+        int64_t xcap = g->force_xcap > 0 ? g->force_xcap : std::max<int64_t>(4096, lcap / 4);
+        xcap = lt ? 1 : std::min(xcap, xmax);
+        int32_t slots = g->force_slots;
+        if (slots <= 0) {
+            size_t free_b = 0, total_b = 0;
+            if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
+            free_b += g->main_tw.bytes;
+            imin::TreeWs one;
+            const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, nclaim, words);
+            const size_t by_mem = std::max<size_t>(1, (free_b / 2) / per);
+            slots = (int32_t)std::min<size_t>((size_t)g->shape.per_cu * g->num_cus, by_mem);
+            if (max_slots > 0) slots = std::min(slots, max_slots);
+            // an allocation that is at least as large stays
+            if (g->main_tw.base && g->main_tw.lcap == lcap && g->main_tw.xcap == xcap)
+                slots = std::max(slots, g->main_tw.slots);
+        }
+        int rc = alloc_tree(g->main_tw, slots, lcap, xcap, nclaim, words, g->stream);
+        if (rc) return rc;
+        if (!lt && xcap < xmax)
+            return alloc_tree(g->big_tw, kSpillSlots, lcap, xmax, nclaim, 0, g->stream);
+        free_tree(g->big_tw);
+        return IMIN_OK;
+    }
     const int64_t lcap = (int64_t)g->n + 1;
     const int64_t xmax = (int64_t)g->m + 1;
     int64_t xcap = g->force_xcap > 0 ? g->force_xcap
@@ -149,9 +242,9 @@ int size_workspaces(imin_graph *g, int32_t max_slots)
     return IMIN_OK;
 }
 
-int prepare_workspaces(imin_graph *g)
+int prepare_workspaces(imin_graph *g, uint32_t theta, bool reach_only = false)
 {
-    return size_workspaces(g, small_enabled(g) ? kSmallModeSlots : 0);
+    return size_workspaces(g, small_enabled(g) ? kSmallModeSlots : 0, theta, reach_only);
 }
 
 int ensure_ovf(imin_graph *g, uint32_t theta)
@@ -182,7 +275,8 @@ bool small_enabled(const imin_graph *g)
 {
     if (g->small_mode == 0) return false;
     if (g->small_mode == 1) return true;
-    return !g->small_auto_off;
+    // automatic: the LDS-claim kernel takes small samples as well as large ones
+    return !g->tree && !g->small_auto_off;
 }
 
 int small_grid(int num_cus, const imin_launch &l)
@@ -262,6 +356,12 @@ void describe(imin_graph *g, int32_t nseeds, uint64_t seed, uint32_t theta)
     I.nseeds = nseeds;
     I.n = g->n;
     I.nquads = (int32_t)std::max<int64_t>(((int64_t)g->m + 3) / 4, 1);
+    I.nclaim = g->nclaim;
+    I.nreach = g->nreach;
+    I.tedge = g->d_tedge;
+    I.rec = g->mask_rec();
+    I.code = g->d_code;
+    I.rid_vtx = g->d_rid_vtx;
     I.seed_lo = (uint32_t)seed;
     I.seed_hi = (uint32_t)(seed >> 32);
     I.theta = theta;
@@ -304,14 +404,15 @@ int upload_call_state(imin_graph *g, const std::vector<int32_t> &seeds,
     if (!g->mask_known) {
         const int64_t quads = std::max<int64_t>(((int64_t)g->m + 3) / 4, 1);
         if (!ok(hipMemcpyAsync(g->d_thr4, g->d_thr_orig, (size_t)quads * sizeof(uint4),
-                               hipMemcpyDeviceToDevice, g->stream)))
+                               hipMemcpyDeviceToDevice, g->stream)) ||
+            (g->mask_rec() && !ok(imin::launch_edge_restore(orig, g->m, g->mask_rec(), g->stream))))
             return IMIN_EDEVICE;
     } else if (!g->mask_prev.empty()) {
         if (!ok(hipMemcpyAsync(g->d_list, g->mask_prev.data(),
                                g->mask_prev.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                g->stream)) ||
-            !ok(imin::launch_mask_list(thr, orig, g->d_in_ptr, g->d_in_edge, g->d_list,
-                                       (int32_t)g->mask_prev.size(), 1, g->stream)))
+            !ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge,
+                                       g->d_list, (int32_t)g->mask_prev.size(), 1, g->stream)))
             return IMIN_EDEVICE;
     }
     g->mask_known = false;
@@ -320,8 +421,8 @@ int upload_call_state(imin_graph *g, const std::vector<int32_t> &seeds,
     if (!g->masked.empty() &&
         (!ok(hipMemcpyAsync(g->d_list + g->n, g->masked.data(), g->masked.size() * sizeof(int32_t),
                             hipMemcpyHostToDevice, g->stream)) ||
-         !ok(imin::launch_mask_list(thr, orig, g->d_in_ptr, g->d_in_edge, g->d_list + g->n,
-                                    (int32_t)g->masked.size(), 0, g->stream))))
+         !ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge,
+                                    g->d_list + g->n, (int32_t)g->masked.size(), 0, g->stream))))
         return IMIN_EDEVICE;
     return IMIN_OK;
 }
@@ -357,8 +458,56 @@ int kernel_events(imin_graph *g, hipEvent_t *a, hipEvent_t *b)
 int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_t key,
                     const uint32_t *list, const uint32_t *count, bool reach_only)
 {
-    const bool spill = t.big_ws->slots > 0;
     if (!ok(imin::launch_fill_u32(t.ctrl, 3, 0, g->stream))) return IMIN_EDEVICE;
+    if (g->tree) {
+        const bool lt = g->model == IMIN_LT;
+        const bool spill = t.big_tw->slots > 0;
+        imin::TreeArgs a{};
+        a.row_ptr = g->d_row_ptr;
+        a.edge = g->d_tedge;
+        a.code = g->d_code;
+        a.thr4 = t.thr4;
+        a.tl = g->d_tl;
+        a.seeds = t.seeds;
+        a.nseeds = t.nseeds;
+        a.nclaim = g->nclaim;
+        a.nreach = g->nreach;
+        a.rid_vtx = g->d_rid_vtx;
+        a.key_lo = (uint32_t)key;
+        a.key_hi = (uint32_t)(key >> 32);
+        a.theta = theta;
+        a.sample_list = list;
+        a.sample_count = count;
+        a.next = t.ctrl + 0;
+        a.D = t.D;
+        a.stats = t.stats;
+        a.ovf_list = t.ovf;
+        a.ovf_count = t.ctrl + 2;
+        a.error = t.ctrl + 3;
+        a.spill_ok = spill ? 1 : 0;
+        a.reach_only = reach_only ? 1 : 0;
+        a.count_reach = reach_only ? 0 : 1;
+        a.ws = *t.main_tw;
+        a.ws.slots = (int32_t)std::min<uint32_t>((uint32_t)t.main_tw->slots, theta);
+        if (g->force_slots <= 0)
+            a.ws.slots = std::min(a.ws.slots, g->shape.per_cu * g->num_cus);
+        const int32_t used = a.ws.slots;
+        if (!ok(imin::launch_tree(a, g->shape, lt, g->stream))) return IMIN_EDEVICE;
+        if (spill && !reach_only) {
+            a.sample_list = t.ovf;
+            a.sample_count = t.ctrl + 2;
+            a.next = t.ctrl + 1;
+            a.spill_ok = 0;
+            a.count_reach = 0;
+            a.ws = *t.big_tw;
+            if (!ok(imin::launch_tree(a, g->shape, lt, g->stream))) return IMIN_EDEVICE;
+        }
+        if (!reach_only && !ok(imin::launch_drain_planes(*t.main_tw, used, g->d_rid_vtx,
+                                                         g->nreach, t.D, g->stream)))
+            return IMIN_EDEVICE;
+        return IMIN_OK;
+    }
+    const bool spill = t.big_ws->slots > 0;
     DecreaseArgs a;
     std::memset(&a, 0, sizeof(a));
     a.row_ptr = g->d_row_ptr;
@@ -416,6 +565,8 @@ void multi_free(MultiScratch &ms)
     ms.table_cap = ms.stages_cap = ms.stage_cap = ms.rounds_cap = ms.out_cap = 0;
     free_ws(ms.main_ws);
     free_ws(ms.big_ws);
+    free_tree(ms.main_tw);
+    free_tree(ms.big_tw);
     dfree(ms.ctrl);
     dfree(ms.pi);
     dfree(ms.pj);
@@ -430,15 +581,46 @@ void multi_free(MultiScratch &ms)
     ms.inst_cap = 0;
 }
 
-int multi_alloc(MultiScratch &ms, int num_cus, int64_t max_n, int64_t max_m, uint32_t cap,
-                int32_t max_inst, hipStream_t stream)
+void MultiSize::add(const imin_graph *g)
 {
+    n = std::max<int64_t>(n, g->n);
+    m = std::max<int64_t>(m, g->m);
+    nclaim = std::max<int64_t>(nclaim, g->nclaim);
+    nreach = std::max<int64_t>(nreach, g->nreach);
+    lt = g->model == IMIN_LT;
+}
+
+// The workgroup kernel's slots for many-instance rounds: as many as a compute unit holds,
+// within a quarter of the free memory.
+int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_t stream)
+{
+    const int64_t max_n = size.n, max_m = size.m;
+    size_t free_b = 0, total_b = 0;
+    if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
+    ms.tree = false;
+    if (ms.tree) {
+        free_ws(ms.main_ws);
+        free_ws(ms.big_ws);
+        const int64_t lcap = size.nreach + 1, xmax = max_m + 1;
+        const int64_t nclaim = size.lt ? 0 : size.nclaim;
+        const int64_t xcap = size.lt ? 1 : std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
+        free_b += ms.main_tw.bytes;
+        imin::TreeWs one;
+        const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, nclaim, 0);
+        const int32_t slots = (int32_t)std::max<size_t>(
+            1, std::min<size_t>((size_t)ms.shape.per_cu * std::max(1, num_cus), (free_b / 4) / per));
+        int rc = alloc_tree(ms.main_tw, slots, lcap, xcap, nclaim, 0, stream);
+        if (rc) return rc;
+        if (!size.lt && xcap < xmax)
+            return alloc_tree(ms.big_tw, (int32_t)kSpillSlots, lcap, xmax, nclaim, 0, stream);
+        free_tree(ms.big_tw);
+        return IMIN_OK;
+    }
+    free_tree(ms.main_tw);
+    free_tree(ms.big_tw);
     const int64_t lcap = max_n + 1;
     const int64_t xmax = max_m + 1;
     const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
-    // kMultiSlotsPerCu workgroup slots per compute unit, within a quarter of the free memory
-    size_t free_b = 0, total_b = 0;
-    if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
     free_b += ms.main_ws.bytes;
     const size_t per = slot_bytes(max_n, lcap, xcap, true);
     const int32_t slots = (int32_t)std::max<size_t>(
@@ -452,6 +634,14 @@ int multi_alloc(MultiScratch &ms, int num_cus, int64_t max_n, int64_t max_m, uin
     } else {
         free_ws(ms.big_ws);
     }
+    return IMIN_OK;
+}
+
+int multi_alloc(MultiScratch &ms, int num_cus, const MultiSize &size, uint32_t cap,
+                int32_t max_inst, hipStream_t stream)
+{
+    const int rc = multi_slots(ms, num_cus, size, stream);
+    if (rc) return rc;
     if (cap > ms.cap) {
         dfree(ms.pi);
         dfree(ms.pj);
@@ -488,8 +678,8 @@ int multi_alloc(MultiScratch &ms, int num_cus, int64_t max_n, int64_t max_m, uin
         return IMIN_ENOMEM;
     }
     if (!ok(imin::launch_fill_u32(ms.ctrl, kMultiCtrl, 0, stream))) return IMIN_EDEVICE;
-    ms.n = max_n;
-    ms.m = max_m;
+    ms.n = size.n;
+    ms.m = size.m;
     return IMIN_OK;
 }
 
@@ -516,7 +706,6 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
                 bool lt, hipStream_t stream)
 {
     if (total > ms.cap) return IMIN_ERANGE;
-    const bool spill = ms.big_ws.slots > 0;
     // words 0-5, 7 and 8 restart every round; the error words 2 and 6 accumulate, and word 9
     // (instances done) over the call
     if (!ok(imin::launch_batch_zero(inst, ninst, stream)) ||
@@ -565,6 +754,34 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
     s.error = ms.ctrl + 2;
     if (!pack && !ok(imin::launch_decrease_small(s, small_grid(num_cus, shape), stream)))
         return IMIN_EDEVICE;
+    if (ms.tree) {
+        const bool spill = ms.big_tw.slots > 0;
+        imin::TreeArgs a{};
+        a.theta = total;
+        a.sample_list = pack ? ms.pj : ms.sj;
+        a.sample_count = pack ? ms.ctrl + 7 : ms.ctrl + 1;
+        a.next = ms.ctrl + 3;
+        a.ovf_list = ms.oj;
+        a.ovf_count = ms.ctrl + 5;
+        a.error = ms.ctrl + 6;
+        a.spill_ok = spill ? 1 : 0;
+        a.ws = ms.main_tw;
+        a.inst = inst;
+        a.sample_inst = pack ? ms.pi : ms.si;
+        a.ovf_inst = ms.oi;
+        a.round = round;
+        if (!ok(imin::launch_tree(a, ms.shape, lt, stream))) return IMIN_EDEVICE;
+        if (spill) {
+            a.sample_list = ms.oj;
+            a.sample_inst = ms.oi;
+            a.sample_count = ms.ctrl + 5;
+            a.next = ms.ctrl + 4;
+            a.spill_ok = 0;
+            a.ws = ms.big_tw;
+            if (!ok(imin::launch_tree(a, ms.shape, lt, stream))) return IMIN_EDEVICE;
+        }
+    } else {
+    const bool spill = ms.big_ws.slots > 0;
     DecreaseArgs a;
     std::memset(&a, 0, sizeof(a));
     a.n = (int32_t)ms.n;
@@ -592,6 +809,7 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
         a.ws = ms.big_ws;
         if (!ok(imin::launch_decrease(a, stream))) return IMIN_EDEVICE;
     }
+    }
     if (select) {
         if (ninst > ms.inst_cap) return IMIN_ERANGE;
         if (!ok(imin::launch_batch_argmax(inst, ninst, (int32_t)round, ms.part_d, ms.part_i,
@@ -617,7 +835,7 @@ int launch_large(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t key,
                  const uint32_t *list, const uint32_t *count, bool reach_only = false)
 {
     LargeTarget t{g->d_thr4, g->d_seeds, nseeds, g->d_D, g->d_stats, g->d_ctrl, g->d_ovf,
-                  &g->main_ws, &g->big_ws};
+                  &g->main_ws, &g->big_ws, &g->main_tw, &g->big_tw};
     return launch_large_on(g, t, theta, key, list, count, reach_only);
 }
 
@@ -632,7 +850,7 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         // Automatic mode, a call that kept the wave kernel: after a timed round with it, a
         // timed trial round of the workgroup kernel alone, at its full slot count.
         g->small_auto_off = true;
-        rc = size_workspaces(g, 0);
+        rc = size_workspaces(g, 0, theta, reach_only);
         if (rc) return rc;
     } else if (g->probe == 3) {
         // The call keeps whichever form ran its round faster (results are the same).
@@ -696,7 +914,7 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
                 g->probe = 1;
             }
             if (drop || handed > (uint32_t)g->main_ws.slots) {
-                rc = size_workspaces(g, 0);
+                rc = size_workspaces(g, 0, theta, reach_only);
                 if (rc) return rc;
             }
         }
@@ -764,6 +982,11 @@ void destroy(imin_graph *g)
     }
     free_ws(g->main_ws);
     free_ws(g->big_ws);
+    free_tree(g->main_tw);
+    free_tree(g->big_tw);
+    dfree(g->d_rid_vtx);
+    dfree(g->d_tedge);
+    dfree(g->d_code);
     dfree(g->d_row_ptr);
     dfree(g->d_col4);
     dfree(g->d_edge);
@@ -956,6 +1179,22 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         std::vector<int32_t> fill(in_ptr.begin(), in_ptr.end() - 1);
         for (int32_t e = 0; e < m; ++e) in_edge[(size_t)fill[(size_t)col[e]]++] = e;
     }
+    // Reach ids: the vertices that need a claim (two or more in-edges), then those with one.
+    std::vector<int32_t> rid, rid_vtx;
+    int32_t nclaim = 0;
+    try {
+        rid.assign((size_t)n, 0);
+        rid_vtx.reserve((size_t)n);
+        for (int32_t v = 0; v < n; ++v)
+            if (in_ptr[(size_t)v + 1] - in_ptr[(size_t)v] > 1) rid_vtx.push_back(v);
+        nclaim = (int32_t)rid_vtx.size();
+        for (int32_t v = 0; v < n; ++v)
+            if (in_ptr[(size_t)v + 1] - in_ptr[(size_t)v] == 1) rid_vtx.push_back(v);
+    } catch (...) {
+        delete g;
+        return IMIN_ENOMEM;
+    }
+    for (size_t r = 0; r < rid_vtx.size(); ++r) rid[(size_t)rid_vtx[r]] = (int32_t)r;
     // Linear-threshold model: the in-edges of v split [0, 2^24) into consecutive intervals,
     // edge k of v (ascending id) getting [bound_{k-1}, bound_k) with
     // bound_k = min(2^24, ceil(2^24 * (w_1 + ... + w_k))) from fp64 running sums.
@@ -986,6 +1225,11 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     }
     g->model = model;
     g->words = (n + 31) / 32;
+    g->nclaim = nclaim;
+    g->nreach = (int32_t)rid_vtx.size();
+    g->tree = imin::tree_shape(g->nclaim, g->nreach, model == IMIN_LT, false, 1, g->num_cus,
+                               g->shape);
+    int32_t *d_rid = nullptr;
     bool good =
         ok(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking)) &&
         ok(hipEventCreate(&g->ev0)) && ok(hipEventCreate(&g->ev1)) &&
@@ -1009,9 +1253,14 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         ok(hipMalloc(&g->d_x, sizeof(int32_t))) &&
         (model != IMIN_LT || ok(hipMalloc(&g->d_lo4, hlo.size() * sizeof(uint32_t)))) &&
         (model != IMIN_LT || ok(hipMalloc(&g->d_tl, 2 * hlo.size() * sizeof(uint32_t)))) &&
-        (model != IMIN_IC || ok(hipMalloc(&g->d_edge, hcol.size() * sizeof(uint4))));
+        (model != IMIN_IC || ok(hipMalloc(&g->d_edge, hcol.size() * sizeof(uint4)))) &&
+        (!g->tree || ok(hipMalloc(&g->d_tedge, hcol.size() * sizeof(uint4)))) &&
+        (!g->tree || model != IMIN_IC || ok(hipMalloc(&g->d_code, hcol.size()))) &&
+        ok(hipMalloc(&g->d_rid_vtx, std::max<size_t>(rid_vtx.size(), 1) * sizeof(int32_t))) &&
+        ok(hipMalloc(&d_rid, (size_t)n * sizeof(int32_t)));
     if (!good) {
         (void)hipGetLastError();
+        dfree(d_rid);
         destroy(g);
         return IMIN_ENOMEM;
     }
@@ -1028,10 +1277,21 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         !ok(hipMemcpy(g->d_in_edge, in_edge.data(), in_edge.size() * sizeof(int32_t),
                       hipMemcpyHostToDevice)) ||
         (model == IMIN_LT && !ok(hipMemcpy(g->d_lo4, hlo.data(), hlo.size() * sizeof(uint32_t),
-                                           hipMemcpyHostToDevice)))) {
+                                           hipMemcpyHostToDevice))) ||
+        (!rid_vtx.empty() &&
+         !ok(hipMemcpy(g->d_rid_vtx, rid_vtx.data(), rid_vtx.size() * sizeof(int32_t),
+                       hipMemcpyHostToDevice))) ||
+        !ok(hipMemcpy(d_rid, rid.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice)) ||
+        !ok(imin::launch_edge_records(reinterpret_cast<const uint32_t *>(g->d_col4), g->d_row_ptr,
+                                      d_rid, reinterpret_cast<const uint32_t *>(g->d_thr_orig), m,
+                                      g->d_tedge, reinterpret_cast<uint8_t *>(g->d_code), g->d_edge,
+                                      g->stream)) ||
+        !ok(hipStreamSynchronize(g->stream))) {
+        dfree(d_rid);
         destroy(g);
         return IMIN_EDEVICE;
     }
+    dfree(d_rid);
     if (model == IMIN_LT) {
         // per quad: its 4 targets, then its 4 lower bounds
         std::vector<uint32_t> htl;
@@ -1047,26 +1307,6 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
                 htl[8 * q + 4 + k] = hlo[4 * q + k];
             }
         if (!ok(hipMemcpy(g->d_tl, htl.data(), htl.size() * sizeof(uint32_t),
-                          hipMemcpyHostToDevice))) {
-            destroy(g);
-            return IMIN_EDEVICE;
-        }
-    }
-    if (model == IMIN_IC) {
-        // edge records: padding slots past m stay zero (their coins are never live)
-        std::vector<uint4> hedge;
-        try {
-            hedge.assign(hcol.size(), make_uint4(0, 0, 0, 0));
-        } catch (...) {
-            destroy(g);
-            return IMIN_ENOMEM;
-        }
-        for (int64_t e = 0; e < (int64_t)m; ++e) {
-            const int32_t v = col[e];
-            hedge[(size_t)e] = make_uint4((uint32_t)v, (uint32_t)row_ptr[v],
-                                          (uint32_t)row_ptr[(size_t)v + 1], 0u);
-        }
-        if (!ok(hipMemcpy(g->d_edge, hedge.data(), hedge.size() * sizeof(uint4),
                           hipMemcpyHostToDevice))) {
             destroy(g);
             return IMIN_EDEVICE;
@@ -1113,7 +1353,7 @@ int one_call(imin_graph *g, const int32_t *S, int32_t nS, const uint8_t *blocked
     }
     rc = begin_call(g);
     if (rc) return rc;
-    rc = prepare_workspaces(g);
+    rc = prepare_workspaces(g, theta, reach_only);
     if (rc) return rc;
     rc = ensure_ovf(g, theta);
     if (rc) return rc;
@@ -1179,7 +1419,7 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
     const int32_t ns = (int32_t)seeds.size();
     rc = begin_call(g);
     if (rc) return rc;
-    rc = prepare_workspaces(g);
+    rc = prepare_workspaces(g, theta);
     if (rc) return rc;
     rc = ensure_ovf(g, theta);
     if (rc) return rc;
@@ -1200,8 +1440,8 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_inelig, 0, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, nullptr,
-                                              g->d_B, r, g->d_x, thr_w(g), g->d_in_ptr,
-                                              g->d_in_edge, g->stream)))
+                                              g->d_B, r, g->d_x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, g->stream)))
                 return IMIN_EDEVICE;
         }
         B.assign((size_t)rounds, -1);
@@ -1223,8 +1463,8 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_cand, 1, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, g->d_cand,
-                                              g->d_B, r, g->d_x, thr_w(g), g->d_in_ptr,
-                                              g->d_in_edge, g->stream)))
+                                              g->d_B, r, g->d_x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, g->stream)))
                 return IMIN_EDEVICE;
         }
         B.assign((size_t)k, -1);
@@ -1242,8 +1482,8 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
             const int32_t slot =
                 (int32_t)(std::find(B.begin(), B.end(), u) - B.begin());
             if (!ok(imin::launch_set_bit(g->d_inelig, u, 0, g->stream)) ||
-                !ok(imin::launch_mask_vertex(thr_w(g), reinterpret_cast<const uint32_t *>(
-                                                           g->d_thr_orig),
+                !ok(imin::launch_mask_vertex(thr_w(g), g->mask_rec(),
+                                             reinterpret_cast<const uint32_t *>(g->d_thr_orig),
                                              g->d_in_ptr, g->d_in_edge, u, nullptr, 1,
                                              g->stream)))
                 return IMIN_EDEVICE;
@@ -1252,8 +1492,8 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_inelig, 0, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, nullptr,
-                                              g->d_B, slot, g->d_x, thr_w(g), g->d_in_ptr,
-                                              g->d_in_edge, g->stream)))
+                                              g->d_B, slot, g->d_x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, g->stream)))
                 return IMIN_EDEVICE;
             int32_t x = -1;
             if (!ok(hipMemcpyAsync(&x, g->d_x, sizeof(int32_t), hipMemcpyDeviceToHost,
@@ -1375,11 +1615,8 @@ int imin_greedy_batch(imin_instance *inst, int32_t count, int mode, const imin_l
         }
     }
     const int32_t stride = imin::kGatherB + std::max(max_nb, 1);
-    int64_t max_n = 0, max_m = 0;
-    for (const BatchItem &it : items) {
-        max_n = std::max<int64_t>(max_n, it.g->n);
-        max_m = std::max<int64_t>(max_m, it.g->m);
-    }
+    MultiSize size;
+    for (const BatchItem &it : items) size.add(it.g);
     // The batch's scratch stays with its first graph for the next batch that graph leads
     // (same shape: nothing is allocated or cleared again).
     if (!g0->batch_ms) {
@@ -1387,7 +1624,7 @@ int imin_greedy_batch(imin_instance *inst, int32_t count, int mode, const imin_l
         if (!g0->batch_ms) return IMIN_ENOMEM;
     }
     MultiScratch &ms = *g0->batch_ms;
-    int rc = multi_alloc(ms, g0->num_cus, max_n, max_m, prefix[(size_t)count], count, bs);
+    int rc = multi_alloc(ms, g0->num_cus, size, prefix[(size_t)count], count, bs);
     if (rc) {
         multi_free(ms);
         return rc;
@@ -1425,7 +1662,11 @@ int imin_greedy_batch(imin_instance *inst, int32_t count, int mode, const imin_l
                                     (int64_t)(uintptr_t)ms.part_d, (int64_t)ms.cap,
                                     (int64_t)(uintptr_t)ms.main_ws.map, ms.main_ws.slots,
                                     ms.main_ws.n, ms.main_ws.lcap, ms.main_ws.xcap,
-                                    (int64_t)(uintptr_t)ms.big_ws.map, ms.big_ws.slots};
+                                    (int64_t)(uintptr_t)ms.big_ws.map, ms.big_ws.slots,
+                                    (int64_t)(uintptr_t)ms.main_tw.base, ms.main_tw.slots,
+                                    ms.main_tw.lcap, ms.main_tw.xcap, ms.main_tw.nclaim,
+                                    (int64_t)(uintptr_t)ms.big_tw.base, ms.big_tw.xcap,
+                                    ms.shape.block, ms.shape.per_cu};
         {
             int32_t act = count;
             for (int32_t r = 0; r < max_rounds; ++r) {

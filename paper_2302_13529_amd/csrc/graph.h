@@ -31,6 +31,13 @@ struct imin_graph {
     uint4 *d_lo4 = nullptr;       // linear-threshold model: interval lower bounds
     uint4 *d_tl = nullptr;        // linear-threshold model: per quad, its targets and then its
                                   // lower bounds (32 bytes, one line)
+    int32_t nclaim = 0, nreach = 0;  // reach ids: first the vertices of two or more in-edges,
+                                  // then those of one, each ascending
+    int32_t *d_rid_vtx = nullptr; // nreach: vertex of each reach id
+    bool tree = false;            // the LDS-claim kernel serves this graph
+    imin::TreeShape shape;        // its launch shape in the current call
+    uint4 *d_tedge = nullptr;     // its edge records (their thresholds masked as d_thr4) and
+    uint32_t *d_code = nullptr;   // threshold codes
     int32_t *d_in_ptr = nullptr;  // in-edges of v: d_in_edge[d_in_ptr[v] .. d_in_ptr[v+1])
     int32_t *d_in_edge = nullptr; // edge ids, grouped by target
     hipStream_t stream = nullptr;
@@ -67,6 +74,7 @@ struct imin_graph {
     int32_t B_cap = 0;
     int32_t *d_x = nullptr;
     imin::Workspace main_ws, big_ws;
+    imin::TreeWs main_tw, big_tw;
     std::vector<int32_t> masked;       // vertices whose in-edges have threshold 0 in d_thr4
     std::vector<int32_t> mask_prev;    // the previous call's list, kept while copies run
     bool mask_known = true;            // false while a call runs, and after one that failed
@@ -75,6 +83,8 @@ struct imin_graph {
     size_t kev_used = 0;
     imin::host::MultiScratch *batch_ms = nullptr;  // scratch of the batches this graph leads
                                                    // (first instance), kept for the next one
+    // the records that masks also go to (the LDS-claim kernel's, independent cascade)
+    uint4 *mask_rec() const { return model == IMIN_IC ? d_tedge : nullptr; }
     int32_t force_slots = 0;
     int64_t force_xcap = 0;
 };
@@ -105,6 +115,10 @@ int alloc_ws(Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap
 // Validated seed set: distinct seeds ascending, and the seed bitmap.
 int seed_setup(imin_graph *g, const int32_t *S, int32_t nS, std::vector<int32_t> &seeds,
                std::vector<uint32_t> &inelig);
+// The arrays of `slots` tree-kernel slots carved from base (null: only counted); returns the
+// bytes they take.
+size_t carve_tree(TreeWs &ws, unsigned char *base, int32_t slots, int64_t lcap, int64_t xcap,
+                  int64_t nclaim, int64_t words);
 int small_grid(int num_cus, const imin_launch &l);
 void small_shape(SmallArgs &s, const imin_launch &l);
 bool launch_ok(const imin_launch *l);
@@ -121,6 +135,8 @@ struct LargeTarget {
     uint32_t *ovf;       // capacity >= theta
     Workspace *main_ws;  // slots > 0
     Workspace *big_ws;   // slots == 0 when no sample can overflow main_ws
+    const TreeWs *main_tw;  // graphs of the LDS-claim kernel: these instead
+    const TreeWs *big_tw;
 };
 // The workgroup kernel over samples 0..theta-1, or over the device list `list` of *count
 // samples, then the large-scratch launch for the samples that overflowed.
@@ -136,6 +152,9 @@ struct MultiScratch {
     int64_t n = 0, m = 0;      // largest instance it serves
     uint32_t cap = 0;          // samples of the largest round
     Workspace main_ws, big_ws;
+    bool tree = false;         // the LDS-claim kernel runs the hand-overs, in these
+    TreeShape shape;
+    TreeWs main_tw, big_tw;
     uint32_t *ctrl = nullptr;  // kMultiCtrl: wave next, wave hand-overs, wave error, main
                                // next, big next, overflow count, workgroup error, packed
                                // hand-overs, packed next, instances done this call
@@ -161,7 +180,13 @@ struct MultiScratch {
     hipGraphExec_t exec = nullptr;
     std::vector<int64_t> exec_key;
 };
-int multi_alloc(MultiScratch &ms, int num_cus, int64_t max_n, int64_t max_m, uint32_t cap,
+// The largest instance of a batch.
+struct MultiSize {
+    int64_t n = 0, m = 0, nclaim = 0, nreach = 0;
+    bool lt = false;
+    void add(const imin_graph *g);
+};
+int multi_alloc(MultiScratch &ms, int num_cus, const MultiSize &size, uint32_t cap,
                 int32_t max_inst, hipStream_t stream);
 void multi_free(MultiScratch &ms);
 // One round of every instance of the device table inst[0..ninst) (sample indices

@@ -116,6 +116,96 @@ hipError_t launch_decrease(const DecreaseArgs &a, hipStream_t stream);
 hipError_t launch_flush_counts(const Workspace &ws, int32_t slots, unsigned long long *D,
                                hipStream_t stream);
 
+// Workgroup-per-sample kernel with LDS claims (tree.hip). Scratch of `slots` concurrent
+// samples, slot-major like Workspace's; local id 0 is the merged seed.
+constexpr size_t kTreeLds = 160 * 1024;      // LDS of one compute unit
+constexpr int kTreeWaves = 4;                // waves per SIMD its registers allow
+constexpr int kTreePlanes = 6;               // bit-sliced reach counters of a slot:
+constexpr uint32_t kTreePlaneMax = 63;       // that many samples before they are drained
+
+struct TreeWs {
+    int32_t slots = 0;
+    int64_t lcap = 0;          // local vertices per sample (root included): nreach + 1
+    int64_t xcap = 0;          // non-tree live edges per sample
+    int64_t nclaim = 0;        // vertices that need a claim, at most
+    int64_t words = 0;         // bitmap words of the reach ids (0: the slots never count)
+    int2 *rng = nullptr;       // slots * lcap: row range of each local vertex
+    int32_t *dom = nullptr;    // slots * lcap: dominators that are not BFS parents
+    int32_t *rid = nullptr;    // slots * lcap: reach id
+    int32_t *par = nullptr;    // slots * lcap: BFS parent
+    int32_t *acc = nullptr;    // slots * lcap: sum of the sizes below the vertex
+    int32_t *lvl = nullptr;    // slots * (lcap + 1): first local id of each BFS level
+    int32_t *lid = nullptr;    // slots * nclaim: local id by reach id (extra edges' targets)
+    int4 *extra = nullptr;     // slots * xcap: source, target (reach id, then local id), the
+                               // target's BFS parent, its dominator
+    uint32_t *planes = nullptr; // slots * kTreePlanes * words
+    uint32_t *used = nullptr;  // slots: samples counted in the planes by the last launch
+    unsigned char *base = nullptr;  // the allocation
+    size_t bytes = 0;
+};
+
+// Launch shape by the number of vertices that need a claim and the samples at hand.
+struct TreeShape {
+    int32_t block = 0;     // threads per workgroup (0: the claims do not fit LDS)
+    int32_t per_cu = 0;    // workgroups per compute unit
+    uint32_t lds = 0;      // LDS bytes of a workgroup
+    int32_t bm_words = 0;  // of those, bitmap words
+};
+
+struct TreeArgs {
+    const int32_t *row_ptr;
+    const uint4 *edge;       // per edge: the target's row start, row end and reach id, and the
+                             // edge's working threshold (independent cascade)
+    const uint32_t *code;    // independent cascade: a byte per edge, 4 to a quad, that no live
+                             // coin's code exceeds (threshold_code)
+    const uint4 *thr4;       // linear threshold: working thresholds, as DecreaseArgs::thr4
+    const uint4 *tl;         // linear threshold: as DecreaseArgs::tl
+    const int32_t *seeds;
+    int32_t nseeds;
+    int32_t nclaim, nreach;  // reach ids: [0, nclaim) have two or more in-edges, the others
+                             // below nreach one
+    const int32_t *rid_vtx;  // nreach: vertex of each reach id
+    uint32_t key_lo, key_hi;
+    uint32_t theta;
+    const uint32_t *sample_list;
+    const uint32_t *sample_count;
+    uint32_t *next;
+    unsigned long long *D;
+    unsigned long long *stats;
+    uint32_t *ovf_list;
+    uint32_t *ovf_count;
+    uint32_t *error;
+    int32_t spill_ok;
+    int32_t reach_only;
+    int32_t count_reach;     // slots may count reached vertices in their planes
+    TreeWs ws;
+    uint32_t lds_bytes;      // set by launch_tree
+    int32_t bm_words;
+    const InstanceDesc *inst;  // many-instance launches, as in DecreaseArgs
+    const uint32_t *sample_inst;
+    uint32_t *ovf_inst;
+    uint32_t round;
+};
+
+// False when nclaim vertices do not fit LDS (independent cascade). The workgroup is the
+// smallest with the most threads at work: all sizes run kTreeWaves waves per SIMD where the
+// claims leave room, and smaller workgroups wait less for each other at level ends (20,000
+// reachability samples of a 131k-vertex R-MAT graph: 7.0 ms with 64 threads, 11.2 with 512).
+// With dominators 512 threads are preferred: their LDS holds the dominator and size steps of
+// samples up to 13,600 vertices (10,000 samples of that graph, 11,800 vertices each: 8.4 ms
+// with 512 threads, 8.7 with 256, 9.9 with 64).
+bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
+                int num_cus, TreeShape &out);
+hipError_t launch_tree(const TreeArgs &a, const TreeShape &s, bool lt, hipStream_t stream);
+// D += the counts of the first `slots` slots, which go back to zero.
+hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *rid_vtx,
+                               int32_t nreach, unsigned long long *D, hipStream_t stream);
+hipError_t launch_edge_records(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
+                               const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
+                               uint4 *plain, hipStream_t stream);
+// The records' thresholds of all edges, as created.
+hipError_t launch_edge_restore(const uint32_t *thr, int64_t m, uint4 *edge, hipStream_t stream);
+
 // Wave-per-sample kernel (small.hip): per-sample capacity in local vertices (root
 // included) and in non-tree live edges, and waves per workgroup.
 constexpr int kSmallV = 256;
@@ -155,6 +245,13 @@ struct InstanceDesc {
     int32_t nseeds;
     int32_t n;
     int32_t nquads;           // quads of thr4
+    int32_t nclaim, nreach;   // the LDS-claim kernel's arrays, as in TreeArgs
+    const uint4 *tedge;
+    uint4 *rec;               // the same records when their thresholds are masked with thr4's
+                              // (batched calls, independent cascade); null for a query's
+                              // thresholds, which the shared records do not follow
+    const uint32_t *code;
+    const int32_t *rid_vtx;
     uint32_t seed_lo, seed_hi;
     uint32_t theta;
     uint32_t sample_base;
@@ -225,17 +322,18 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t count, uint32_t value, hipStream
 hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits, int mode,
                                int32_t n, unsigned long long *part_d, int32_t *part_i,
                                int32_t parts, uint32_t *inelig, uint32_t *cand, int32_t *B,
-                               int32_t slot, int32_t *out_x, uint32_t *thr,
+                               int32_t slot, int32_t *out_x, uint32_t *thr, uint4 *rec,
                                const int32_t *in_ptr, const int32_t *in_edge,
                                hipStream_t stream);
 hipError_t launch_set_bit(uint32_t *bits, int32_t v, int value, hipStream_t stream);
 // Thresholds of the in-edges of the vertices list[0..count) (device list), or of the one
 // vertex v (host value; or the device-resident id at v_dev when v_dev is non-null, ignored
 // when negative): set to 0 (restore == 0) or copied back from thr_orig (restore != 0).
-hipError_t launch_mask_list(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+// rec (may be null): edge records whose last word holds the same threshold.
+hipError_t launch_mask_list(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                             const int32_t *in_edge, const int32_t *list, int32_t count,
                             int restore, hipStream_t stream);
-hipError_t launch_mask_vertex(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+hipError_t launch_mask_vertex(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                               const int32_t *in_edge, int32_t v, const int32_t *v_dev,
                               int restore, hipStream_t stream);
 // Batched greedy over instances inst[0..ninst): zero every instance's D; and per instance,

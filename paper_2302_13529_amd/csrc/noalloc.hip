@@ -59,7 +59,7 @@ __global__ void seed_set_kernel(const int32_t *S, int32_t nS, uint32_t *bits, in
 }
 
 // In-edge thresholds of every vertex v with marks[v] != 0: 0, or restored from orig.
-__global__ void mask_marked_kernel(uint32_t *thr, const uint32_t *orig, const int32_t *in_ptr,
+__global__ void mask_marked_kernel(uint32_t *thr, uint4 *rec, const uint32_t *orig, const int32_t *in_ptr,
                                    const int32_t *in_edge, const uint8_t *marks, int32_t n,
                                    int restore)
 {
@@ -68,7 +68,9 @@ __global__ void mask_marked_kernel(uint32_t *thr, const uint32_t *orig, const in
         if (!marks[v]) continue;
         for (int32_t k = in_ptr[v]; k < in_ptr[v + 1]; ++k) {
             const int32_t e = in_edge[k];
-            thr[e] = restore ? orig[e] : 0u;
+            const uint32_t t = restore ? orig[e] : 0u;
+            thr[e] = t;
+            if (rec) rec[e].w = t;
         }
     }
 }
@@ -96,6 +98,18 @@ struct Carve {
         return reinterpret_cast<T *>(base + off);
     }
 };
+
+// The LDS-claim kernel's scratch of `slots` slots in the carve.
+bool carve_tree_ws(Carve &c, imin::TreeWs &ws, int32_t slots, int64_t lcap, int64_t xcap,
+                   int64_t nclaim, int64_t words)
+{
+    const size_t off = (c.used + 255) & ~size_t(255);
+    const size_t bytes =
+        imin::host::carve_tree(ws, c.base + off, slots, lcap, xcap, nclaim, words);
+    if (off + bytes > kScratchBytes) return c.fits = false;
+    c.used = off + bytes;
+    return true;
+}
 
 // Slot-major workgroup-kernel scratch of `slots` slots in the carve.
 bool carve_ws(Carve &c, imin::Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap,
@@ -154,21 +168,40 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     uint32_t *ovf = c.take<uint32_t>(theta);
     // independent cascade: slots keep each claimed vertex's row range
     const bool rng = g->model == IMIN_IC;
-    imin::Workspace big_ws;
-    if (xcap < xmax && !carve_ws(c, big_ws, n, 2, lcap, xmax, rng)) return IMIN_ERANGE;
-    if (!c.fits) return IMIN_ERANGE;
-    const size_t fixed = c.used;
-    // as many workgroup slots as the rest holds, up to the usual count
-    Carve probe{base, fixed};
-    imin::Workspace one;
-    if (!carve_ws(probe, one, n, 1, lcap, xcap, rng)) return IMIN_ERANGE;
-    const size_t per_slot = probe.used - fixed + 7 * 256;
-    const int32_t slots = (int32_t)std::max<size_t>(
-        1, std::min<size_t>((size_t)imin::kSlotsPerCu * g->num_cus,
-                            (kScratchBytes - fixed) / per_slot));
-    imin::Workspace main_ws;
-    if (!carve_ws(c, main_ws, n, slots, lcap, xcap, rng)) return IMIN_ERANGE;
-    if (xcap >= xmax) big_ws = imin::Workspace();
+    imin::Workspace main_ws, big_ws;
+    imin::TreeWs main_tw, big_tw;
+    if (g->tree) {
+        // every reachable vertex and the root fit a slot; as many slots as the array holds,
+        // up to the usual count
+        const bool lt = g->model == IMIN_LT;
+        const int64_t cap = (int64_t)g->nreach + 1, nclaim = lt ? 0 : g->nclaim;
+        const int64_t words = ((int64_t)g->nreach + 31) / 32;
+        const int64_t xc = lt ? 1 : std::min<int64_t>(std::max<int64_t>(4096, cap / 4), xmax);
+        if (!lt && xc < xmax && !carve_tree_ws(c, big_tw, 2, cap, xmax, nclaim, 0))
+            return IMIN_ERANGE;
+        if (!c.fits) return IMIN_ERANGE;
+        imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus, g->shape);
+        imin::TreeWs one;
+        const size_t per_slot = carve_tree(one, nullptr, 1, cap, xc, nclaim, words);
+        const int32_t slots = (int32_t)std::max<size_t>(
+            1, std::min<size_t>((size_t)g->shape.per_cu * g->num_cus,
+                                (kScratchBytes - c.used) / per_slot));
+        if (!carve_tree_ws(c, main_tw, slots, cap, xc, nclaim, words)) return IMIN_ERANGE;
+    } else {
+        if (xcap < xmax && !carve_ws(c, big_ws, n, 2, lcap, xmax, rng)) return IMIN_ERANGE;
+        if (!c.fits) return IMIN_ERANGE;
+        const size_t fixed = c.used;
+        // as many workgroup slots as the rest holds, up to the usual count
+        Carve probe{base, fixed};
+        imin::Workspace one;
+        if (!carve_ws(probe, one, n, 1, lcap, xcap, rng)) return IMIN_ERANGE;
+        const size_t per_slot = probe.used - fixed + 7 * 256;
+        const int32_t slots = (int32_t)std::max<size_t>(
+            1, std::min<size_t>((size_t)imin::kSlotsPerCu * g->num_cus,
+                                (kScratchBytes - fixed) / per_slot));
+        if (!carve_ws(c, main_ws, n, slots, lcap, xcap, rng)) return IMIN_ERANGE;
+        if (xcap >= xmax) big_ws = imin::Workspace();
+    }
 
     hipStream_t st = g->stream;
     uint32_t *thr = reinterpret_cast<uint32_t *>(g->d_thr4);
@@ -178,12 +211,13 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     if (!g->mask_known) {
         const int64_t quads = std::max<int64_t>((m + 3) / 4, 1);
         if (!ok(hipMemcpyAsync(g->d_thr4, g->d_thr_orig, (size_t)quads * sizeof(uint4),
-                               hipMemcpyDeviceToDevice, st)))
+                               hipMemcpyDeviceToDevice, st)) ||
+            (g->mask_rec() && !ok(imin::launch_edge_restore(orig, m, g->mask_rec(), st))))
             return IMIN_EDEVICE;
     } else if (!g->masked.empty()) {
         if (!ok(hipMemcpyAsync(g->d_list, g->masked.data(), g->masked.size() * sizeof(int32_t),
                                hipMemcpyHostToDevice, st)) ||
-            !ok(imin::launch_mask_list(thr, orig, g->d_in_ptr, g->d_in_edge, g->d_list,
+            !ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge, g->d_list,
                                        (int32_t)g->masked.size(), 1, st)))
             return IMIN_EDEVICE;
     }
@@ -203,11 +237,11 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         !ok(hipMemcpyAsync(&nseeds, s_count, sizeof(nseeds), hipMemcpyDeviceToHost, st)) ||
         !ok(hipStreamSynchronize(st)))
         return IMIN_EDEVICE;
-    if (!ok(imin::launch_mask_list(thr, orig, g->d_in_ptr, g->d_in_edge, s_set, (int32_t)nseeds,
+    if (!ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge, s_set, (int32_t)nseeds,
                                    0, st)))
         return IMIN_EDEVICE;
     if (blocked) {
-        hipLaunchKernelGGL(mask_marked_kernel, dim3(grid_of(n)), dim3(kBlock), 0, st, thr, orig,
+        hipLaunchKernelGGL(mask_marked_kernel, dim3(grid_of(n)), dim3(kBlock), 0, st, thr, g->mask_rec(), orig,
                            g->d_in_ptr, g->d_in_edge, marks, (int32_t)n, 0);
         if (!ok(hipGetLastError())) return IMIN_EDEVICE;
     }
@@ -220,6 +254,10 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
             !ok(imin::launch_fill_u32(w->dirty, w->slots, 0u, st)))
             return IMIN_EDEVICE;
     }
+    if (g->tree && !ok(imin::launch_fill_u32(main_tw.planes,
+                                             (int64_t)main_tw.slots * imin::kTreePlanes *
+                                                 main_tw.words, 0u, st)))
+        return IMIN_EDEVICE;
     if (!ok(imin::launch_fill_u64(reinterpret_cast<unsigned long long *>(d_counts), n, 0ull, st)) ||
         !ok(imin::launch_fill_u64(g->d_stats, kStats, 0ull, st)) ||
         !ok(imin::launch_fill_u32(g->d_ctrl, imin::kCtrlWords, 0u, st)) ||
@@ -245,6 +283,11 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     I.nseeds = (int32_t)nseeds;
     I.n = g->n;
     I.nquads = (int32_t)std::max<int64_t>((m + 3) / 4, 1);
+    I.nclaim = g->nclaim;
+    I.nreach = g->nreach;
+    I.tedge = g->d_tedge;
+    I.code = g->d_code;
+    I.rid_vtx = g->d_rid_vtx;
     I.seed_lo = (uint32_t)seed;
     I.seed_hi = (uint32_t)(seed >> 32);
     I.theta = theta;
@@ -252,31 +295,38 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     if (!ok(hipEventRecord(g->ev0, st)) ||
         !ok(hipMemcpyAsync(g->d_inst, &I, sizeof(I), hipMemcpyHostToDevice, st)))
         return IMIN_EDEVICE;
-    imin::SmallArgs s;
-    std::memset(&s, 0, sizeof(s));
-    s.inst = g->d_inst;
-    s.ninst = 1;
-    s.total = theta;
-    s.round = 0;
-    small_shape(s, g->small_launch);
-    s.lt = g->model == IMIN_LT ? 1 : 0;
-    s.next = g->d_sctrl + 0;
-    s.spill_j = sj;
-    s.spill_count = g->d_sctrl + 1;
-    s.error = g->d_ctrl + 3;
-    if (!ok(imin::launch_decrease_small(s, small_grid(g->num_cus, g->small_launch), st)))
-        return IMIN_EDEVICE;
+    // the LDS-claim kernel takes every sample itself; the other workgroup kernel those that
+    // the wave kernel leaves
+    const uint32_t *list = nullptr, *list_count = nullptr;
+    if (!g->tree) {
+        imin::SmallArgs s;
+        std::memset(&s, 0, sizeof(s));
+        s.inst = g->d_inst;
+        s.ninst = 1;
+        s.total = theta;
+        s.round = 0;
+        small_shape(s, g->small_launch);
+        s.lt = g->model == IMIN_LT ? 1 : 0;
+        s.next = g->d_sctrl + 0;
+        s.spill_j = sj;
+        s.spill_count = g->d_sctrl + 1;
+        s.error = g->d_ctrl + 3;
+        if (!ok(imin::launch_decrease_small(s, small_grid(g->num_cus, g->small_launch), st)))
+            return IMIN_EDEVICE;
+        list = sj;
+        list_count = g->d_sctrl + 1;
+    }
     LargeTarget t{g->d_thr4, s_set, (int32_t)nseeds, reinterpret_cast<unsigned long long *>(d_counts),
-                  g->d_stats, g->d_ctrl, ovf, &main_ws, &big_ws};
-    rc = launch_large_on(g, t, theta, seed, sj, g->d_sctrl + 1, false);
+                  g->d_stats, g->d_ctrl, ovf, &main_ws, &big_ws, &main_tw, &big_tw};
+    rc = launch_large_on(g, t, theta, seed, list, list_count, false);
     if (rc) return rc;
 
     // Leave the graph's thresholds as created.
-    if (!ok(imin::launch_mask_list(thr, orig, g->d_in_ptr, g->d_in_edge, s_set, (int32_t)nseeds,
+    if (!ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge, s_set, (int32_t)nseeds,
                                    1, st)))
         return IMIN_EDEVICE;
     if (blocked) {
-        hipLaunchKernelGGL(mask_marked_kernel, dim3(grid_of(n)), dim3(kBlock), 0, st, thr, orig,
+        hipLaunchKernelGGL(mask_marked_kernel, dim3(grid_of(n)), dim3(kBlock), 0, st, thr, g->mask_rec(), orig,
                            g->d_in_ptr, g->d_in_edge, marks, (int32_t)n, 1);
         if (!ok(hipGetLastError())) return IMIN_EDEVICE;
     }

@@ -74,16 +74,19 @@ __global__ void argmax_partial_kernel(const unsigned long long *D, const uint32_
 }
 
 // Threshold 0 for every in-edge of v, by the threads of one workgroup.
-__device__ __forceinline__ void mask_in_edges(uint32_t *thr, const int32_t *in_ptr,
+__device__ __forceinline__ void mask_in_edges(uint32_t *thr, uint4 *rec, const int32_t *in_ptr,
                                               const int32_t *in_edge, int v)
 {
-    for (int32_t k = in_ptr[v] + threadIdx.x; k < in_ptr[v + 1]; k += blockDim.x)
-        thr[in_edge[k]] = 0u;
+    for (int32_t k = in_ptr[v] + threadIdx.x; k < in_ptr[v + 1]; k += blockDim.x) {
+        const int32_t e = in_edge[k];
+        thr[e] = 0u;
+        if (rec) rec[e].w = 0u;
+    }
 }
 
 __global__ void argmax_final_kernel(const unsigned long long *part_d, const int32_t *part_i,
                                     int32_t parts, uint32_t *inelig, uint32_t *cand, int32_t *B,
-                                    int32_t slot, int32_t *out_x, uint32_t *thr,
+                                    int32_t slot, int32_t *out_x, uint32_t *thr, uint4 *rec,
                                     const int32_t *in_ptr, const int32_t *in_edge)
 {
     unsigned long long bd = 0;
@@ -98,7 +101,7 @@ __global__ void argmax_final_kernel(const unsigned long long *part_d, const int3
         }
         *out_x = bi;
     }
-    if (bi >= 0) mask_in_edges(thr, in_ptr, in_edge, bi);
+    if (bi >= 0) mask_in_edges(thr, rec, in_ptr, in_edge, bi);
 }
 
 __global__ void set_bit_kernel(uint32_t *bits, int32_t v, int value)
@@ -108,7 +111,7 @@ __global__ void set_bit_kernel(uint32_t *bits, int32_t v, int value)
 }
 
 // In-edge thresholds of list[blockIdx.x ...] (grid-stride over the list): 0, or restored.
-__global__ void mask_list_kernel(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+__global__ void mask_list_kernel(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                                  const int32_t *in_edge, const int32_t *list, int32_t count,
                                  int restore)
 {
@@ -116,12 +119,14 @@ __global__ void mask_list_kernel(uint32_t *thr, const uint32_t *thr_orig, const 
         const int32_t v = list[i];
         for (int32_t k = in_ptr[v] + threadIdx.x; k < in_ptr[v + 1]; k += kSelBlock) {
             const int32_t e = in_edge[k];
-            thr[e] = restore ? thr_orig[e] : 0u;
+            const uint32_t t = restore ? thr_orig[e] : 0u;
+            thr[e] = t;
+            if (rec) rec[e].w = t;
         }
     }
 }
 
-__global__ void mask_vertex_kernel(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+__global__ void mask_vertex_kernel(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                                    const int32_t *in_edge, int32_t v, const int32_t *v_dev,
                                    int restore)
 {
@@ -130,7 +135,9 @@ __global__ void mask_vertex_kernel(uint32_t *thr, const uint32_t *thr_orig, cons
     for (int64_t k = in_ptr[x] + blockIdx.x * (int64_t)kSelBlock + threadIdx.x; k < in_ptr[x + 1];
          k += (int64_t)gridDim.x * kSelBlock) {
         const int32_t e = in_edge[k];
-        thr[e] = restore ? thr_orig[e] : 0u;
+        const uint32_t t = restore ? thr_orig[e] : 0u;
+        thr[e] = t;
+        if (rec) rec[e].w = t;
     }
 }
 
@@ -235,7 +242,7 @@ __global__ void batch_argmax_apply_kernel(const InstanceDesc *inst,
         }
     }
     __syncthreads();
-    if (s_go) mask_in_edges(reinterpret_cast<uint32_t *>(I.thr4), I.in_ptr, I.in_edge, bi);
+    if (s_go) mask_in_edges(reinterpret_cast<uint32_t *>(I.thr4), I.rec, I.in_ptr, I.in_edge, bi);
 }
 
 // One workgroup per instance in GreedyReplace's replacement pass: unblock the blocker u of
@@ -250,8 +257,11 @@ __global__ void batch_gr_prepare_kernel(const InstanceDesc *inst, int32_t round)
     if (threadIdx.x == 0) I.inelig[u >> 5] &= ~(1u << (u & 31));
     uint32_t *thr = reinterpret_cast<uint32_t *>(I.thr4);
     const uint32_t *orig = reinterpret_cast<const uint32_t *>(I.thr_orig);
-    for (int32_t k = I.in_ptr[u] + threadIdx.x; k < I.in_ptr[u + 1]; k += kSelBlock)
-        thr[I.in_edge[k]] = orig[I.in_edge[k]];
+    for (int32_t k = I.in_ptr[u] + threadIdx.x; k < I.in_ptr[u + 1]; k += kSelBlock) {
+        const int32_t e = I.in_edge[k];
+        thr[e] = orig[e];
+        if (I.rec) I.rec[e].w = orig[e];
+    }
 }
 
 __global__ void batch_done_kernel(const InstanceDesc *inst, int32_t ninst, uint32_t *out)
@@ -277,16 +287,22 @@ __global__ void batch_setup_kernel(const InstanceDesc *inst, const BatchStage *s
     uint32_t *thr = reinterpret_cast<uint32_t *>(I.thr4);
     const uint32_t *orig = reinterpret_cast<const uint32_t *>(I.thr_orig);
     if (S.nprev < 0) {
-        for (int64_t e = threadIdx.x; e < (int64_t)I.nquads * 4; e += kSelBlock) thr[e] = orig[e];
+        for (int64_t e = threadIdx.x; e < (int64_t)I.nquads * 4; e += kSelBlock) {
+            thr[e] = orig[e];
+            if (I.rec) I.rec[e].w = orig[e];
+        }
     } else {
         for (int32_t i = 0; i < S.nprev; ++i) {
             const int32_t v = stage[S.prev + i];
-            for (int32_t k = I.in_ptr[v] + threadIdx.x; k < I.in_ptr[v + 1]; k += kSelBlock)
-                thr[I.in_edge[k]] = orig[I.in_edge[k]];
+            for (int32_t k = I.in_ptr[v] + threadIdx.x; k < I.in_ptr[v + 1]; k += kSelBlock) {
+                const int32_t e = I.in_edge[k];
+                thr[e] = orig[e];
+                if (I.rec) I.rec[e].w = orig[e];
+            }
         }
     }
     __syncthreads();
-    for (int32_t i = 0; i < S.nnow; ++i) mask_in_edges(thr, I.in_ptr, I.in_edge, stage[S.now + i]);
+    for (int32_t i = 0; i < S.nnow; ++i) mask_in_edges(thr, I.rec, I.in_ptr, I.in_edge, stage[S.now + i]);
 }
 
 __global__ void batch_gather_kernel(const InstanceDesc *inst, const int32_t *rounds, int32_t *out,
@@ -333,7 +349,7 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t count, uint32_t value, hipStream
 hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits, int mode,
                                int32_t n, unsigned long long *part_d, int32_t *part_i,
                                int32_t parts, uint32_t *inelig, uint32_t *cand, int32_t *B,
-                               int32_t slot, int32_t *out_x, uint32_t *thr,
+                               int32_t slot, int32_t *out_x, uint32_t *thr, uint4 *rec,
                                const int32_t *in_ptr, const int32_t *in_edge,
                                hipStream_t stream)
 {
@@ -344,7 +360,7 @@ hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(argmax_final_kernel, dim3(1), dim3(kSelBlock), 0, stream, part_d, part_i, g,
-                       inelig, cand, B, slot, out_x, thr, in_ptr, in_edge);
+                       inelig, cand, B, slot, out_x, thr, rec, in_ptr, in_edge);
     return hipGetLastError();
 }
 
@@ -354,21 +370,21 @@ hipError_t launch_set_bit(uint32_t *bits, int32_t v, int value, hipStream_t stre
     return hipGetLastError();
 }
 
-hipError_t launch_mask_list(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+hipError_t launch_mask_list(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                             const int32_t *in_edge, const int32_t *list, int32_t count,
                             int restore, hipStream_t stream)
 {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(mask_list_kernel, dim3(std::min<int32_t>(count, 4096)), dim3(kSelBlock), 0,
-                       stream, thr, thr_orig, in_ptr, in_edge, list, count, restore);
+                       stream, thr, rec, thr_orig, in_ptr, in_edge, list, count, restore);
     return hipGetLastError();
 }
 
-hipError_t launch_mask_vertex(uint32_t *thr, const uint32_t *thr_orig, const int32_t *in_ptr,
+hipError_t launch_mask_vertex(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                               const int32_t *in_edge, int32_t v, const int32_t *v_dev,
                               int restore, hipStream_t stream)
 {
-    hipLaunchKernelGGL(mask_vertex_kernel, dim3(16), dim3(kSelBlock), 0, stream, thr, thr_orig,
+    hipLaunchKernelGGL(mask_vertex_kernel, dim3(16), dim3(kSelBlock), 0, stream, thr, rec, thr_orig,
                        in_ptr, in_edge, v, v_dev, restore);
     return hipGetLastError();
 }

@@ -189,6 +189,11 @@ void carve(imin_server *s, Query &q)
     I.nseeds = (int32_t)q.seeds.size();
     I.n = g->n;
     I.nquads = (int32_t)quads;
+    I.nclaim = g->nclaim;
+    I.nreach = g->nreach;
+    I.tedge = g->d_tedge;
+    I.code = g->d_code;
+    I.rid_vtx = g->d_rid_vtx;
     I.theta = q.theta;
     I.gr_k = q.mode == IMIN_GR ? q.nb : -1;
     I.step = 0;
@@ -375,7 +380,9 @@ int imin_server_create(imin_graph *g, const imin_server_config *cfg, imin_server
         server_free(s);
         return IMIN_ENOMEM;
     }
-    int rc = multi_alloc(s->ms, g->num_cus, g->n, g->m, (uint32_t)c.max_active * c.max_theta,
+    MultiSize size;
+    size.add(g);
+    int rc = multi_alloc(s->ms, g->num_cus, size, (uint32_t)c.max_active * c.max_theta,
                          c.max_active, s->stream);
     size_t cap = 0;
     if (!rc) rc = ensure_dev(s->d_table, cap, (size_t)c.max_active);

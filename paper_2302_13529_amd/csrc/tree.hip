@@ -1,0 +1,1064 @@
+// tree.hip -- Algorithm 2 of arXiv 2302.13529 on gfx950, one workgroup per sample, with every
+// claim made in LDS.
+//
+// What bounds it. Measured on MI355X, random accesses of 64-lane waves: 32- and 64-bit atomics
+// on global memory run at 17-28 G lanes/s whatever level of the memory holds the line (17.5
+// over 17 GB, 27 inside L2); loads that miss L2 at 49 G lines/s from HBM and 55 from the
+// memory-side cache, a limit that 150 lines in flight per compute unit already reach; L2 hits
+// at hundreds of G. So the kernel keeps atomics off global memory wherever a sample's size
+// multiplies them, and then counts lines:
+//   * claims. A vertex needs a claim only when it has two or more in-edges; those vertices
+//     are numbered densely (reach ids below nclaim), and the sample's visited set is a bitmap
+//     of nclaim bits in LDS (141 KB of 160 for a 4M-vertex R-MAT graph with 35M edges). A
+//     vertex with one in-edge can only be reached through it. Under the linear-threshold
+//     model (Section V-E) every vertex has at most one live in-edge, so nothing is ever
+//     claimed twice and there is no bitmap at all;
+//   * thresholds. The first test of a coin reads a byte per edge (threshold_code); only the
+//     edges that pass, about 6 % more than are live, cost a 16-byte record, which holds the
+//     exact threshold, the target's reach id and its row range;
+//   * order. A wave's live edges pass through an LDS queue in frontier order, so a batch of 64
+//     is claimed with every lane at work, a parent's children get consecutive local ids and
+//     the local arrays are written in full lines. Waves take chunks of the frontier and need
+//     no barrier until the level ends;
+//   * subtree sizes. With consecutive children, sizes are summed over runs of equal parents
+//     inside a wave; only runs that may go on elsewhere and the few vertices whose dominator
+//     is not their BFS parent use atomics;
+//   * counts. A reached vertex's own 1 goes into bit-sliced per-slot counters, one pass over
+//     the bitmap per sample; only subtree sizes above 1 are added into D with atomics.
+// Against the kernel of decrease.hip (a 64-bit global atomic per claim): 5000 samples of that
+// R-MAT graph, 370k vertices each, 277 -> 167 ms (L2 misses per reached vertex 7.1 -> 3.1);
+// 10,000 samples of a 131k-vertex one 17.3 -> 8.3 ms; linear threshold, 1000 samples of a
+// 1M-vertex one, 298k vertices each, 53 -> 36 ms.
+//
+// The dominator tree (Section V-B3) comes from raising the BFS tree: t(v) <- NCA_t of t(v) and
+// v's reached predecessors, in place and in any order, until a whole pass changes nothing.
+// Why unordered, unsynchronised passes are right: (1) every value t(v) ever holds is dominated
+// by (or is) each strict dominator d of v. A walk from a predecessor of v never passes such a
+// d without standing on it, because a strict dominator of a vertex x is on or above every
+// value t(x) ever held; and of two walkers, one on d and one below, the one below moves (its
+// BFS index is larger). So the NCA found, and hence the new t(v), is on or below d too. (2) A
+// pass that stores anything for v stores only values above the one it read, so t(v) is strictly
+// higher after it, and passes end. (3) In a pass without a store the tree stood still: t(v) is
+// an ancestor of every predecessor of v, the tree paths are a post-fixpoint of the dominator
+// equations, and by (1) they hold every dominator: the tree is the dominator tree.
+#include "imin_internal.h"
+#include "philox.h"
+#include "wave.h"
+
+#include <algorithm>
+#include <cstddef>
+
+namespace imin {
+namespace {
+
+using namespace wave;
+
+constexpr int kItems = 2;        // items in flight per lane
+constexpr int kRing = 128;       // a wave's queue of live edges: at most 63 wait for company
+constexpr int kHeavy = 128;      // a row of more items is shared by all waves,
+constexpr int kPart = 256;       // in parts of that many
+constexpr int kHeavyCap = 256;
+
+// LDS of a workgroup of B threads ahead of its bitmap.
+template <int B>
+struct TreeHead {
+    // one set of level counters in use, one being cleared, one being read (by level mod 3)
+    int chunk[3];     // next chunk of the level's frontier
+    int grown[3];     // vertices the level has claimed
+    int nheavy[3];
+    uint32_t idx;
+    int nextra;
+    int changed;
+    // behind here: the BFS; with the bitmap, free after it
+    int heavy[3][B > 64 ? kHeavyCap : 1];  // row start, row end, source
+    uint32_t qe[B / 64][kRing];       // live edge
+    int qs[B / 64][kRing];            // its source's local id
+    uint8_t mark[B / 64][64 * kItems];        // a wave's round: the rows that begin at its items
+};
+
+template <int B>
+__host__ __device__ constexpr size_t head_bytes()
+{
+    return (sizeof(TreeHead<B>) + 15) / 16 * 16;
+}
+
+// Bytes of the head that hold no per-sample scalars: reused by the dominator steps.
+template <int B>
+__host__ __device__ constexpr size_t free_offset()
+{
+    return offsetof(TreeHead<B>, heavy);
+}
+
+struct TreeCall {
+    const int32_t *row_ptr;
+    const uint4 *edge;
+    const uint32_t *code;
+    const uint4 *thr4;
+    const uint4 *tl;
+    const int32_t *seeds;
+    const int32_t *rid_vtx;
+    int32_t nseeds;
+    int32_t nclaim, nreach;
+    uint32_t key_lo, key_hi;
+    unsigned long long *D;
+    unsigned long long *stats;
+};
+
+// Thresholds in a byte. A coin below a threshold t has a value of at most t - 1, and so has its
+// code: the exponent and the three leading mantissa bits of the value as a float, which grow
+// with it. An edge whose coin passes this test (about 6 % more than are live) is decided by
+// the exact threshold in its record. Rows are 21 edges long on average where it matters, so
+// the byte array is a quarter of the lines, and a level's hub rows stay in L2.
+__device__ __forceinline__ int coin_code(uint32_t coin)
+{
+    return (int)(__float_as_uint((float)coin) >> 20) - 1015;
+}
+
+__device__ __forceinline__ uint32_t threshold_code(uint32_t thr)
+{
+    return thr == 0u ? 0u : (uint32_t)max(1, coin_code(thr - 1u));
+}
+
+struct TreeSlot {
+    int2 *rng;
+    int32_t *dom, *rid, *par, *acc, *lvl, *lid;
+    int4 *extra;
+    uint32_t *planes;
+};
+
+// A wave-uniform value in scalar registers.
+template <class T>
+__device__ __forceinline__ T scalar(T v)
+{
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_readfirstlane((int)v);
+    } else {
+        const unsigned long long x = (unsigned long long)v;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+        return (T)(((unsigned long long)hi << 32) | lo);
+    }
+}
+
+template <class T>
+__device__ __forceinline__ T ld(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class T>
+__device__ __forceinline__ void st(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Nearest common ancestor of x and y in the tree t (larger index walks up). Vertices below
+// `deep` are children of the root: a walk that gets there needs no more loads.
+template <class T>
+__device__ __forceinline__ int tree_nca(const T *t, int deep, int x, int y)
+{
+    while (x != y) {
+        if (x > y) x = x < deep ? 0 : (int)ld(&t[x]);
+        else y = y < deep ? 0 : (int)ld(&t[y]);
+    }
+    return x;
+}
+
+// Inclusive running maximum of non-negative values across the wave, as wave_scan.
+__device__ __forceinline__ int wave_scan_max(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+
+// A wave's queue of live edges, in frontier order: a ring in LDS.
+struct WaveQueue {
+    uint32_t *qe;
+    int *qs;
+    int head, n;  // uniform
+};
+
+// What the waves of a workgroup share while one level is expanded.
+struct Level {
+    int base;      // local id of the level's first claim
+    int *grown;
+    int *nextra;
+    bool shared;   // the rows at hand are shared with other waves
+};
+
+// The first k (at most 64) queued edges: claim their targets. The winners get consecutive
+// local ids in queue order, so equal parents are adjacent; a run of equal parents that may
+// go on in another batch (the first, the last, any of a shared row) is marked (sign of acc).
+template <bool kLT>
+__device__ __forceinline__ void consume(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv,
+                                        uint32_t *bm, const Level &lv, WaveQueue &q, int k,
+                                        uint32_t j, uint32_t &live)
+{
+    const int lane = lane_id();
+    bool has = lane < k;
+    uint4 r = make_uint4(0, 0, 0, 0);
+    int from = 0;
+    uint32_t e = 0;
+    if (has) {
+        const int at = (q.head + lane) & (kRing - 1);
+        e = q.qe[at];
+        r = c.edge[e];
+        from = q.qs[at];
+    }
+    if (!kLT) {
+        uint32_t k0 = c.key_lo, k1 = c.key_hi, w0, w1, w2, w3;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        philox4x32_10(e >> 2, j, k0, k1, w0, w1, w2, w3);
+        const uint32_t w = (e & 2) ? ((e & 1) ? w3 : w2) : ((e & 1) ? w1 : w0);
+        has = has && (w >> 8) < r.w;
+    }
+    live += has ? 1u : 0u;
+    bool won = has;
+    if (!kLT && has && r.z < (uint32_t)c.nclaim) {
+        const uint32_t bit = 1u << (r.z & 31);
+        won = (atomicOr(&bm[r.z >> 5], bit) & bit) == 0u;
+        // another live edge into a reached vertex; edges from the merged seed never matter for
+        // dominators (their targets are its children)
+        if (!won && from != 0 && !a.reach_only) {
+            const int x = atomicAdd(lv.nextra, 1);
+            if (x < a.ws.xcap) sv.extra[x] = make_int4(from, (int)r.z, 0, 0);
+        }
+    }
+    const unsigned long long b = __ballot(won);
+    if (b) {
+        const int wins = __builtin_popcountll(b);
+        int first = 0;
+        if (lane == 0) first = atomicAdd(lv.grown, wins);
+        first = lv.base + __builtin_amdgcn_readfirstlane(first);
+        const int id = first + __builtin_popcountll(b & ((1ull << lane) - 1ull));
+        const int p0 = __builtin_amdgcn_readlane(from, __builtin_ctzll(b));
+        const int p1 = __builtin_amdgcn_readlane(from, 63 - __builtin_clzll(b));
+        if (won) {
+            sv.rng[id] = make_int2((int)r.x, (int)r.y);
+            if (!a.reach_only) {
+                sv.rid[id] = (int)r.z;
+                sv.par[id] = from;
+                sv.acc[id] = lv.shared || from == p0 || from == p1 ? (int)0x80000000 : 0;
+            }
+        }
+    }
+    q.head = (q.head + k) & (kRing - 1);
+    q.n -= k;
+}
+
+// Items in flight per lane: edge quads (independent cascade: one Philox block decides 4
+// edges), or edges (linear threshold: a block per edge, keyed by its target).
+template <bool kLT>
+struct Items {
+    static constexpr int N = kItems;
+    int at[N];         // quad, or edge
+    int src[N];        // local id of the row's vertex
+    uint32_t ok[N];    // quad: its edges inside the row; edge: 1 inside
+    uint32_t code[kLT ? 1 : N];
+    uint32_t hi[kLT ? N : 1], lo[kLT ? N : 1], tgt[kLT ? N : 1];
+};
+
+template <bool kLT>
+__device__ __forceinline__ void load_items(const TreeCall &c, Items<kLT> &it)
+{
+#pragma unroll
+    for (int u = 0; u < Items<kLT>::N; ++u) {
+        if constexpr (kLT) {
+            it.hi[u] = it.lo[u] = it.tgt[u] = 0;
+            if (it.ok[u]) {
+                const uint32_t *thr = reinterpret_cast<const uint32_t *>(c.thr4);
+                const uint32_t *tl = reinterpret_cast<const uint32_t *>(c.tl);
+                const size_t e = (size_t)it.at[u];
+                it.hi[u] = thr[e];
+                it.tgt[u] = tl[((e >> 2) << 3) + (e & 3)];
+                it.lo[u] = tl[((e >> 2) << 3) + (e & 3) + 4];
+            }
+        } else {
+            it.code[u] = 0;
+            if (it.ok[u]) it.code[u] = c.code[it.at[u]];
+        }
+    }
+}
+
+// The items' live edges (independent cascade: those that pass the test of the codes).
+template <bool kLT>
+__device__ __forceinline__ void decide(const TreeCall &c, const Items<kLT> &it, uint32_t j,
+                                       uint32_t (&m)[Items<kLT>::N])
+{
+    // opaque here, so that the ten round keys are added up where they are used instead of
+    // being kept in twenty scalar registers (the loop around this would spill them)
+    uint32_t k0 = c.key_lo, k1 = c.key_hi;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+#pragma unroll
+    for (int u = 0; u < Items<kLT>::N; ++u) {
+        if constexpr (kLT) {
+            const uint32_t r = vertex_choice(it.tgt[u], j, k0, k1);
+            m[u] = (r >= it.lo[u] && r < it.hi[u]) ? 1u : 0u;
+        } else {
+            uint32_t w0, w1, w2, w3;
+            philox4x32_10((uint32_t)it.at[u], j, k0, k1, w0, w1, w2, w3);
+            const uint32_t t = it.code[u];
+            m[u] = ((coin_code(w0 >> 8) <= (int)(t & 0xFFu) ? 1u : 0u) |
+                    (coin_code(w1 >> 8) <= (int)((t >> 8) & 0xFFu) ? 2u : 0u) |
+                    (coin_code(w2 >> 8) <= (int)((t >> 16) & 0xFFu) ? 4u : 0u) |
+                    (coin_code(w3 >> 8) <= (int)(t >> 24) ? 8u : 0u)) & it.ok[u];
+        }
+    }
+}
+
+// Append the items' edges to the queue in order; full batches are consumed.
+template <bool kLT>
+__device__ __forceinline__ void enqueue(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv,
+                                        uint32_t *bm, const Level &lv, WaveQueue &q,
+                                        const int (&at)[Items<kLT>::N],
+                                        const int (&src)[Items<kLT>::N],
+                                        uint32_t (&m)[Items<kLT>::N], uint32_t j,
+                                        uint32_t &live)
+{
+    constexpr int N = Items<kLT>::N;
+    // positions by item number, then lane: at most 256 of each number, two counts in a word
+    int pos[N];
+    int found = 0;
+#pragma unroll
+    for (int u = 0; u < N; u += 2) {
+        const int c0 = __builtin_popcount(m[u]), c1 = __builtin_popcount(m[u + 1]);
+        const int incl = wave_scan(c0 | (c1 << 16));
+        const int tot = __builtin_amdgcn_readlane(incl, 63);
+        pos[u] = found + (incl & 0xFFFF) - c0;
+        found += tot & 0xFFFF;
+        pos[u + 1] = found + (incl >> 16) - c1;
+        found += tot >> 16;
+    }
+    int done = 0;
+    while (done < found) {
+        const int room = min(found - done, kRing - q.n);
+        const int off = q.head + q.n - done;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            while (m[u] && pos[u] < done + room) {
+                const int i = __builtin_ctz(m[u]);
+                m[u] &= m[u] - 1;
+                const int slot = (off + pos[u]) & (kRing - 1);
+                q.qe[slot] = (uint32_t)(kLT ? at[u] : (at[u] << 2) + i);
+                q.qs[slot] = src[u];
+                ++pos[u];
+            }
+        }
+        wave_sync();
+        q.n += room;
+        done += room;
+        while (q.n >= 64) consume<kLT>(a, c, sv, bm, lv, q, 64, j, live);
+        wave_sync();
+    }
+}
+
+// Expand one level, the frontier [lo, hi): the seeds (source: the merged seed, local id 0) or
+// local ids. Waves take chunks of the frontier, at most 64 vertices, from the level's counter
+// and need no barrier until the level ends: claims and local ids are LDS atomics. A row of
+// more than kHeavy items is left to a second pass in which all waves share it. Returns the
+// number of vertices claimed.
+template <int B, bool kLT>
+__device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c,
+                                            const TreeSlot &sv, TreeHead<B> &sh, uint32_t *bm,
+                                            bool from_seeds, int lo, int hi, int base, int lset,
+                                            uint32_t j, uint32_t &scanned, uint32_t &live)
+{
+    constexpr int W = B / 64;
+    constexpr int N = Items<kLT>::N;
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Level lv{base, &sh.grown[lset], &sh.nextra, false};
+    WaveQueue q{sh.qe[wid], sh.qs[wid], 0, 0};
+    uint8_t *mark = sh.mark[wid];
+    // at least four chunks a wave, so that the level's waves end together
+    const int csz = max(8, min(64, (hi - lo) / (4 * W)));
+    int nh = -1;            // heavy rows of the level, once the first pass is over
+    int h = 0, part = wid;  // this wave's next part of them: parts go round the waves
+    // the rows at hand, one a lane: [e0, e1), items before them; the first lane's source
+    int e0 = 0, e1 = 0, pre = 0, items = 0, total = 0, src0 = 0;
+    // The next rows; false when the pass has none left.
+    auto next_rows = [&]() {
+        e0 = e1 = items = 0;
+        if (nh < 0) {
+            int k = 0;
+            if (lane == 0) k = atomicAdd(&sh.chunk[lset], csz);
+            src0 = lo + __builtin_amdgcn_readfirstlane(k);
+            if (src0 >= hi) return false;
+            k = src0 + lane;
+            if (lane < csz && k < hi) {
+                if (from_seeds) {
+                    const int v = c.seeds[k];
+                    e0 = c.row_ptr[v];
+                    e1 = c.row_ptr[v + 1];
+                } else {
+                    const int2 r = sv.rng[k];
+                    e0 = r.x;
+                    e1 = r.y;
+                }
+            }
+            scanned += (uint32_t)(e1 - e0);
+            items = kLT ? e1 - e0 : quads_of(e0, e1);
+            if (W > 1 && items > kHeavy) {
+                const int x = atomicAdd(&sh.nheavy[lset], 1);
+                if (x < kHeavyCap) {
+                    sh.heavy[0][x] = e0;
+                    sh.heavy[1][x] = e1;
+                    sh.heavy[2][x] = k;
+                    items = 0;
+                }
+            }
+        } else {
+            // lane 0 holds the wave's next part of a heavy row
+            int f0 = 0, f1 = 0, parts = 0;
+            for (; h < nh; ++h) {
+                f0 = __builtin_amdgcn_readfirstlane(sh.heavy[0][h]);
+                f1 = __builtin_amdgcn_readfirstlane(sh.heavy[1][h]);
+                parts = ((kLT ? f1 - f0 : quads_of(f0, f1)) + kPart - 1) / kPart;
+                if (part < parts) break;
+                part -= parts;
+            }
+            if (h >= nh) return false;
+            const int first = kLT ? f0 + part * kPart : (f0 & ~3) + part * (4 * kPart);
+            src0 = __builtin_amdgcn_readfirstlane(sh.heavy[2][h]);
+            e0 = max(f0, first);
+            e1 = part + 1 == parts ? f1 : first + (kLT ? kPart : 4 * kPart);
+            items = lane == 0 ? (kLT ? e1 - e0 : quads_of(e0, e1)) : 0;
+            part += W;
+        }
+        const int incl = wave_scan(items);
+        pre = incl - items;
+        total = __builtin_amdgcn_readlane(incl, 63);
+        return true;
+    };
+    // Items sub + 64 u + lane of the rows: each row marks the item it begins at, and a running
+    // maximum over the items gives each its row.
+    auto place = [&](int sub, Items<kLT> &it) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) mark[64 * u + lane] = 0;
+        wave_sync();
+        const bool begins = items > 0 && pre >= sub && pre < sub + 64 * N;
+        if (begins) mark[pre - sub] = (uint8_t)lane;
+        int run = 63 - __builtin_clzll(__ballot(items > 0 && pre <= sub) | 1ull);
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int i = sub + 64 * u + lane;
+            const int l = max(run, wave_scan_max((int)mark[64 * u + lane]));
+            run = __builtin_amdgcn_readlane(l, 63);
+            const int f0 = __shfl(e0, l, 64), f1 = __shfl(e1, l, 64);
+            const int d = i - __shfl(pre, l, 64);
+            it.src[u] = from_seeds ? 0 : src0 + l;
+            if constexpr (kLT) {
+                it.at[u] = f0 + d;
+                it.ok[u] = i < total ? 1u : 0u;
+            } else {
+                const int quad = (f0 >> 2) + d;
+                const int eb = quad << 2;
+                uint32_t ok = 0xFu;
+                if (eb < f0) ok &= 0xFu << ((f0 - eb) & 3);
+                if (eb + 4 > f1) ok &= 0xFu >> ((eb + 4 - f1) & 3);
+                it.at[u] = quad;
+                it.ok[u] = i < total ? ok : 0u;
+            }
+        }
+        wave_sync();
+    };
+    for (;;) {
+        while (next_rows()) {
+            Items<kLT> it;
+            if (total > 0) {
+                place(0, it);
+                load_items<kLT>(c, it);
+            }
+            for (int sub = 0; sub < total; sub += 64 * N) {
+                uint32_t m[N];
+                int ats[N], srcs[N];
+                decide<kLT>(c, it, j, m);
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    ats[u] = it.at[u];
+                    srcs[u] = it.src[u];
+                }
+                // the next round's loads go out before this round's edges are followed
+                if (sub + 64 * N < total) {
+                    place(sub + 64 * N, it);
+                    load_items<kLT>(c, it);
+                }
+                enqueue<kLT>(a, c, sv, bm, lv, q, ats, srcs, m, j, live);
+            }
+        }
+        if (q.n > 0) {
+            consume<kLT>(a, c, sv, bm, lv, q, q.n, j, live);
+            wave_sync();
+        }
+        __syncthreads();
+        if (W == 1 || nh >= 0) break;
+        nh = __builtin_amdgcn_readfirstlane(min(sh.nheavy[lset], kHeavyCap));
+        if (nh == 0) break;
+        lv.shared = true;
+    }
+    // the counters of the level before last: every wave is past reading them, and none
+    // touches them again before the next level's barrier
+    const int grown = sh.grown[lset];
+    if (threadIdx.x == 0) {
+        const int old = lset == 0 ? 2 : lset - 1;
+        sh.chunk[old] = sh.grown[old] = sh.nheavy[old] = 0;
+    }
+    return grown;
+}
+
+// Add the set bits of bm[0..n) into the words of the slot's bit-sliced counters from w0 on.
+template <int B>
+__device__ __forceinline__ void plane_add(uint32_t *planes, int64_t words, int64_t w0,
+                                          const uint32_t *bm, int n)
+{
+    for (int w = threadIdx.x; w < n; w += 4 * B) {
+        uint32_t x[4], o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = w + u * B < n ? bm[w + u * B] : 0u;
+            o[u] = x[u] ? planes[w0 + w + u * B] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (!x[u]) continue;
+            uint32_t *at = planes + w0 + w + u * B;
+            *at = o[u] ^ x[u];
+            uint32_t carry = o[u] & x[u];
+            for (int p = 1; p < kTreePlanes && carry; ++p) {
+                at += words;
+                const uint32_t v = *at;
+                *at = v ^ carry;
+                carry &= v;
+            }
+        }
+    }
+}
+
+// The slot's bit-sliced counters into D with atomics, and back to zero (a slot that has
+// counted as many samples as its planes hold).
+template <int B>
+__device__ void planes_drain(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv)
+{
+    const int64_t words = a.ws.words;
+    for (int64_t w = threadIdx.x; w < words; w += B) {
+        uint32_t p[kTreePlanes], any = 0;
+#pragma unroll
+        for (int i = 0; i < kTreePlanes; ++i) {
+            p[i] = sv.planes[i * words + w];
+            any |= p[i];
+        }
+        if (!any) continue;
+#pragma unroll
+        for (int i = 0; i < kTreePlanes; ++i) sv.planes[i * words + w] = 0u;
+        while (any) {
+            const int b = __builtin_ctz(any);
+            any &= any - 1;
+            uint32_t v = 0;
+#pragma unroll
+            for (int i = 0; i < kTreePlanes; ++i) v |= ((p[i] >> b) & 1u) << i;
+            atomicAdd(&c.D[c.rid_vtx[w * 32 + b]], (unsigned long long)v);
+        }
+    }
+}
+
+// kMulti: every sample of the launch's list names its instance.
+template <bool kMulti, bool kLT, int B>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(kTreeWaves, kTreeWaves)))
+void tree_kernel(TreeArgs a)
+{
+    extern __shared__ __align__(16) unsigned char dyn[];
+    TreeHead<B> &sh = *reinterpret_cast<TreeHead<B> *>(dyn);
+    uint32_t *bm = reinterpret_cast<uint32_t *>(dyn + head_bytes<B>());
+    const int tid = threadIdx.x, lane = lane_id();
+    const size_t slot = blockIdx.x;
+    TreeSlot sv;
+    sv.rng = a.ws.rng + slot * (size_t)a.ws.lcap;
+    sv.dom = a.ws.dom + slot * (size_t)a.ws.lcap;
+    sv.rid = a.ws.rid + slot * (size_t)a.ws.lcap;
+    sv.par = a.ws.par + slot * (size_t)a.ws.lcap;
+    sv.acc = a.ws.acc + slot * (size_t)a.ws.lcap;
+    sv.lvl = a.ws.lvl + slot * (size_t)(a.ws.lcap + 1);
+    sv.extra = a.ws.extra + slot * (size_t)a.ws.xcap;
+    sv.lid = a.ws.lid + slot * (size_t)a.ws.nclaim;
+    sv.planes = a.ws.planes + slot * (size_t)(kTreePlanes * a.ws.words);
+    const uint32_t count = a.sample_list ? *a.sample_count : a.theta;
+    // samples whose dominator and size steps run in LDS: 6 bytes a vertex over everything
+    // behind the scalars
+    unsigned char *const over = dyn + free_offset<B>();
+    const int lds_v = min(65535, (int)((a.lds_bytes - free_offset<B>()) / 6));
+
+    uint32_t counted = 0;  // samples in the slot's planes
+    unsigned long long t_samples = 0, t_reached = 0, t_scanned = 0, t_live = 0;
+    uint32_t cur = 0xFFFFFFFFu;
+    TreeCall c{a.row_ptr, a.edge, a.code, a.thr4, a.tl, a.seeds, a.rid_vtx, a.nseeds, a.nclaim,
+               a.nreach, a.key_lo, a.key_hi, a.D, a.stats};
+
+    auto flush_stats = [&]() {
+        const unsigned long long sc = t_scanned, lv = t_live;
+        unsigned long long s1 = sc, s2 = lv;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            s1 += __shfl_xor(s1, o, 64);
+            s2 += __shfl_xor(s2, o, 64);
+        }
+        if (lane == 0) {
+            if (s1) atomicAdd(&c.stats[2], s1);
+            if (s2) atomicAdd(&c.stats[3], s2);
+        }
+        if (tid == 0 && t_samples) {
+            atomicAdd(&c.stats[0], t_samples);
+            atomicAdd(&c.stats[1], t_reached);
+        }
+        t_samples = t_reached = t_scanned = t_live = 0;
+    };
+
+    for (;;) {
+        if (tid == 0) {
+            sh.idx = atomicAdd(a.next, 1u);
+            sh.nextra = 0;
+            for (int i = 0; i < 3; ++i) sh.chunk[i] = sh.grown[i] = sh.nheavy[i] = 0;
+        }
+        __syncthreads();
+        const uint32_t idx = sh.idx;
+        if (idx >= count) break;
+        const uint32_t j = a.sample_list ? a.sample_list[idx] : idx;
+        if (kMulti) {
+            const uint32_t i = __builtin_amdgcn_readfirstlane(a.sample_inst[idx]);
+            if (i != cur) {
+                if (cur != 0xFFFFFFFFu) flush_stats();
+                cur = i;
+                const InstanceDesc &I = a.inst[i];
+                const unsigned long long key =
+                    (((unsigned long long)I.seed_hi << 32) | I.seed_lo) + a.round;
+                c = TreeCall{scalar(I.row_ptr), scalar(I.tedge), scalar(I.code), scalar(I.thr4),
+                             scalar(I.tl), scalar(I.seeds), scalar(I.rid_vtx),
+                             scalar(I.nseeds), scalar(I.nclaim), scalar(I.nreach), scalar((uint32_t)key),
+                             scalar((uint32_t)(key >> 32)), scalar(I.D), scalar(I.stats)};
+            }
+        }
+        const int cwords = kLT ? 0 : (c.nclaim + 31) >> 5;
+        for (int w = tid; w < cwords; w += B) bm[w] = 0u;
+        if (tid == 0) {
+            sv.lvl[0] = 0;
+            sv.lvl[1] = 1;
+        }
+        __syncthreads();
+
+        uint32_t p_scanned = 0, p_live = 0;
+        int L = 0, lo = 0, hi = c.nseeds, base = 1, lset = 0;
+        do {
+            if (tid == 0 && L > 0) sv.lvl[L + 1] = hi;
+            const int grown = expand_level<B, kLT>(a, c, sv, sh, bm, L == 0, lo, hi, base, lset, j,
+                                                   p_scanned, p_live);
+            lset = lset == 2 ? 0 : lset + 1;
+            lo = base;
+            base += grown;
+            hi = base;
+            ++L;
+        } while (lo < hi);
+        __syncthreads();
+        const int nV = base;
+        const int nX = kLT ? 0 : sh.nextra;
+        if (nX > a.ws.xcap) {
+            // more extra edges than the slot holds: the sample is re-run in large scratch
+            if (tid == 0) {
+                if (a.spill_ok) {
+                    const uint32_t pos = atomicAdd(a.ovf_count, 1u);
+                    a.ovf_list[pos] = j;
+                    if (kMulti) a.ovf_inst[pos] = cur;
+                    atomicAdd(&c.stats[4], 1ull);
+                } else {
+                    atomicOr(a.error, 1u);
+                }
+            }
+            __syncthreads();
+            continue;
+        }
+        t_scanned += p_scanned;
+        t_live += p_live;
+        if (tid == 0) {
+            t_samples += 1;
+            t_reached += (unsigned long long)(nV - 1);
+        }
+        if (a.reach_only || nV == 1) {
+            __syncthreads();
+            continue;
+        }
+
+        // Each reached vertex's own 1. A sample that reaches at least one vertex per two
+        // bitmap words adds its bitmap to the slot's counters (the pass reads every word);
+        // a smaller one leaves its ones to the D atomics below.
+        const bool sliced = !kMulti && a.count_reach && (int64_t)nV * 64 >= c.nreach;
+        if (sliced) {
+            if (counted == kTreePlaneMax) {
+                planes_drain<B>(a, c, sv);
+                counted = 0;
+                __syncthreads();
+            }
+            ++counted;
+            // reach ids below nclaim are in the bitmap already
+            const int64_t full = (int64_t)c.nclaim >> 5;
+            if (!kLT) plane_add<B>(sv.planes, a.ws.words, 0, bm, (int)full);
+            // the others one LDS bitmap at a time; the word that nclaim falls into is shared,
+            // so its claimed bits are carried over
+            const int64_t from = kLT ? 0 : full;
+            for (int64_t r0 = from; r0 < a.ws.words; r0 += a.bm_words) {
+                const int nw = (int)min<int64_t>(a.bm_words, a.ws.words - r0);
+                const uint32_t carry = (!kLT && r0 == full && (c.nclaim & 31)) ? bm[full] : 0u;
+                __syncthreads();
+                for (int w = tid; w < nw; w += B) bm[w] = w == 0 ? carry : 0u;
+                __syncthreads();
+                for (int i = 1 + tid; i < nV; i += 4 * B) {
+                    int r[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) r[u] = sv.rid[min(i + u * B, nV - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int64_t w = (r[u] >> 5) - r0;
+                        if ((kLT || r[u] >= c.nclaim) && w >= 0 && w < nw)
+                            atomicOr(&bm[w], 1u << (r[u] & 31));
+                    }
+                }
+                __syncthreads();
+                plane_add<B>(sv.planes, a.ws.words, r0, bm, nw);
+            }
+            __syncthreads();
+        }
+
+        // Extra edges: the target's reach id -> its local id. Mark the targets in the bitmap,
+        // let each marked vertex leave its local id, then look them up.
+        if (nX > 0) {
+            for (int w = tid; w < cwords; w += B) bm[w] = 0u;
+            __syncthreads();
+            for (int x = tid; x < nX; x += B) {
+                const uint32_t r = (uint32_t)sv.extra[x].y;
+                atomicOr(&bm[r >> 5], 1u << (r & 31));
+            }
+            __syncthreads();
+            for (int i = 1 + tid; i < nV; i += 4 * B) {
+                uint32_t r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r[u] = (uint32_t)sv.rid[min(i + u * B, nV - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (r[u] < (uint32_t)c.nclaim && ((bm[r[u] >> 5] >> (r[u] & 31)) & 1u))
+                        sv.lid[r[u]] = min(i + u * B, nV - 1);
+            }
+            __syncthreads();
+            for (int x = tid; x < nX; x += B) {
+                int4 e = sv.extra[x];
+                e.y = sv.lid[e.y];
+                e.z = sv.par[e.y];
+                sv.extra[x] = e;
+            }
+            __syncthreads();
+        }
+
+        const int deep = sv.lvl[2];
+        if (nV <= lds_v) {
+            int *sz = reinterpret_cast<int *>(over);
+            uint16_t *dom = reinterpret_cast<uint16_t *>(over + 4 * (size_t)nV);
+            for (int i = tid; i < nV; i += B) {
+                dom[i] = i ? (uint16_t)sv.par[i] : (uint16_t)0;
+                sz[i] = 1;
+            }
+            __syncthreads();
+            while (nX > 0) {
+                if (tid == 0) sh.changed = 0;
+                __syncthreads();
+                for (int x = tid; x < nX; x += B) {
+                    const int4 e = sv.extra[x];
+                    const int tv = ld(&dom[e.y]);
+                    if (tv == 0) continue;
+                    const int m = tree_nca(dom, deep, tree_nca(dom, deep, tv, e.x), e.z);
+                    if (m < tv) {
+                        st(&dom[e.y], (uint16_t)m);
+                        sh.changed = 1;
+                    }
+                }
+                __syncthreads();
+                const int ch = sh.changed;
+                __syncthreads();
+                if (!ch) break;
+            }
+            for (int l = L - 1; l >= 1; --l) {
+                const int b0 = sv.lvl[l], b1 = sv.lvl[l + 1];
+                for (int i = b0 + tid; i < b1; i += B) {
+                    const int t = dom[i];
+                    const int size = sz[i];
+                    if (t != 0) atomicAdd(&sz[t], size);
+                    const int add = sliced ? size - 1 : size;
+                    if (add > 0) atomicAdd(&c.D[c.rid_vtx[sv.rid[i]]], (unsigned long long)add);
+                }
+                __syncthreads();
+            }
+        } else {
+            // The tentative dominators take the place of the parents of extra edges' targets
+            // while they are raised; then such a vertex gets its parent back, with the sign
+            // bit set when its dominator differs, which is left in dom[].
+            while (nX > 0) {
+                if (tid == 0) sh.changed = 0;
+                __syncthreads();
+                for (int x = tid; x < nX; x += B) {
+                    const int4 e = sv.extra[x];
+                    const int tv = ld(&sv.par[e.y]);
+                    if (tv == 0) continue;
+                    const int m = tree_nca(sv.par, deep, tree_nca(sv.par, deep, tv, e.x), e.z);
+                    if (m < tv) {
+                        st(&sv.par[e.y], m);
+                        sh.changed = 1;
+                    }
+                }
+                __syncthreads();
+                const int ch = sh.changed;
+                __syncthreads();
+                if (!ch) break;
+            }
+            if (nX > 0) {
+                for (int x = tid; x < nX; x += B) {
+                    const int4 e = sv.extra[x];
+                    sv.extra[x].w = ld(&sv.par[e.y]);
+                }
+                __syncthreads();
+                for (int x = tid; x < nX; x += B) {
+                    const int4 e = sv.extra[x];
+                    if (e.w != e.z) {
+                        st(&sv.par[e.y], e.z | (int)0x80000000);
+                        sv.dom[e.y] = e.w;
+                    }
+                }
+                __syncthreads();
+            }
+            // Subtree sizes, deepest level first. A wave sums the runs of equal parents over 64
+            // vertices. An unmarked run that lies inside them holds all children of its parent
+            // and is the only writer of that sum; a marked or cut one is added with an atomic,
+            // as is a vertex whose dominator is not its parent (that dominator is at least two
+            // levels above, where no run of this level ends).
+            for (int l = L - 1; l >= 1; --l) {
+                const int b0 = sv.lvl[l], b1 = sv.lvl[l + 1];
+                for (int i0 = b0 + (tid & ~63); i0 < b1; i0 += B) {
+                    const int i = i0 + lane;
+                    const bool in = i < b1;
+                    int p = 0, s = 0, t = 0;
+                    if (in) {
+                        p = sv.par[i];
+                        s = ld(&sv.acc[i]);
+                        if (p < 0) t = sv.dom[i];
+                    }
+                    const bool moved = p < 0, shared = s < 0;
+                    p &= 0x7FFFFFFF;
+                    s = in ? (s & 0x7FFFFFFF) + 1 : 0;
+                    if (l > 1) {
+                        const int incl = wave_scan(moved ? 0 : s);
+                        const int pp = __shfl_up(p, 1, 64), pn = __shfl_down(p, 1, 64);
+                        const bool head = in && (lane == 0 || pp != p);
+                        const bool last = in && (i + 1 >= b1 || lane == 63 || pn != p);
+                        const unsigned long long hm = __ballot(head);
+                        const int h = 63 - __builtin_clzll((hm & (~0ull >> (63 - lane))) | 1ull);
+                        const int upto = __shfl(incl, max(h - 1, 0), 64);
+                        if (last) {
+                            const int sum = incl - (h > 0 ? upto : 0);
+                            const bool cut = shared || (h == 0 && i0 > b0) || (lane == 63 && i + 1 < b1);
+                            if (sum > 0) {
+                                if (cut)
+                                    __hip_atomic_fetch_add(&sv.acc[p], sum, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                                else
+                                    st(&sv.acc[p], ld(&sv.acc[p]) + sum);
+                            }
+                        }
+                        if (moved && t != 0)
+                            __hip_atomic_fetch_add(&sv.acc[t], s, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    const int add = sliced ? s - 1 : s;
+                    if (in && add > 0) atomicAdd(&c.D[c.rid_vtx[sv.rid[i]]], (unsigned long long)add);
+                }
+                __syncthreads();
+            }
+        }
+    }
+    if (!kMulti || cur != 0xFFFFFFFFu) flush_stats();
+    if (!kMulti && tid == 0 && a.count_reach) a.ws.used[slot] = counted;
+}
+
+// D[v] += the bit-sliced reach counts of every slot that kept some (used), which go back to 0.
+// A workgroup takes 16 bitmap words (512 reach ids) and shares the slots of its part (grid y)
+// among 16 thread rows; each thread adds its slots' planes into a bit-sliced sum and the rows
+// meet in LDS counters, so D is touched once per vertex and part.
+constexpr int kDrainWords = 16;
+constexpr int kDrainRows = 16;
+constexpr int kDrainBits = 20;  // 63 samples in each of at most 4096 slots
+
+__global__ __launch_bounds__(kDrainWords *kDrainRows) void drain_planes_kernel(
+    uint32_t *planes, const uint32_t *used, int32_t slots, int64_t words, const int32_t *rid_vtx,
+    int32_t nreach, unsigned long long *D)
+{
+    __shared__ uint32_t sum[kDrainWords * 32];
+    const int wd = threadIdx.x % kDrainWords, row = threadIdx.x / kDrainWords;
+    for (int i = threadIdx.x; i < kDrainWords * 32; i += kDrainWords * kDrainRows) sum[i] = 0u;
+    __syncthreads();
+    const int64_t w = (int64_t)blockIdx.x * kDrainWords + wd;
+    uint32_t s[kDrainBits];
+#pragma unroll
+    for (int i = 0; i < kDrainBits; ++i) s[i] = 0u;
+    if (w < words) {
+        for (int32_t sl = blockIdx.y * kDrainRows + row; sl < slots; sl += gridDim.y * kDrainRows) {
+            const uint32_t n = used[sl];
+            if (!n) continue;
+            uint32_t *at = planes + (size_t)sl * kTreePlanes * words + w;
+            uint32_t p[kTreePlanes];
+#pragma unroll
+            for (int i = 0; i < kTreePlanes; ++i) p[i] = (n >> i) ? at[i * words] : 0u;
+            uint32_t carry = 0;
+#pragma unroll
+            for (int i = 0; i < kDrainBits; ++i) {
+                const uint32_t x = i < kTreePlanes ? p[i] : 0u;
+                const uint32_t o = s[i];
+                s[i] = o ^ x ^ carry;
+                carry = (o & x) | (carry & (o ^ x));
+            }
+#pragma unroll
+            for (int i = 0; i < kTreePlanes; ++i)
+                if (p[i]) at[i * words] = 0u;
+        }
+    }
+    for (int b = 0; b < 32; ++b) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int i = 0; i < kDrainBits; ++i) v |= ((s[i] >> b) & 1u) << i;
+        if (v) atomicAdd(&sum[wd * 32 + b], v);
+    }
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * kDrainWords * 32;
+    for (int i = threadIdx.x; i < kDrainWords * 32; i += kDrainWords * kDrainRows)
+        if (sum[i] && r0 + i < nreach) atomicAdd(&D[rid_vtx[r0 + i]], (unsigned long long)sum[i]);
+}
+
+// Per edge: the target's row range, its reach id and the edge's threshold; the threshold's
+// code; and the record without a threshold (target, its row range) of the other kernels. Null
+// outputs are left out.
+__global__ void edge_records_kernel(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
+                                    const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
+                                    uint4 *plain)
+{
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t v = col[e];
+        const uint32_t r0 = (uint32_t)row_ptr[v], r1 = (uint32_t)row_ptr[v + 1];
+        if (edge) edge[e] = make_uint4(r0, r1, (uint32_t)rid[v], thr[e]);
+        if (code) code[e] = (uint8_t)threshold_code(thr[e]);
+        if (plain) plain[e] = make_uint4(v, r0, r1, 0u);
+    }
+}
+
+// Every record's threshold as created.
+__global__ void edge_restore_kernel(const uint32_t *thr, int64_t m, uint4 *edge)
+{
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * blockDim.x)
+        edge[e].w = thr[e];
+}
+
+// The shape with workgroups of B threads, if it has more threads at work on `theta` samples
+// than the best so far.
+template <int B>
+void shape_for(int64_t bits, int64_t theta, int num_cus, TreeShape &best, int64_t &best_threads)
+{
+    const size_t need = head_bytes<B>() + (size_t)((bits + 31) / 32) * 4;
+    if (need > kTreeLds) return;
+    const int wgs = (int)std::min<size_t>(256 * kTreeWaves / B, kTreeLds / need);
+    const int64_t threads = std::min<int64_t>(theta, (int64_t)wgs * num_cus) * B;
+    if (threads <= best_threads) return;
+    best_threads = threads;
+    best.block = B;
+    best.per_cu = wgs;
+    // the whole share: what the bitmap leaves goes to the dominator steps
+    best.lds = (uint32_t)(kTreeLds / wgs / 16 * 16);
+    best.bm_words = (int32_t)((best.lds - head_bytes<B>()) / 4);
+}
+
+template <bool kMulti, bool kLT>
+hipError_t launch_shape(const TreeArgs &a, const TreeShape &s, hipStream_t stream)
+{
+    const dim3 grid(a.ws.slots);
+    void (*k)(TreeArgs) = nullptr;
+    if (s.block == 64) k = tree_kernel<kMulti, kLT, 64>;
+    else if (s.block == 128) k = tree_kernel<kMulti, kLT, 128>;
+    else if (s.block == 256) k = tree_kernel<kMulti, kLT, 256>;
+    else if (s.block == 512) k = tree_kernel<kMulti, kLT, 512>;
+    else k = tree_kernel<kMulti, kLT, 1024>;
+    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)s.lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(k, grid, dim3(s.block), s.lds, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
+                int num_cus, TreeShape &out)
+{
+    int64_t threads = 0;
+    out = TreeShape{};
+    // linear threshold: the bitmap only counts, a part of the reach ids at a time
+    const int64_t cap = (int64_t)(kTreeLds - head_bytes<1024>()) * 8;
+    const int64_t bits = lt ? std::min((nreach + 3) / 4, cap) : nclaim;
+    if (!reach_only) shape_for<512>(bits, theta, num_cus, out, threads);
+    shape_for<64>(bits, theta, num_cus, out, threads);
+    shape_for<128>(bits, theta, num_cus, out, threads);
+    shape_for<256>(bits, theta, num_cus, out, threads);
+    shape_for<512>(bits, theta, num_cus, out, threads);
+    shape_for<1024>(bits, theta, num_cus, out, threads);
+    return threads > 0;
+}
+
+hipError_t launch_tree(const TreeArgs &args, const TreeShape &s, bool lt, hipStream_t stream)
+{
+    if (args.ws.slots <= 0 || s.block == 0) return hipErrorInvalidValue;
+    TreeArgs a = args;
+    a.lds_bytes = s.lds;
+    a.bm_words = s.bm_words;
+    if (a.inst) return lt ? launch_shape<true, true>(a, s, stream) : launch_shape<true, false>(a, s, stream);
+    return lt ? launch_shape<false, true>(a, s, stream) : launch_shape<false, false>(a, s, stream);
+}
+
+hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *rid_vtx,
+                               int32_t nreach, unsigned long long *D, hipStream_t stream)
+{
+    if (slots <= 0 || nreach <= 0) return hipSuccess;
+    const int64_t bx = (ws.words + kDrainWords - 1) / kDrainWords;
+    const int by = (int)std::max<int64_t>(1, std::min<int64_t>(8, 512 / bx));
+    hipLaunchKernelGGL(drain_planes_kernel, dim3((uint32_t)bx, by), dim3(kDrainWords * kDrainRows), 0,
+                       stream, ws.planes, ws.used, slots, ws.words, rid_vtx, nreach, D);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_records(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
+                               const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
+                               uint4 *plain, hipStream_t stream)
+{
+    if (m <= 0) return hipSuccess;
+    const int grid = (int)std::min<int64_t>(8192, (m + 255) / 256);
+    hipLaunchKernelGGL(edge_records_kernel, dim3(grid), dim3(256), 0, stream, col, row_ptr, rid, thr,
+                       m, edge, code, plain);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_restore(const uint32_t *thr, int64_t m, uint4 *edge, hipStream_t stream)
+{
+    if (m <= 0) return hipSuccess;
+    const int grid = (int)std::min<int64_t>(8192, (m + 255) / 256);
+    hipLaunchKernelGGL(edge_restore_kernel, dim3(grid), dim3(256), 0, stream, thr, m, edge);
+    return hipGetLastError();
+}
+
+}  // namespace imin

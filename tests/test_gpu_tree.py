@@ -1,0 +1,113 @@
+"""The LDS-claim kernel (tree.hip) where it can go wrong, bit-exact against the CPU oracle:
+threshold codes at their steps, rows at and beyond the size that all waves share (and more of
+them than the list holds), claim counts around a bitmap word, samples on both sides of the
+dominator steps' LDS space, counter planes that fill up, and every workgroup size."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2302_13529_amd import graphgen as gg
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def check(gpu, n, row_ptr, col, prob, seeds, blocked, theta, key, label, slots=0, lt=False):
+    print(f"[case] {label}: n={n} m={col.shape[0]} theta={theta} slots={slots}", flush=True)
+    g = gpu.Graph(row_ptr, col, prob, model=gpu.IMIN_LT if lt else gpu.IMIN_IC)
+    g.set_launch(slots, 0)
+    D, st = g.decrease(seeds, blocked, theta, key)
+    Do, so = orc.decrease(n, row_ptr, col, prob, seeds, blocked, theta, key,
+                          **(dict(model=orc.LT) if lt else {}))
+    assert st["wave_samples"] == 0
+    assert np.array_equal(D, Do), (label, np.nonzero(D != Do)[0][:10])
+    for k in ("samples", "reached", "edges_scanned", "live_edges"):
+        assert st[k] == so[k], (label, k)
+    spread, ss = g.spread(seeds, blocked, theta, key)
+    assert ss["reached"] == so["reached"] and ss["live_edges"] == so["live_edges"]
+    g.close()
+
+
+def csr(n, src, dst, p):
+    order = np.lexsort((dst, src))
+    row_ptr = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(src, minlength=n), out=row_ptr[1:])
+    return row_ptr, dst[order].astype(np.int32), p[order].astype(np.float32)
+
+
+def test_thresholds_at_code_steps(gpu):
+    """Thresholds 2^k - 1, 2^k, 2^k + 1 and mantissa steps: the byte test never loses an edge."""
+    thr = sorted({t for k in range(0, 25) for d in (-1, 0, 1) for t in [2**k + d]} |
+                 {(8 + i) << k for k in range(21) for i in range(8)} |
+                 {((8 + i) << k) + 1 for k in range(20) for i in range(8)})
+    thr = np.array([t for t in thr if 0 <= t <= 2**24])
+    p = np.repeat(thr / 2.0**24, 40)  # exact in fp32: ceil(p * 2^24) is the threshold
+    n = p.size + 1
+    row_ptr, col, prob = csr(n, np.zeros(p.size, np.int64), np.arange(1, n), p)
+    assert np.array_equal(np.ceil(prob.astype(np.float64) * 2**24), np.repeat(thr, 40))
+    check(gpu, n, row_ptr, col, prob, [0], None, 3000, 11, "code steps")
+
+
+@pytest.mark.parametrize("width, hubs", [(509, 3), (512, 3), (513, 3), (520, 300), (4099, 5)])
+def test_heavy_rows(gpu, width, hubs):
+    """Hubs of `width` out-edges, all reached in one level: rows on both sides of the 128 quads
+    from which a row is shared, and more of them than the shared list holds."""
+    rng = np.random.default_rng(width)
+    n = 1 + hubs + 6000
+    src = [np.zeros(hubs, np.int64)]
+    dst = [np.arange(1, hubs + 1)]
+    p = [np.full(hubs, 0.9)]
+    for h in range(hubs):
+        src.append(np.full(width, h + 1))
+        dst.append(1 + rng.choice(n - 1, size=width, replace=False))
+        p.append(np.full(width, 0.02))
+    k = 4000
+    src.append(rng.integers(1 + hubs, n, k))
+    dst.append(rng.integers(1, n, k))
+    p.append(np.full(k, 0.3))
+    row_ptr, col, prob = csr(n, np.concatenate(src), np.concatenate(dst), np.concatenate(p))
+    check(gpu, n, row_ptr, col, prob, [0], None, 150, 5, f"heavy {width}x{hubs}")
+
+
+@pytest.mark.parametrize("extra", [0, 1, 31, 32, 33])
+def test_claim_counts_around_a_word(gpu, extra):
+    """nclaim = 32 + extra vertices of two in-edges, then some of one."""
+    two, one = 32 + extra, 45
+    n = 2 + two + one
+    src = np.concatenate([np.zeros(two), np.ones(two), np.full(one, 2)]).astype(np.int64)
+    dst = np.concatenate([2 + np.arange(two), 2 + np.arange(two), 2 + two + np.arange(one)])
+    p = np.full(src.size, 0.5)
+    row_ptr, col, prob = csr(n, src, dst, p)
+    check(gpu, n, row_ptr, col, prob, [0, 1], None, 700, 3, f"words {extra}", slots=2)
+
+
+@pytest.mark.parametrize("n, slots", [(3000, 0), (13000, 1), (30000, 3)])
+def test_dense_samples_and_full_planes(gpu, n, slots):
+    """Most vertices reached in every sample: dominator steps in LDS and in memory, and slots
+    that run more samples than their counter planes hold."""
+    rng = np.random.default_rng(n)
+    src = np.concatenate([rng.integers(0, n, 3 * n), np.arange(0, n - 1, 3)])
+    dst = np.concatenate([rng.integers(0, n, 3 * n), np.arange(1, n, 3)])
+    row_ptr, col, prob = csr(n, src, dst, np.full(src.size, 0.6))
+    blocked = np.zeros(n, np.uint8)
+    blocked[rng.choice(np.arange(5, n), 40, replace=False)] = 1
+    check(gpu, n, row_ptr, col, prob, [0, 1, 2], blocked, 150 if slots else 40, 9,
+          f"dense {n}", slots=slots)
+
+
+def test_every_workgroup_size(gpu):
+    """The workgroup size follows from theta and the bitmap."""
+    t = gg.tiny_plain()
+    for theta in (1, 100, 600, 1100, 2100, 5000):
+        check(gpu, t.n, t.row_ptr, t.col, t.prob, t.seeds, None, theta, theta, "tiny")
+
+
+def test_linear_threshold(gpu):
+    rng = np.random.default_rng(8)
+    n = 20000
+    src, dst = rng.integers(0, n, 6 * n), rng.integers(0, n, 6 * n)
+    indeg = np.bincount(dst, minlength=n)
+    row_ptr, col, prob = csr(n, src, dst, 0.95 / indeg[dst])
+    seeds = list(range(50))
+    check(gpu, n, row_ptr, col, prob, seeds, None, 120, 4, "lt", lt=True)
+    check(gpu, n, row_ptr, col, prob, seeds, None, 200, 4, "lt", slots=2, lt=True)
