@@ -142,6 +142,50 @@ size_t carve_tree(imin::TreeWs &ws, unsigned char *base, int32_t slots, int64_t 
     return at;
 }
 
+void free_forest(imin::ForestWs &ws)
+{
+    dfree(ws.base);
+    ws = imin::ForestWs();
+}
+
+int alloc_forest(imin::ForestWs &ws, int32_t slots, const imin::ForestShape &shape, int64_t words,
+                 hipStream_t stream)
+{
+    const int64_t entries = shape.entries;
+    if (ws.base && ws.slots >= slots && ws.entries == entries && ws.words == words) return IMIN_OK;
+    free_forest(ws);
+    const size_t S = (size_t)slots, o_planes = S * (size_t)entries * 4;
+    const size_t planes = S * imin::kTreePlanes * (size_t)words * 4;
+    if (!ok(hipMalloc(&ws.base, o_planes + planes + S * 4))) {
+        (void)hipGetLastError();
+        ws.base = nullptr;
+        return IMIN_ENOMEM;
+    }
+    ws.slots = slots;
+    ws.entries = entries;
+    ws.words = words;
+    ws.parent = reinterpret_cast<uint32_t *>(ws.base);
+    ws.planes = reinterpret_cast<uint32_t *>(ws.base + o_planes);
+    ws.used = reinterpret_cast<uint32_t *>(ws.base + o_planes + planes);
+    if (words > 0 && !ok(hipMemsetAsync(ws.planes, 0, planes, stream))) {
+        free_forest(ws);
+        return IMIN_EDEVICE;
+    }
+    return IMIN_OK;
+}
+
+// The wave-per-sample form's scratch.
+int ensure_leaf(unsigned char *&leaf, int num_cus)
+{
+    if (leaf) return IMIN_OK;
+    if (!ok(hipMalloc(&leaf, (size_t)imin::leaf_slots(num_cus) * imin::leaf_slot_bytes()))) {
+        (void)hipGetLastError();
+        leaf = nullptr;
+        return IMIN_ENOMEM;
+    }
+    return IMIN_OK;
+}
+
 int alloc_tree(imin::TreeWs &ws, int32_t slots, int64_t lcap, int64_t xcap, int64_t nclaim,
                int64_t words, hipStream_t stream)
 {
@@ -177,6 +221,11 @@ bool small_enabled(const imin_graph *g);
 // max_slots > 0 caps a new allocation (an existing one of the right shape is kept).
 int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach_only)
 {
+    if (g->forest && !small_enabled(g)) {
+        const int32_t slots = g->force_slots > 0 ? g->force_slots : g->fshape.per_cu * g->num_cus;
+        const int rc = alloc_forest(g->fws, slots, g->fshape, ((int64_t)g->nreach + 31) / 32, g->stream);
+        return rc ? rc : ensure_leaf(g->leaf, g->num_cus);
+    }
     if (g->tree) {
         imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT, reach_only, theta, g->num_cus,
                          g->shape);
@@ -362,6 +411,12 @@ void describe(imin_graph *g, int32_t nseeds, uint64_t seed, uint32_t theta)
     I.rec = g->mask_rec();
     I.code = g->d_code;
     I.rid_vtx = g->d_rid_vtx;
+    I.fnode = g->d_fnode;
+    I.fin16 = g->d_fin16;
+    I.fbound = g->d_fbound;
+    I.fsrc = g->d_fsrc;
+    I.rid_of = g->d_rid_of;
+    I.nsrc = g->nsrc;
     I.seed_lo = (uint32_t)seed;
     I.seed_hi = (uint32_t)(seed >> 32);
     I.theta = theta;
@@ -479,7 +534,7 @@ int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_
         a.sample_list = list;
         a.sample_count = count;
         a.next = t.ctrl + 0;
-        a.D = t.D;
+        a.D = t.Dr;
         a.stats = t.stats;
         a.ovf_list = t.ovf;
         a.ovf_count = t.ctrl + 2;
@@ -503,7 +558,7 @@ int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_
             if (!ok(imin::launch_tree(a, g->shape, lt, g->stream))) return IMIN_EDEVICE;
         }
         if (!reach_only && !ok(imin::launch_drain_planes(*t.main_tw, used, g->d_rid_vtx,
-                                                         g->nreach, t.D, g->stream)))
+                                                         g->nreach, t.Dr, t.D, g->stream)))
             return IMIN_EDEVICE;
         return IMIN_OK;
     }
@@ -565,8 +620,9 @@ void multi_free(MultiScratch &ms)
     ms.table_cap = ms.stages_cap = ms.stage_cap = ms.rounds_cap = ms.out_cap = 0;
     free_ws(ms.main_ws);
     free_ws(ms.big_ws);
-    free_tree(ms.main_tw);
-    free_tree(ms.big_tw);
+    free_forest(ms.fws);
+    free_forest(ms.low_ws);
+    dfree(ms.leaf);
     dfree(ms.ctrl);
     dfree(ms.pi);
     dfree(ms.pj);
@@ -587,6 +643,8 @@ void MultiSize::add(const imin_graph *g)
     m = std::max<int64_t>(m, g->m);
     nclaim = std::max<int64_t>(nclaim, g->nclaim);
     nreach = std::max<int64_t>(nreach, g->nreach);
+    nsrc = std::max<int64_t>(nsrc, g->nsrc);
+    forest = forest && g->forest;
     lt = g->model == IMIN_LT;
 }
 
@@ -597,27 +655,18 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
     const int64_t max_n = size.n, max_m = size.m;
     size_t free_b = 0, total_b = 0;
     if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
-    ms.tree = false;
-    if (ms.tree) {
-        free_ws(ms.main_ws);
-        free_ws(ms.big_ws);
-        const int64_t lcap = size.nreach + 1, xmax = max_m + 1;
-        const int64_t nclaim = size.lt ? 0 : size.nclaim;
-        const int64_t xcap = size.lt ? 1 : std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
-        free_b += ms.main_tw.bytes;
-        imin::TreeWs one;
-        const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, nclaim, 0);
-        const int32_t slots = (int32_t)std::max<size_t>(
-            1, std::min<size_t>((size_t)ms.shape.per_cu * std::max(1, num_cus), (free_b / 4) / per));
-        int rc = alloc_tree(ms.main_tw, slots, lcap, xcap, nclaim, 0, stream);
-        if (rc) return rc;
-        if (!size.lt && xcap < xmax)
-            return alloc_tree(ms.big_tw, (int32_t)kSpillSlots, lcap, xmax, nclaim, 0, stream);
-        free_tree(ms.big_tw);
-        return IMIN_OK;
+    ms.forest = size.lt && size.forest && imin::forest_shape(size.nreach, size.nsrc, ms.fshape);
+    if (ms.forest) {
+        const int cus = std::max(1, num_cus);
+        int rc = ensure_leaf(ms.leaf, num_cus);
+        if (!rc) rc = alloc_forest(ms.fws, ms.fshape.per_cu * cus, ms.fshape, 0, stream);
+        ms.split = size.nreach > imin::kForestLow &&
+                   imin::forest_shape(imin::kForestLow, size.nsrc, ms.low_shape) &&
+                   ms.low_shape.block < ms.fshape.block;
+        if (!rc && ms.split)
+            rc = alloc_forest(ms.low_ws, ms.low_shape.per_cu * cus, ms.low_shape, 0, stream);
+        return rc;
     }
-    free_tree(ms.main_tw);
-    free_tree(ms.big_tw);
     const int64_t lcap = max_n + 1;
     const int64_t xmax = max_m + 1;
     const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
@@ -752,11 +801,55 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
     s.spill_j = ms.sj;
     s.spill_count = ms.ctrl + 1;
     s.error = ms.ctrl + 2;
-    if (!pack && !ok(imin::launch_decrease_small(s, small_grid(num_cus, shape), stream)))
+    // Linear threshold on graphs that all fit the forest kernel: samples that stay small first,
+    // one per wavefront, then it, the smaller graphs' samples in workgroups sized for those.
+    const bool leaf = ms.forest && shape.pack_per_cu >= 0, split = leaf && ms.split;
+    if (leaf) {
+        imin::LeafArgs f{};
+        f.inst = inst;
+        f.ninst = ninst;
+        f.total = total;
+        f.round = round;
+        f.next = ms.ctrl + 0;
+        f.out_inst = ms.si;
+        f.out_j = ms.sj;
+        f.out_count = ms.ctrl + 1;
+        if (split) {
+            f.low_reach = imin::kForestLow;
+            f.low_inst = ms.pi;
+            f.low_j = ms.pj;
+            f.low_count = ms.ctrl + 7;
+        }
+        if (!ok(imin::launch_leaf(f, ms.leaf, imin::leaf_slots(num_cus), true, true, stream)))
+            return IMIN_EDEVICE;
+    } else if (!pack && !ok(imin::launch_decrease_small(s, small_grid(num_cus, shape), stream))) {
         return IMIN_EDEVICE;
-    if (ms.tree) {
-        const bool spill = ms.big_tw.slots > 0;
-        imin::TreeArgs a{};
+    }
+    if (ms.forest) {
+        imin::ForestArgs f{};
+        f.inst = inst;
+        f.theta = total;
+        f.round = round;
+        if (split) {
+            f.sample_list = ms.pj;
+            f.sample_inst = ms.pi;
+            f.sample_count = ms.ctrl + 7;
+            f.next = ms.ctrl + 4;
+            f.ws = ms.low_ws;
+            if (!ok(imin::launch_forest(f, ms.low_shape, ms.low_ws.slots, true, stream)))
+                return IMIN_EDEVICE;
+        }
+        f.sample_list = ms.sj;
+        f.sample_inst = ms.si;
+        f.sample_count = ms.ctrl + 1;
+        f.next = ms.ctrl + 3;
+        f.ws = ms.fws;
+        if (!ok(imin::launch_forest(f, ms.fshape, ms.fws.slots, true, stream))) return IMIN_EDEVICE;
+    } else {
+        const bool spill = ms.big_ws.slots > 0;
+        DecreaseArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.n = (int32_t)ms.n;
         a.theta = total;
         a.sample_list = pack ? ms.pj : ms.sj;
         a.sample_count = pack ? ms.ctrl + 7 : ms.ctrl + 1;
@@ -765,50 +858,22 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
         a.ovf_count = ms.ctrl + 5;
         a.error = ms.ctrl + 6;
         a.spill_ok = spill ? 1 : 0;
-        a.ws = ms.main_tw;
+        a.ws = ms.main_ws;
         a.inst = inst;
         a.sample_inst = pack ? ms.pi : ms.si;
         a.ovf_inst = ms.oi;
         a.round = round;
-        if (!ok(imin::launch_tree(a, ms.shape, lt, stream))) return IMIN_EDEVICE;
+        a.lt = lt ? 1 : 0;
+        if (!ok(imin::launch_decrease(a, stream))) return IMIN_EDEVICE;
         if (spill) {
             a.sample_list = ms.oj;
             a.sample_inst = ms.oi;
             a.sample_count = ms.ctrl + 5;
             a.next = ms.ctrl + 4;
             a.spill_ok = 0;
-            a.ws = ms.big_tw;
-            if (!ok(imin::launch_tree(a, ms.shape, lt, stream))) return IMIN_EDEVICE;
+            a.ws = ms.big_ws;
+            if (!ok(imin::launch_decrease(a, stream))) return IMIN_EDEVICE;
         }
-    } else {
-    const bool spill = ms.big_ws.slots > 0;
-    DecreaseArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.n = (int32_t)ms.n;
-    a.theta = total;
-    a.sample_list = pack ? ms.pj : ms.sj;
-    a.sample_count = pack ? ms.ctrl + 7 : ms.ctrl + 1;
-    a.next = ms.ctrl + 3;
-    a.ovf_list = ms.oj;
-    a.ovf_count = ms.ctrl + 5;
-    a.error = ms.ctrl + 6;
-    a.spill_ok = spill ? 1 : 0;
-    a.ws = ms.main_ws;
-    a.inst = inst;
-    a.sample_inst = pack ? ms.pi : ms.si;
-    a.ovf_inst = ms.oi;
-    a.round = round;
-    a.lt = lt ? 1 : 0;
-    if (!ok(imin::launch_decrease(a, stream))) return IMIN_EDEVICE;
-    if (spill) {
-        a.sample_list = ms.oj;
-        a.sample_inst = ms.oi;
-        a.sample_count = ms.ctrl + 5;
-        a.next = ms.ctrl + 4;
-        a.spill_ok = 0;
-        a.ws = ms.big_ws;
-        if (!ok(imin::launch_decrease(a, stream))) return IMIN_EDEVICE;
-    }
     }
     if (select) {
         if (ninst > ms.inst_cap) return IMIN_ERANGE;
@@ -835,7 +900,7 @@ int launch_large(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t key,
                  const uint32_t *list, const uint32_t *count, bool reach_only = false)
 {
     LargeTarget t{g->d_thr4, g->d_seeds, nseeds, g->d_D, g->d_stats, g->d_ctrl, g->d_ovf,
-                  &g->main_ws, &g->big_ws, &g->main_tw, &g->big_tw};
+                  &g->main_ws, &g->big_ws, &g->main_tw, &g->big_tw, g->d_D + g->n};
     return launch_large_on(g, t, theta, key, list, count, reach_only);
 }
 
@@ -864,7 +929,8 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         g->small_auto_off = without < with;
     }
     const bool small = small_enabled(g);
-    if ((!reach_only && !ok(imin::launch_fill_u64(g->d_D, g->n, 0, g->stream))) ||
+    if ((!reach_only &&
+         !ok(imin::launch_fill_u64(g->d_D, (int64_t)g->n + g->nreach, 0, g->stream))) ||
         (small && !ok(imin::launch_fill_u32(g->d_sctrl, 2, 0, g->stream))))
         return IMIN_EDEVICE;
     hipEvent_t k0, k1;
@@ -875,6 +941,51 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         ++g->probe;
     }
     if (!ok(hipEventRecord(k0, g->stream))) return IMIN_EDEVICE;
+    if (g->forest && !small) {
+        // Linear threshold on a graph that fits the forest kernel: samples that stay small
+        // first (automatic mode), then it.
+        const bool leaf = g->small_mode == -1;
+        if (!ok(imin::launch_fill_u32(g->d_sctrl, 3, 0, g->stream))) return IMIN_EDEVICE;
+        if (leaf) {
+            imin::LeafArgs f{};
+            f.inst = g->d_inst;
+            f.ninst = 1;
+            f.total = theta;
+            f.round = call;
+            f.reach_only = reach_only ? 1 : 0;
+            f.next = g->d_sctrl + 0;
+            f.out_j = g->d_sj;
+            f.out_count = g->d_sctrl + 1;
+            if (!ok(imin::launch_leaf(f, g->leaf,
+                                      (int)std::min<uint32_t>(theta, (uint32_t)imin::leaf_slots(g->num_cus)),
+                                      false, true, g->stream)))
+                return IMIN_EDEVICE;
+        }
+        imin::ForestArgs f{};
+        f.inst = g->d_inst;
+        f.theta = theta;
+        f.round = call;
+        f.sample_list = leaf ? g->d_sj : nullptr;
+        f.sample_count = g->d_sctrl + 1;
+        f.next = g->d_sctrl + 2;
+        f.reach_only = reach_only ? 1 : 0;
+        f.Dr = g->d_D + g->n;
+        f.ws = g->fws;
+        int32_t slots = g->force_slots > 0 ? g->force_slots : g->fshape.per_cu * g->num_cus;
+        slots = (int32_t)std::min<uint32_t>(theta, (uint32_t)slots);
+        if (!ok(imin::launch_forest(f, g->fshape, slots, false, g->stream))) return IMIN_EDEVICE;
+        if (!reach_only) {
+            imin::TreeWs counted;
+            counted.planes = g->fws.planes;
+            counted.used = g->fws.used;
+            counted.words = g->fws.words;
+            if (!ok(imin::launch_drain_planes(counted, slots, g->d_rid_vtx, g->nreach, g->d_D + g->n,
+                                              g->d_D, g->stream)))
+                return IMIN_EDEVICE;
+        }
+        if (!ok(hipEventRecord(k1, g->stream))) return IMIN_EDEVICE;
+        return IMIN_OK;
+    }
     if (small) {
         imin::SmallArgs s;
         std::memset(&s, 0, sizeof(s));
@@ -984,6 +1095,13 @@ void destroy(imin_graph *g)
     free_ws(g->big_ws);
     free_tree(g->main_tw);
     free_tree(g->big_tw);
+    free_forest(g->fws);
+    dfree(g->d_fnode);
+    dfree(g->d_fin16);
+    dfree(g->d_fbound);
+    dfree(g->d_fsrc);
+    dfree(g->d_rid_of);
+    dfree(g->leaf);
     dfree(g->d_rid_vtx);
     dfree(g->d_tedge);
     dfree(g->d_code);
@@ -1195,6 +1313,16 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         return IMIN_ENOMEM;
     }
     for (size_t r = 0; r < rid_vtx.size(); ++r) rid[(size_t)rid_vtx[r]] = (int32_t)r;
+    // Linear threshold, few enough reachable vertices: the in-edges by reach id.
+    imin::ForestShape fshape;
+    int32_t nsrc = 0;
+    for (int32_t v = 0; v < n; ++v)
+        if (in_ptr[(size_t)v + 1] == in_ptr[(size_t)v]) rid[(size_t)v] = -1 - nsrc++;
+    const bool forest =
+        model == IMIN_LT && imin::forest_shape((int64_t)rid_vtx.size(), nsrc, fshape);
+    std::vector<uint4> fnode;
+    std::vector<uint32_t> fin16, fbound;
+    std::vector<int32_t> fsrc;
     // Linear-threshold model: the in-edges of v split [0, 2^24) into consecutive intervals,
     // edge k of v (ascending id) getting [bound_{k-1}, bound_k) with
     // bound_k = min(2^24, ceil(2^24 * (w_1 + ... + w_k))) from fp64 running sums.
@@ -1223,12 +1351,42 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
             }
         }
     }
+    if (forest) {
+        try {
+            fnode.reserve(rid_vtx.size());
+            fin16.reserve((size_t)m);
+            fbound.reserve((size_t)m);
+            fsrc.reserve((size_t)m);
+            std::vector<int32_t> src((size_t)m);
+            for (int32_t v = 0; v < n; ++v)
+                std::fill(src.begin() + row_ptr[v], src.begin() + row_ptr[(size_t)v + 1], v);
+            for (int32_t v : rid_vtx) {
+                const int32_t k0 = in_ptr[(size_t)v], k1 = in_ptr[(size_t)v + 1];
+                fnode.push_back(make_uint4((uint32_t)v, (uint32_t)fin16.size(), (uint32_t)(k1 - k0),
+                                           (uint32_t)(row_ptr[(size_t)v + 1] - row_ptr[v])));
+                for (int32_t k = k0; k < k1; ++k) {
+                    const size_t e = (size_t)in_edge[(size_t)k];
+                    const int32_t s = src[e], r = rid[(size_t)s];
+                    const uint32_t b = hthr[e];
+                    fin16.push_back(((b ? b - 1 : 0u) >> 8 << 16) | (r >= 0 ? (uint32_t)r : 0xFFFDu));
+                    fbound.push_back(b);
+                    fsrc.push_back(r >= 0 ? s : -1 - r);
+                }
+            }
+        } catch (...) {
+            delete g;
+            return IMIN_ENOMEM;
+        }
+    }
     g->model = model;
     g->words = (n + 31) / 32;
     g->nclaim = nclaim;
     g->nreach = (int32_t)rid_vtx.size();
     g->tree = imin::tree_shape(g->nclaim, g->nreach, model == IMIN_LT, false, 1, g->num_cus,
                                g->shape);
+    g->forest = g->tree && forest;
+    g->fshape = fshape;
+    g->nsrc = nsrc;
     int32_t *d_rid = nullptr;
     bool good =
         ok(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking)) &&
@@ -1243,10 +1401,10 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         ok(hipMalloc(&g->d_cand, (size_t)g->words * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_seeds, (size_t)n * sizeof(int32_t))) &&
         ok(hipMalloc(&g->d_list, 2 * (size_t)n * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_D, (size_t)n * sizeof(unsigned long long))) &&
+        ok(hipMalloc(&g->d_D, ((size_t)n + rid_vtx.size()) * sizeof(unsigned long long))) &&
         ok(hipMalloc(&g->d_stats, kStats * sizeof(unsigned long long))) &&
         ok(hipMalloc(&g->d_ctrl, imin::kCtrlWords * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_sctrl, 2 * sizeof(uint32_t))) &&
+        ok(hipMalloc(&g->d_sctrl, 3 * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_inst, sizeof(imin::InstanceDesc))) &&
         ok(hipMalloc(&g->d_part_d, (size_t)g->parts * sizeof(unsigned long long))) &&
         ok(hipMalloc(&g->d_part_i, (size_t)g->parts * sizeof(int32_t))) &&
@@ -1257,7 +1415,11 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         (!g->tree || ok(hipMalloc(&g->d_tedge, hcol.size() * sizeof(uint4)))) &&
         (!g->tree || model != IMIN_IC || ok(hipMalloc(&g->d_code, hcol.size()))) &&
         ok(hipMalloc(&g->d_rid_vtx, std::max<size_t>(rid_vtx.size(), 1) * sizeof(int32_t))) &&
-        ok(hipMalloc(&d_rid, (size_t)n * sizeof(int32_t)));
+        ok(hipMalloc(&d_rid, (size_t)n * sizeof(int32_t))) &&
+        (!g->forest || (ok(hipMalloc(&g->d_fnode, fnode.size() * sizeof(uint4))) &&
+                        ok(hipMalloc(&g->d_fin16, fin16.size() * 4)) &&
+                        ok(hipMalloc(&g->d_fbound, fbound.size() * 4)) &&
+                        ok(hipMalloc(&g->d_fsrc, fsrc.size() * 4))));
     if (!good) {
         (void)hipGetLastError();
         dfree(d_rid);
@@ -1282,6 +1444,12 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
          !ok(hipMemcpy(g->d_rid_vtx, rid_vtx.data(), rid_vtx.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice))) ||
         !ok(hipMemcpy(d_rid, rid.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice)) ||
+        (g->forest &&
+         (!ok(hipMemcpy(g->d_fnode, fnode.data(), fnode.size() * sizeof(uint4),
+                        hipMemcpyHostToDevice)) ||
+          !ok(hipMemcpy(g->d_fin16, fin16.data(), fin16.size() * 4, hipMemcpyHostToDevice)) ||
+          !ok(hipMemcpy(g->d_fbound, fbound.data(), fbound.size() * 4, hipMemcpyHostToDevice)) ||
+          !ok(hipMemcpy(g->d_fsrc, fsrc.data(), fsrc.size() * 4, hipMemcpyHostToDevice)))) ||
         !ok(imin::launch_edge_records(reinterpret_cast<const uint32_t *>(g->d_col4), g->d_row_ptr,
                                       d_rid, reinterpret_cast<const uint32_t *>(g->d_thr_orig), m,
                                       g->d_tedge, reinterpret_cast<uint8_t *>(g->d_code), g->d_edge,
@@ -1291,7 +1459,8 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         destroy(g);
         return IMIN_EDEVICE;
     }
-    dfree(d_rid);
+    if (g->forest) g->d_rid_of = d_rid;
+    else dfree(d_rid);
     if (model == IMIN_LT) {
         // per quad: its 4 targets, then its 4 lower bounds
         std::vector<uint32_t> htl;
@@ -1663,10 +1832,12 @@ int imin_greedy_batch(imin_instance *inst, int32_t count, int mode, const imin_l
                                     (int64_t)(uintptr_t)ms.main_ws.map, ms.main_ws.slots,
                                     ms.main_ws.n, ms.main_ws.lcap, ms.main_ws.xcap,
                                     (int64_t)(uintptr_t)ms.big_ws.map, ms.big_ws.slots,
-                                    (int64_t)(uintptr_t)ms.main_tw.base, ms.main_tw.slots,
-                                    ms.main_tw.lcap, ms.main_tw.xcap, ms.main_tw.nclaim,
-                                    (int64_t)(uintptr_t)ms.big_tw.base, ms.big_tw.xcap,
-                                    ms.shape.block, ms.shape.per_cu};
+                                    ms.forest ? 1 : 0, ms.split ? 1 : 0,
+                                    (int64_t)(uintptr_t)ms.leaf, (int64_t)(uintptr_t)ms.fws.base,
+                                    ms.fws.entries, ms.fshape.block, ms.fws.slots,
+                                    (int64_t)(uintptr_t)ms.low_ws.base, ms.low_ws.entries,
+                                    ms.low_ws.slots, (int64_t)ms.low_shape.lds,
+                                    (int64_t)ms.fshape.lds};
         {
             int32_t act = count;
             for (int32_t r = 0; r < max_rounds; ++r) {

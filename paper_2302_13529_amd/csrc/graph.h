@@ -38,6 +38,13 @@ struct imin_graph {
     imin::TreeShape shape;        // its launch shape in the current call
     uint4 *d_tedge = nullptr;     // its edge records (their thresholds masked as d_thr4) and
     uint32_t *d_code = nullptr;   // threshold codes
+    // linear threshold, few enough reachable vertices: forest.hip's arrays (InstanceDesc)
+    bool forest = false;
+    imin::ForestShape fshape;
+    int32_t nsrc = 0;
+    uint4 *d_fnode = nullptr;
+    uint32_t *d_fin16 = nullptr, *d_fbound = nullptr;
+    int32_t *d_fsrc = nullptr, *d_rid_of = nullptr;
     int32_t *d_in_ptr = nullptr;  // in-edges of v: d_in_edge[d_in_ptr[v] .. d_in_ptr[v+1])
     int32_t *d_in_edge = nullptr; // edge ids, grouped by target
     hipStream_t stream = nullptr;
@@ -46,7 +53,7 @@ struct imin_graph {
     uint32_t *d_inelig = nullptr;            // seeds and blocked vertices
     uint32_t *d_cand = nullptr;              // GR candidate set CB
     int32_t *d_seeds = nullptr;              // distinct seeds (capacity n)
-    unsigned long long *d_D = nullptr;       // n
+    unsigned long long *d_D = nullptr;       // n, then nreach by reach id
     unsigned long long *d_stats = nullptr;   // kStats: samples, reached, scanned, live,
                                              // spilled, wave-kernel samples
     uint32_t *d_ctrl = nullptr;              // kCtrlWords: next main, next spill, spill count,
@@ -75,6 +82,8 @@ struct imin_graph {
     int32_t *d_x = nullptr;
     imin::Workspace main_ws, big_ws;
     imin::TreeWs main_tw, big_tw;
+    unsigned char *leaf = nullptr;     // the wave-per-sample form's scratch
+    imin::ForestWs fws;
     std::vector<int32_t> masked;       // vertices whose in-edges have threshold 0 in d_thr4
     std::vector<int32_t> mask_prev;    // the previous call's list, kept while copies run
     bool mask_known = true;            // false while a call runs, and after one that failed
@@ -137,6 +146,7 @@ struct LargeTarget {
     Workspace *big_ws;   // slots == 0 when no sample can overflow main_ws
     const TreeWs *main_tw;  // graphs of the LDS-claim kernel: these instead
     const TreeWs *big_tw;
+    unsigned long long *Dr; // and its counters by reach id, zero when the launch starts
 };
 // The workgroup kernel over samples 0..theta-1, or over the device list `list` of *count
 // samples, then the large-scratch launch for the samples that overflowed.
@@ -152,9 +162,11 @@ struct MultiScratch {
     int64_t n = 0, m = 0;      // largest instance it serves
     uint32_t cap = 0;          // samples of the largest round
     Workspace main_ws, big_ws;
-    bool tree = false;         // the LDS-claim kernel runs the hand-overs, in these
-    TreeShape shape;
-    TreeWs main_tw, big_tw;
+    unsigned char *leaf = nullptr;  // the wave-per-sample form's scratch
+    bool forest = false;            // linear threshold: the forest kernel takes the hand-overs,
+    bool split = false;             // the smaller graphs' in launches of their own
+    ForestShape fshape, low_shape;
+    ForestWs fws, low_ws;
     uint32_t *ctrl = nullptr;  // kMultiCtrl: wave next, wave hand-overs, wave error, main
                                // next, big next, overflow count, workgroup error, packed
                                // hand-overs, packed next, instances done this call
@@ -182,8 +194,8 @@ struct MultiScratch {
 };
 // The largest instance of a batch.
 struct MultiSize {
-    int64_t n = 0, m = 0, nclaim = 0, nreach = 0;
-    bool lt = false;
+    int64_t n = 0, m = 0, nclaim = 0, nreach = 0, nsrc = 0;
+    bool lt = false, forest = true;
     void add(const imin_graph *g);
 };
 int multi_alloc(MultiScratch &ms, int num_cus, const MultiSize &size, uint32_t cap,

@@ -170,7 +170,7 @@ struct TreeArgs {
     const uint32_t *sample_list;
     const uint32_t *sample_count;
     uint32_t *next;
-    unsigned long long *D;
+    unsigned long long *D;   // nreach counters by reach id (single calls)
     unsigned long long *stats;
     uint32_t *ovf_list;
     uint32_t *ovf_count;
@@ -187,6 +187,73 @@ struct TreeArgs {
     uint32_t round;
 };
 
+// Linear threshold from the chosen in-edges (forest.hip), for graphs of fewer than 65,533
+// reachable vertices.
+// Many-instance launches split the handed samples at so many reach ids, the most that a
+// workgroup of 256 threads takes: up to it four share a compute unit. 32 graphs of 1,000 to 50,000
+// vertices: 4.5 ms a round in one launch of 1,024 threads for all, 4.2 in two.
+constexpr int32_t kForestLow = 16382;
+struct ForestShape {
+    int32_t block = 0;       // threads per workgroup (0: the graph is too large)
+    int32_t words = 0;       // of two vertices, per thread at the most
+    int32_t entries = 0;     // words of two vertices
+    int32_t per_cu = 0;
+    uint32_t lds = 0;
+};
+
+struct ForestWs {
+    int32_t slots = 0;
+    int64_t entries = 0;           // words of two vertices per array
+    int64_t words = 0;             // bitmap words of the planes (0: not counted there)
+    uint32_t *parent = nullptr;    // slots * entries: the chosen in-edges' sources
+    uint32_t *planes = nullptr;    // slots * kTreePlanes * words
+    uint32_t *used = nullptr;      // slots: samples counted in the planes by the last launch
+    unsigned char *base = nullptr;
+};
+
+struct ForestArgs {
+    const InstanceDesc *inst;      // single calls: one
+    uint32_t theta;                // samples 0..theta-1 when sample_list is null
+    uint32_t round;
+    const uint32_t *sample_list;
+    const uint32_t *sample_inst;
+    const uint32_t *sample_count;
+    uint32_t *next;
+    int32_t reach_only;
+    unsigned long long *Dr;        // single calls: counters by reach id
+    ForestWs ws;
+};
+bool forest_shape(int64_t nreach, int64_t nsrc, ForestShape &out);
+hipError_t launch_forest(const ForestArgs &a, const ForestShape &s, int slots, bool multi,
+                         hipStream_t stream);
+
+// Wave-per-sample form of the same kernel (tree.hip), for samples of a few hundred vertices;
+// the others are listed for the workgroup form.
+struct LeafArgs {
+    const InstanceDesc *inst;  // ascending sample_base (single calls: one)
+    int32_t ninst;
+    uint32_t total;            // samples 0..total-1 when sample_list is null
+    uint32_t round;
+    const uint32_t *sample_list;   // else: samples sample_list[0..*sample_count), of instances
+    const uint32_t *sample_inst;   // sample_inst[..]
+    const uint32_t *sample_count;
+    int32_t reach_only;
+    uint32_t *next;
+    uint32_t *out_inst;        // samples handed over (single calls: out_j alone)
+    uint32_t *out_j;
+    uint32_t *out_count;
+    int32_t low_reach;         // those of graphs with at most so many reach ids go here
+    uint32_t *low_inst;
+    uint32_t *low_j;
+    uint32_t *low_count;
+    int2 *rng;                 // set by launch_leaf
+    int4 *extra;
+};
+int leaf_slots(int num_cus);
+size_t leaf_slot_bytes();
+hipError_t launch_leaf(const LeafArgs &a, unsigned char *scratch, int slots, bool multi, bool lt,
+                       hipStream_t stream);
+
 // False when nclaim vertices do not fit LDS (independent cascade). The workgroup is the
 // smallest with the most threads at work: all sizes run kTreeWaves waves per SIMD where the
 // claims leave room, and smaller workgroups wait less for each other at level ends (20,000
@@ -197,9 +264,11 @@ struct TreeArgs {
 bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
                 int num_cus, TreeShape &out);
 hipError_t launch_tree(const TreeArgs &a, const TreeShape &s, bool lt, hipStream_t stream);
-// D += the counts of the first `slots` slots, which go back to zero.
+// D += the sizes Dr by reach id and the counts of the first `slots` slots, which go back to
+// zero.
 hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *rid_vtx,
-                               int32_t nreach, unsigned long long *D, hipStream_t stream);
+                               int32_t nreach, const unsigned long long *Dr, unsigned long long *D,
+                               hipStream_t stream);
 hipError_t launch_edge_records(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
                                const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
                                uint4 *plain, hipStream_t stream);
@@ -252,6 +321,16 @@ struct InstanceDesc {
                               // thresholds, which the shared records do not follow
     const uint32_t *code;
     const int32_t *rid_vtx;
+    // forest.hip (linear threshold): per reach id its vertex, first in-edge, in-degree and
+    // out-degree; in-edges by target: the high 16 bits of (bound - 1) above the source's reach
+    // id, the exact bound, and the number of a source without a reach id; and per vertex its
+    // reach id, or -1 - that number
+    const uint4 *fnode;
+    const uint32_t *fin16;
+    const uint32_t *fbound;
+    const int32_t *fsrc;
+    const int32_t *rid_of;
+    int32_t nsrc;
     uint32_t seed_lo, seed_hi;
     uint32_t theta;
     uint32_t sample_base;

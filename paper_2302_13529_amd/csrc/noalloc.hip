@@ -254,9 +254,10 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
             !ok(imin::launch_fill_u32(w->dirty, w->slots, 0u, st)))
             return IMIN_EDEVICE;
     }
-    if (g->tree && !ok(imin::launch_fill_u32(main_tw.planes,
-                                             (int64_t)main_tw.slots * imin::kTreePlanes *
-                                                 main_tw.words, 0u, st)))
+    if (g->tree && (!ok(imin::launch_fill_u32(main_tw.planes,
+                                              (int64_t)main_tw.slots * imin::kTreePlanes *
+                                                  main_tw.words, 0u, st)) ||
+                    !ok(imin::launch_fill_u64(g->d_D + n, g->nreach, 0ull, st))))
         return IMIN_EDEVICE;
     if (!ok(imin::launch_fill_u64(reinterpret_cast<unsigned long long *>(d_counts), n, 0ull, st)) ||
         !ok(imin::launch_fill_u64(g->d_stats, kStats, 0ull, st)) ||
@@ -317,7 +318,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         list_count = g->d_sctrl + 1;
     }
     LargeTarget t{g->d_thr4, s_set, (int32_t)nseeds, reinterpret_cast<unsigned long long *>(d_counts),
-                  g->d_stats, g->d_ctrl, ovf, &main_ws, &big_ws, &main_tw, &big_tw};
+                  g->d_stats, g->d_ctrl, ovf, &main_ws, &big_ws, &main_tw, &big_tw, g->d_D + n};
     rc = launch_large_on(g, t, theta, seed, list, list_count, false);
     if (rc) return rc;
 

@@ -194,6 +194,12 @@ void carve(imin_server *s, Query &q)
     I.tedge = g->d_tedge;
     I.code = g->d_code;
     I.rid_vtx = g->d_rid_vtx;
+    I.fnode = g->d_fnode;
+    I.fin16 = g->d_fin16;
+    I.fbound = g->d_fbound;
+    I.fsrc = g->d_fsrc;
+    I.rid_of = g->d_rid_of;
+    I.nsrc = g->nsrc;
     I.theta = q.theta;
     I.gr_k = q.mode == IMIN_GR ? q.nb : -1;
     I.step = 0;

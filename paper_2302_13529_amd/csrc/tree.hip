@@ -43,6 +43,7 @@
 // equations, and by (1) they hold every dominator: the tree is the dominator tree.
 #include "imin_internal.h"
 #include "philox.h"
+#include "planes.h"
 #include "wave.h"
 
 #include <algorithm>
@@ -52,6 +53,7 @@ namespace imin {
 namespace {
 
 using namespace wave;
+using namespace planes;
 
 constexpr int kItems = 2;        // items in flight per lane
 constexpr int kRing = 128;       // a wave's queue of live edges: at most 63 wait for company
@@ -102,6 +104,7 @@ struct TreeCall {
     uint32_t key_lo, key_hi;
     unsigned long long *D;
     unsigned long long *stats;
+    int32_t own_thr;  // the exact thresholds are thr4's, not the records' (a query's masks)
 };
 
 // Thresholds in a byte. A coin below a threshold t has a value of at most t - 1, and so has its
@@ -183,73 +186,89 @@ struct WaveQueue {
     int head, n;  // uniform
 };
 
-// What the waves of a workgroup share while one level is expanded.
-struct Level {
-    int base;      // local id of the level's first claim
-    int *grown;
-    int *nextra;
-    bool shared;   // the rows at hand are shared with other waves
-};
-
-// The first k (at most 64) queued edges: claim their targets. The winners get consecutive
-// local ids in queue order, so equal parents are adjacent; a run of equal parents that may
-// go on in another batch (the first, the last, any of a shared row) is marked (sign of acc).
+// A queued edge's record, and whether it is live: an edge queued under the independent cascade
+// has passed the test of the codes and is decided here.
 template <bool kLT>
-__device__ __forceinline__ void consume(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv,
-                                        uint32_t *bm, const Level &lv, WaveQueue &q, int k,
-                                        uint32_t j, uint32_t &live)
+__device__ __forceinline__ bool follow(const TreeCall &c, const WaveQueue &q, bool has, uint32_t j,
+                                       uint4 &r, int &from)
 {
-    const int lane = lane_id();
-    bool has = lane < k;
-    uint4 r = make_uint4(0, 0, 0, 0);
-    int from = 0;
+    r = make_uint4(0, 0, 0, 0);
+    from = 0;
     uint32_t e = 0;
     if (has) {
-        const int at = (q.head + lane) & (kRing - 1);
+        const int at = (q.head + lane_id()) & (kRing - 1);
         e = q.qe[at];
-        r = c.edge[e];
+        r = glob(c.edge)[e];
         from = q.qs[at];
+        if (!kLT && c.own_thr) r.w = reinterpret_cast<const uint32_t *>(glob(c.thr4))[e];
     }
-    if (!kLT) {
-        uint32_t k0 = c.key_lo, k1 = c.key_hi, w0, w1, w2, w3;
-        asm volatile("" : "+s"(k0), "+s"(k1));
-        philox4x32_10(e >> 2, j, k0, k1, w0, w1, w2, w3);
-        const uint32_t w = (e & 2) ? ((e & 1) ? w3 : w2) : ((e & 1) ? w1 : w0);
-        has = has && (w >> 8) < r.w;
-    }
-    live += has ? 1u : 0u;
-    bool won = has;
-    if (!kLT && has && r.z < (uint32_t)c.nclaim) {
-        const uint32_t bit = 1u << (r.z & 31);
-        won = (atomicOr(&bm[r.z >> 5], bit) & bit) == 0u;
-        // another live edge into a reached vertex; edges from the merged seed never matter for
-        // dominators (their targets are its children)
-        if (!won && from != 0 && !a.reach_only) {
-            const int x = atomicAdd(lv.nextra, 1);
-            if (x < a.ws.xcap) sv.extra[x] = make_int4(from, (int)r.z, 0, 0);
-        }
-    }
-    const unsigned long long b = __ballot(won);
-    if (b) {
-        const int wins = __builtin_popcountll(b);
-        int first = 0;
-        if (lane == 0) first = atomicAdd(lv.grown, wins);
-        first = lv.base + __builtin_amdgcn_readfirstlane(first);
-        const int id = first + __builtin_popcountll(b & ((1ull << lane) - 1ull));
-        const int p0 = __builtin_amdgcn_readlane(from, __builtin_ctzll(b));
-        const int p1 = __builtin_amdgcn_readlane(from, 63 - __builtin_clzll(b));
-        if (won) {
-            sv.rng[id] = make_int2((int)r.x, (int)r.y);
-            if (!a.reach_only) {
-                sv.rid[id] = (int)r.z;
-                sv.par[id] = from;
-                sv.acc[id] = lv.shared || from == p0 || from == p1 ? (int)0x80000000 : 0;
+    if (kLT) return has;
+    uint32_t k0 = c.key_lo, k1 = c.key_hi, w0, w1, w2, w3;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    philox4x32_10(e >> 2, j, k0, k1, w0, w1, w2, w3);
+    const uint32_t w = (e & 2) ? ((e & 1) ? w3 : w2) : ((e & 1) ? w1 : w0);
+    return has && (w >> 8) < r.w;
+}
+
+// Where the live edges of a workgroup's sample go.
+template <bool kLT>
+struct GroupSink {
+    const TreeCall &c;
+    const TreeSlot &sv;
+    int64_t xcap;
+    bool reach_only;
+    uint32_t *bm;
+    int *nextra;
+    int base;      // local id of the level's first claim
+    int *grown;
+    bool shared;   // the rows at hand are shared with other waves
+
+    __device__ __forceinline__ bool full() const { return false; }
+
+    // The first k (at most 64) queued edges: claim their targets. The winners get consecutive
+    // local ids in queue order, so equal parents are adjacent; a run of equal parents that may
+    // go on in another batch (the first, the last, any of a shared row) is marked (sign of
+    // acc).
+    __device__ __forceinline__ void consume(WaveQueue &q, int k, uint32_t j, uint32_t &live)
+    {
+        const int lane = lane_id();
+        uint4 r;
+        int from;
+        const bool has = follow<kLT>(c, q, lane < k, j, r, from);
+        live += has ? 1u : 0u;
+        bool won = has;
+        if (!kLT && has && r.z < (uint32_t)c.nclaim) {
+            const uint32_t bit = 1u << (r.z & 31);
+            won = (atomicOr(&bm[r.z >> 5], bit) & bit) == 0u;
+            // another live edge into a reached vertex; edges from the merged seed never matter
+            // for dominators (their targets are its children)
+            if (!won && from != 0 && !reach_only) {
+                const int x = atomicAdd(nextra, 1);
+                if (x < xcap) sv.extra[x] = make_int4(from, (int)r.z, 0, 0);
             }
         }
+        const unsigned long long b = __ballot(won);
+        if (b) {
+            const int wins = __builtin_popcountll(b);
+            int first = 0;
+            if (lane == 0) first = atomicAdd(grown, wins);
+            first = base + __builtin_amdgcn_readfirstlane(first);
+            const int id = first + __builtin_popcountll(b & ((1ull << lane) - 1ull));
+            const int p0 = __builtin_amdgcn_readlane(from, __builtin_ctzll(b));
+            const int p1 = __builtin_amdgcn_readlane(from, 63 - __builtin_clzll(b));
+            if (won) {
+                sv.rng[id] = make_int2((int)r.x, (int)r.y);
+                if (!reach_only) {
+                    sv.rid[id] = (int)r.z;
+                    sv.par[id] = from;
+                    sv.acc[id] = shared || from == p0 || from == p1 ? (int)0x80000000 : 0;
+                }
+            }
+        }
+        q.head = (q.head + k) & (kRing - 1);
+        q.n -= k;
     }
-    q.head = (q.head + k) & (kRing - 1);
-    q.n -= k;
-}
+};
 
 // Items in flight per lane: edge quads (independent cascade: one Philox block decides 4
 // edges), or edges (linear threshold: a block per edge, keyed by its target).
@@ -271,8 +290,8 @@ __device__ __forceinline__ void load_items(const TreeCall &c, Items<kLT> &it)
         if constexpr (kLT) {
             it.hi[u] = it.lo[u] = it.tgt[u] = 0;
             if (it.ok[u]) {
-                const uint32_t *thr = reinterpret_cast<const uint32_t *>(c.thr4);
-                const uint32_t *tl = reinterpret_cast<const uint32_t *>(c.tl);
+                const uint32_t *thr = reinterpret_cast<const uint32_t *>(glob(c.thr4));
+                const uint32_t *tl = reinterpret_cast<const uint32_t *>(glob(c.tl));
                 const size_t e = (size_t)it.at[u];
                 it.hi[u] = thr[e];
                 it.tgt[u] = tl[((e >> 2) << 3) + (e & 3)];
@@ -280,7 +299,7 @@ __device__ __forceinline__ void load_items(const TreeCall &c, Items<kLT> &it)
             }
         } else {
             it.code[u] = 0;
-            if (it.ok[u]) it.code[u] = c.code[it.at[u]];
+            if (it.ok[u]) it.code[u] = glob(c.code)[it.at[u]];
         }
     }
 }
@@ -312,10 +331,8 @@ __device__ __forceinline__ void decide(const TreeCall &c, const Items<kLT> &it, 
 }
 
 // Append the items' edges to the queue in order; full batches are consumed.
-template <bool kLT>
-__device__ __forceinline__ void enqueue(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv,
-                                        uint32_t *bm, const Level &lv, WaveQueue &q,
-                                        const int (&at)[Items<kLT>::N],
+template <bool kLT, class Sink>
+__device__ __forceinline__ void enqueue(Sink &sink, WaveQueue &q, const int (&at)[Items<kLT>::N],
                                         const int (&src)[Items<kLT>::N],
                                         uint32_t (&m)[Items<kLT>::N], uint32_t j,
                                         uint32_t &live)
@@ -352,7 +369,7 @@ __device__ __forceinline__ void enqueue(const TreeArgs &a, const TreeCall &c, co
         wave_sync();
         q.n += room;
         done += room;
-        while (q.n >= 64) consume<kLT>(a, c, sv, bm, lv, q, 64, j, live);
+        while (q.n >= 64) sink.consume(q, 64, j, live);
         wave_sync();
     }
 }
@@ -362,21 +379,19 @@ __device__ __forceinline__ void enqueue(const TreeArgs &a, const TreeCall &c, co
 // and need no barrier until the level ends: claims and local ids are LDS atomics. A row of
 // more than kHeavy items is left to a second pass in which all waves share it. Returns the
 // number of vertices claimed.
-template <int B, bool kLT>
-__device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c,
-                                            const TreeSlot &sv, TreeHead<B> &sh, uint32_t *bm,
-                                            bool from_seeds, int lo, int hi, int base, int lset,
+template <int B, bool kLT, class Sink>
+__device__ __forceinline__ int expand_level(const TreeCall &c, const int2 *rng, TreeHead<B> &sh,
+                                            Sink &sink, bool from_seeds, int lo, int hi, int lset,
                                             uint32_t j, uint32_t &scanned, uint32_t &live)
 {
     constexpr int W = B / 64;
     constexpr int N = Items<kLT>::N;
     const int lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    Level lv{base, &sh.grown[lset], &sh.nextra, false};
     WaveQueue q{sh.qe[wid], sh.qs[wid], 0, 0};
     uint8_t *mark = sh.mark[wid];
-    // at least four chunks a wave, so that the level's waves end together
-    const int csz = max(8, min(64, (hi - lo) / (4 * W)));
+    // several waves: at least four chunks each, so that they end together
+    const int csz = W == 1 ? 64 : max(8, min(64, (hi - lo) / (4 * W)));
     int nh = -1;            // heavy rows of the level, once the first pass is over
     int h = 0, part = wid;  // this wave's next part of them: parts go round the waves
     // the rows at hand, one a lane: [e0, e1), items before them; the first lane's source
@@ -392,11 +407,11 @@ __device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c
             k = src0 + lane;
             if (lane < csz && k < hi) {
                 if (from_seeds) {
-                    const int v = c.seeds[k];
-                    e0 = c.row_ptr[v];
-                    e1 = c.row_ptr[v + 1];
+                    const int v = glob(c.seeds)[k];
+                    e0 = glob(c.row_ptr)[v];
+                    e1 = glob(c.row_ptr)[v + 1];
                 } else {
-                    const int2 r = sv.rng[k];
+                    const int2 r = rng[k];
                     e0 = r.x;
                     e1 = r.y;
                 }
@@ -469,7 +484,7 @@ __device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c
         wave_sync();
     };
     for (;;) {
-        while (next_rows()) {
+        while (!sink.full() && next_rows()) {
             Items<kLT> it;
             if (total > 0) {
                 place(0, it);
@@ -489,18 +504,18 @@ __device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c
                     place(sub + 64 * N, it);
                     load_items<kLT>(c, it);
                 }
-                enqueue<kLT>(a, c, sv, bm, lv, q, ats, srcs, m, j, live);
+                enqueue<kLT>(sink, q, ats, srcs, m, j, live);
             }
         }
         if (q.n > 0) {
-            consume<kLT>(a, c, sv, bm, lv, q, q.n, j, live);
+            sink.consume(q, q.n, j, live);
             wave_sync();
         }
         __syncthreads();
         if (W == 1 || nh >= 0) break;
         nh = __builtin_amdgcn_readfirstlane(min(sh.nheavy[lset], kHeavyCap));
         if (nh == 0) break;
-        lv.shared = true;
+        sink.shared = true;
     }
     // the counters of the level before last: every wave is past reading them, and none
     // touches them again before the next level's barrier
@@ -512,59 +527,12 @@ __device__ __forceinline__ int expand_level(const TreeArgs &a, const TreeCall &c
     return grown;
 }
 
-// Add the set bits of bm[0..n) into the words of the slot's bit-sliced counters from w0 on.
-template <int B>
-__device__ __forceinline__ void plane_add(uint32_t *planes, int64_t words, int64_t w0,
-                                          const uint32_t *bm, int n)
+// A subtree size into D: by reach id in single calls (folded into D by vertex once per
+// launch, so that no add waits for a vertex id), by vertex in many-instance launches.
+template <bool kMulti>
+__device__ __forceinline__ void add_size(const TreeCall &c, int rid, int size)
 {
-    for (int w = threadIdx.x; w < n; w += 4 * B) {
-        uint32_t x[4], o[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            x[u] = w + u * B < n ? bm[w + u * B] : 0u;
-            o[u] = x[u] ? planes[w0 + w + u * B] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (!x[u]) continue;
-            uint32_t *at = planes + w0 + w + u * B;
-            *at = o[u] ^ x[u];
-            uint32_t carry = o[u] & x[u];
-            for (int p = 1; p < kTreePlanes && carry; ++p) {
-                at += words;
-                const uint32_t v = *at;
-                *at = v ^ carry;
-                carry &= v;
-            }
-        }
-    }
-}
-
-// The slot's bit-sliced counters into D with atomics, and back to zero (a slot that has
-// counted as many samples as its planes hold).
-template <int B>
-__device__ void planes_drain(const TreeArgs &a, const TreeCall &c, const TreeSlot &sv)
-{
-    const int64_t words = a.ws.words;
-    for (int64_t w = threadIdx.x; w < words; w += B) {
-        uint32_t p[kTreePlanes], any = 0;
-#pragma unroll
-        for (int i = 0; i < kTreePlanes; ++i) {
-            p[i] = sv.planes[i * words + w];
-            any |= p[i];
-        }
-        if (!any) continue;
-#pragma unroll
-        for (int i = 0; i < kTreePlanes; ++i) sv.planes[i * words + w] = 0u;
-        while (any) {
-            const int b = __builtin_ctz(any);
-            any &= any - 1;
-            uint32_t v = 0;
-#pragma unroll
-            for (int i = 0; i < kTreePlanes; ++i) v |= ((p[i] >> b) & 1u) << i;
-            atomicAdd(&c.D[c.rid_vtx[w * 32 + b]], (unsigned long long)v);
-        }
-    }
+    atomicAdd(&glob(c.D)[kMulti ? glob(c.rid_vtx)[rid] : rid], (unsigned long long)size);
 }
 
 // kMulti: every sample of the launch's list names its instance.
@@ -597,7 +565,7 @@ void tree_kernel(TreeArgs a)
     unsigned long long t_samples = 0, t_reached = 0, t_scanned = 0, t_live = 0;
     uint32_t cur = 0xFFFFFFFFu;
     TreeCall c{a.row_ptr, a.edge, a.code, a.thr4, a.tl, a.seeds, a.rid_vtx, a.nseeds, a.nclaim,
-               a.nreach, a.key_lo, a.key_hi, a.D, a.stats};
+               a.nreach, a.key_lo, a.key_hi, a.D, a.stats, 0};
 
     auto flush_stats = [&]() {
         const unsigned long long sc = t_scanned, lv = t_live;
@@ -608,12 +576,12 @@ void tree_kernel(TreeArgs a)
             s2 += __shfl_xor(s2, o, 64);
         }
         if (lane == 0) {
-            if (s1) atomicAdd(&c.stats[2], s1);
-            if (s2) atomicAdd(&c.stats[3], s2);
+            if (s1) atomicAdd(&glob(c.stats)[2], s1);
+            if (s2) atomicAdd(&glob(c.stats)[3], s2);
         }
         if (tid == 0 && t_samples) {
-            atomicAdd(&c.stats[0], t_samples);
-            atomicAdd(&c.stats[1], t_reached);
+            atomicAdd(&glob(c.stats)[0], t_samples);
+            atomicAdd(&glob(c.stats)[1], t_reached);
         }
         t_samples = t_reached = t_scanned = t_live = 0;
     };
@@ -639,7 +607,8 @@ void tree_kernel(TreeArgs a)
                 c = TreeCall{scalar(I.row_ptr), scalar(I.tedge), scalar(I.code), scalar(I.thr4),
                              scalar(I.tl), scalar(I.seeds), scalar(I.rid_vtx),
                              scalar(I.nseeds), scalar(I.nclaim), scalar(I.nreach), scalar((uint32_t)key),
-                             scalar((uint32_t)(key >> 32)), scalar(I.D), scalar(I.stats)};
+                             scalar((uint32_t)(key >> 32)), scalar(I.D), scalar(I.stats),
+                             scalar(I.rec ? 0 : 1)};
             }
         }
         const int cwords = kLT ? 0 : (c.nclaim + 31) >> 5;
@@ -654,7 +623,9 @@ void tree_kernel(TreeArgs a)
         int L = 0, lo = 0, hi = c.nseeds, base = 1, lset = 0;
         do {
             if (tid == 0 && L > 0) sv.lvl[L + 1] = hi;
-            const int grown = expand_level<B, kLT>(a, c, sv, sh, bm, L == 0, lo, hi, base, lset, j,
+            GroupSink<kLT> sink{c, sv, a.ws.xcap, a.reach_only != 0, bm, &sh.nextra, base,
+                                &sh.grown[lset], false};
+            const int grown = expand_level<B, kLT>(c, sv.rng, sh, sink, L == 0, lo, hi, lset, j,
                                                    p_scanned, p_live);
             lset = lset == 2 ? 0 : lset + 1;
             lo = base;
@@ -672,7 +643,7 @@ void tree_kernel(TreeArgs a)
                     const uint32_t pos = atomicAdd(a.ovf_count, 1u);
                     a.ovf_list[pos] = j;
                     if (kMulti) a.ovf_inst[pos] = cur;
-                    atomicAdd(&c.stats[4], 1ull);
+                    atomicAdd(&glob(c.stats)[4], 1ull);
                 } else {
                     atomicOr(a.error, 1u);
                 }
@@ -697,7 +668,7 @@ void tree_kernel(TreeArgs a)
         const bool sliced = !kMulti && a.count_reach && (int64_t)nV * 64 >= c.nreach;
         if (sliced) {
             if (counted == kTreePlaneMax) {
-                planes_drain<B>(a, c, sv);
+                planes_drain<B>(sv.planes, a.ws.words, c.D);
                 counted = 0;
                 __syncthreads();
             }
@@ -787,17 +758,27 @@ void tree_kernel(TreeArgs a)
                 __syncthreads();
                 if (!ch) break;
             }
-            for (int l = L - 1; l >= 1; --l) {
+            for (int l = L - 1; l > 1; --l) {
                 const int b0 = sv.lvl[l], b1 = sv.lvl[l + 1];
                 for (int i = b0 + tid; i < b1; i += B) {
                     const int t = dom[i];
-                    const int size = sz[i];
-                    if (t != 0) atomicAdd(&sz[t], size);
-                    const int add = sliced ? size - 1 : size;
-                    if (add > 0) atomicAdd(&c.D[c.rid_vtx[sv.rid[i]]], (unsigned long long)add);
+                    if (t != 0) atomicAdd(&sz[t], sz[i]);
                 }
                 __syncthreads();
             }
+            for (int i = 1 + tid; i < nV; i += 4 * B) {
+                int add[4], r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = i + u * B;
+                    add[u] = k < nV ? sz[k] - (sliced ? 1 : 0) : 0;
+                    r[u] = add[u] > 0 ? sv.rid[k] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (add[u] > 0) add_size<kMulti>(c, r[u], add[u]);
+            }
+            __syncthreads();
         } else {
             // The tentative dominators take the place of the parents of extra edges' targets
             // while they are raised; then such a vertex gets its parent back, with the sign
@@ -840,21 +821,26 @@ void tree_kernel(TreeArgs a)
             // and is the only writer of that sum; a marked or cut one is added with an atomic,
             // as is a vertex whose dominator is not its parent (that dominator is at least two
             // levels above, where no run of this level ends).
-            for (int l = L - 1; l >= 1; --l) {
+            constexpr int U = 4;  // vertices in flight per lane
+            for (int l = L - 1; l > 1; --l) {
                 const int b0 = sv.lvl[l], b1 = sv.lvl[l + 1];
-                for (int i0 = b0 + (tid & ~63); i0 < b1; i0 += B) {
-                    const int i = i0 + lane;
-                    const bool in = i < b1;
-                    int p = 0, s = 0, t = 0;
-                    if (in) {
-                        p = sv.par[i];
-                        s = ld(&sv.acc[i]);
-                        if (p < 0) t = sv.dom[i];
+                for (int j0 = b0 + U * (tid & ~63); j0 < b1; j0 += U * B) {
+                    int pu[U], su[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = j0 + 64 * u + lane;
+                        pu[u] = i < b1 ? sv.par[i] : 0;
+                        su[u] = i < b1 ? ld(&sv.acc[i]) : 0;
                     }
-                    const bool moved = p < 0, shared = s < 0;
-                    p &= 0x7FFFFFFF;
-                    s = in ? (s & 0x7FFFFFFF) + 1 : 0;
-                    if (l > 1) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i0 = j0 + 64 * u;
+                        if (i0 >= b1) break;
+                        const int i = i0 + lane;
+                        const bool in = i < b1;
+                        const bool moved = pu[u] < 0, shared = su[u] < 0;
+                        const int p = pu[u] & 0x7FFFFFFF;
+                        const int s = in ? (su[u] & 0x7FFFFFFF) + 1 : 0;
                         const int incl = wave_scan(moved ? 0 : s);
                         const int pp = __shfl_up(p, 1, 64), pn = __shfl_down(p, 1, 64);
                         const bool head = in && (lane == 0 || pp != p);
@@ -873,22 +859,317 @@ void tree_kernel(TreeArgs a)
                                     st(&sv.acc[p], ld(&sv.acc[p]) + sum);
                             }
                         }
-                        if (moved && t != 0)
-                            __hip_atomic_fetch_add(&sv.acc[t], s, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (moved) {
+                            const int t = sv.dom[i];
+                            if (t != 0)
+                                __hip_atomic_fetch_add(&sv.acc[t], s, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
                     }
-                    const int add = sliced ? s - 1 : s;
-                    if (in && add > 0) atomicAdd(&c.D[c.rid_vtx[sv.rid[i]]], (unsigned long long)add);
                 }
                 __syncthreads();
             }
+            for (int i = 1 + tid; i < nV; i += 4 * B) {
+                int add[4], r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = i + u * B;
+                    add[u] = k < nV ? (ld(&sv.acc[k]) & 0x7FFFFFFF) + (sliced ? 0 : 1) : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r[u] = add[u] > 0 ? sv.rid[i + u * B] : 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (add[u] > 0) add_size<kMulti>(c, r[u], add[u]);
+            }
+            __syncthreads();
         }
     }
     if (!kMulti || cur != 0xFFFFFFFFu) flush_stats();
     if (!kMulti && tid == 0 && a.count_reach) a.ws.used[slot] = counted;
 }
 
-// D[v] += the bit-sliced reach counts of every slot that kept some (used), which go back to 0.
+// The same for samples of at most kLeafV vertices: one wavefront per sample, sixteen samples
+// per compute unit, everything but the row ranges and the extra edges in 10 KB of LDS, and no
+// barrier. Reach ids are claimed in a hash table (independent cascade). What bounds such
+// samples is latency: a level costs the row ranges, the codes and the records one after the
+// other, so what counts is how many samples are in flight. A sample that outgrows the space
+// is handed over to the workgroup kernel, with nothing accumulated.
+constexpr int kLeafV = 576;      // local vertices, root included
+constexpr int kLeafX = 512;      // extra edges
+constexpr int kLeafHash = 1024;
+constexpr int kLeafLevels = 120;
+constexpr uint32_t kLeafRun = 16;  // samples taken at a time, at most
+
+struct LeafShared {
+    TreeHead<64> h;
+    uint16_t lvl[kLeafLevels + 2];
+    uint16_t par[kLeafV];        // BFS parents, then dominators
+    uint16_t slot[kLeafV];       // hash slot of each local vertex
+    int4 key[kLeafHash / 4];     // reach ids: by hash slot (-1: empty); linear threshold: by
+                                 // local id
+    union {
+        uint16_t lid[kLeafHash]; // local id by hash slot
+        int size[kLeafV];        // once the extra edges are resolved
+    };
+};
+static_assert(sizeof(LeafShared) <= kTreeLds / 16, "sixteen samples per compute unit");
+
+template <bool kLT>
+struct LeafSink {
+    const TreeCall &c;
+    LeafShared &sm;
+    int *key;
+    int2 *rng;
+    int4 *extra;
+    bool reach_only;
+    int tail = 1, nextra = 0;
+    bool over = false;
+    bool shared = false;
+
+    __device__ __forceinline__ bool full() const { return over; }
+
+    __device__ __forceinline__ void consume(WaveQueue &q, int k, uint32_t j, uint32_t &live)
+    {
+        const int lane = lane_id();
+        if (tail + k > kLeafV) over = true;
+        if (!over) {
+            uint4 r;
+            int from;
+            const bool has = follow<kLT>(c, q, lane < k, j, r, from);
+            live += has ? 1u : 0u;
+            bool won = has;
+            uint32_t h = 0;
+            if (!kLT && has) {
+                // at most kLeafV of the kLeafHash slots are ever taken
+                h = (r.z * 2654435761u) >> 22;
+                for (;;) {
+                    const int old = atomicCAS(&key[h], -1, (int)r.z);
+                    won = old == -1;
+                    if (won || old == (int)r.z) break;
+                    h = (h + 1) & (kLeafHash - 1);
+                }
+            }
+            const unsigned long long below = (1ull << lane) - 1ull;
+            const unsigned long long b = __ballot(won);
+            if (won) {
+                const int id = tail + __builtin_popcountll(b & below);
+                rng[id] = make_int2((int)r.x, (int)r.y);
+                sm.par[id] = (uint16_t)from;
+                if (kLT) {
+                    key[id] = (int)r.z;
+                } else {
+                    sm.slot[id] = (uint16_t)h;
+                    sm.lid[h] = (uint16_t)id;
+                }
+            }
+            tail += __builtin_popcountll(b);
+            if (!kLT && !reach_only) {
+                const bool x = has && !won && from != 0;
+                const unsigned long long bx = __ballot(x);
+                const int at = nextra + __builtin_popcountll(bx & below);
+                if (x && at < kLeafX) extra[at] = make_int4(from, (int)h, 0, 0);
+                nextra += __builtin_popcountll(bx);
+                if (nextra > kLeafX) over = true;
+            }
+        }
+        q.head = (q.head + k) & (kRing - 1);
+        q.n -= k;
+    }
+};
+
+// One sample; false when it must be handed over.
+template <bool kLT>
+__device__ __forceinline__ bool leaf_sample(const TreeCall &c, LeafShared &sm, int2 *rng,
+                                            int4 *extra, bool reach_only, uint32_t j,
+                                            uint32_t &scanned, uint32_t &live, int &reached)
+{
+    const int lane = lane_id();
+    wave_sync();
+    int *const key = reinterpret_cast<int *>(sm.key);
+    if (!kLT) {
+#pragma unroll
+        for (int i = 0; i < kLeafHash / 256; ++i) sm.key[i * 64 + lane] = make_int4(-1, -1, -1, -1);
+    }
+    if (lane < 3) sm.h.chunk[lane] = sm.h.grown[lane] = sm.h.nheavy[lane] = 0;
+    if (lane == 0) {
+        sm.lvl[0] = 0;
+        sm.lvl[1] = 1;
+        sm.par[0] = 0;
+    }
+    wave_sync();
+    LeafSink<kLT> sink{c, sm, key, rng, extra, reach_only};
+    int L = 0, lo = 0, hi = c.nseeds, lset = 0;
+    do {
+        if (L >= kLeafLevels) return false;
+        if (lane == 0 && L > 0) sm.lvl[L + 1] = (uint16_t)hi;
+        const int base = sink.tail;
+        expand_level<64, kLT>(c, rng, sm.h, sink, L == 0, lo, hi, lset, j, scanned, live);
+        if (sink.over) return false;
+        lset = lset == 2 ? 0 : lset + 1;
+        lo = base;
+        hi = sink.tail;
+        ++L;
+    } while (lo < hi);
+    wave_sync();
+    const int nV = sink.tail, nX = sink.nextra;
+    reached = nV - 1;
+    if (reach_only || nV == 1) return true;
+
+    if (!kLT && nX > 0) {
+        for (int x = lane; x < nX; x += 64) {
+            int4 e = extra[x];
+            e.y = sm.lid[e.y];
+            e.z = sm.par[e.y];
+            extra[x] = e;
+        }
+        wave_sync();
+        const int deep = sm.lvl[2];
+        for (;;) {
+            bool changed = false;
+            for (int x = lane; x < nX; x += 64) {
+                const int4 e = extra[x];
+                const int tv = ld(&sm.par[e.y]);
+                if (tv == 0) continue;
+                const int m = tree_nca(sm.par, deep, tree_nca(sm.par, deep, tv, e.x), e.z);
+                if (m < tv) {
+                    st(&sm.par[e.y], (uint16_t)m);
+                    changed = true;
+                }
+            }
+            wave_sync();
+            if (!__any(changed)) break;
+        }
+    }
+    int *size = sm.size;
+    for (int i = lane; i < nV; i += 64) size[i] = 1;
+    wave_sync();
+    for (int l = L - 1; l > 1; --l) {
+        const int b0 = sm.lvl[l], b1 = sm.lvl[l + 1];
+        for (int i = b0 + lane; i < b1; i += 64) {
+            const int t = sm.par[i];
+            if (t != 0) atomicAdd(&size[t], size[i]);
+        }
+        wave_sync();
+    }
+    for (int i = 1 + lane; i < nV; i += 64) {
+        const int rid = key[kLT ? i : sm.slot[i]];
+        atomicAdd(&glob(c.D)[glob(c.rid_vtx)[rid]], (unsigned long long)size[i]);
+    }
+    return true;
+}
+
+template <bool kMulti, bool kLT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kTreeWaves, kTreeWaves)))
+void leaf_kernel(LeafArgs a)
+{
+    __shared__ LeafShared sm;
+    const int lane = lane_id();
+    int2 *rng = a.rng + (size_t)blockIdx.x * kLeafV;
+    int4 *extra = a.extra + (size_t)blockIdx.x * kLeafX;
+    const uint32_t count = a.sample_list ? *a.sample_count : a.total;
+    uint32_t cur = 0xFFFFFFFFu, cur_lo = 0, cur_hi = 0;
+    bool skip = false, done = false;
+    TreeCall c{};
+    uint32_t *ctrl = nullptr;
+    unsigned long long t_samples = 0, t_reached = 0, t_scanned = 0, t_live = 0;
+    auto flush_stats = [&]() {
+        unsigned long long s1 = t_scanned, s2 = t_live;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            s1 += __shfl_xor(s1, o, 64);
+            s2 += __shfl_xor(s2, o, 64);
+        }
+        if (lane == 0 && t_samples) {
+            atomicAdd(&glob(c.stats)[0], t_samples);
+            atomicAdd(&glob(c.stats)[1], t_reached);
+            atomicAdd(&glob(c.stats)[2], s1);
+            atomicAdd(&glob(c.stats)[3], s2);
+            atomicAdd(&glob(c.stats)[5], t_samples);
+        }
+        t_samples = t_reached = t_scanned = t_live = 0;
+    };
+    auto hand_over = [&](uint32_t j) {
+        if (lane == 0) {
+            const bool low = kMulti && c.nreach <= a.low_reach;
+            const uint32_t at = atomicAdd(low ? a.low_count : a.out_count, 1u);
+            (low ? a.low_j : a.out_j)[at] = j;
+            if (kMulti) (low ? a.low_inst : a.out_inst)[at] = cur;
+        }
+    };
+    uint32_t seen = 0;
+    for (;;) {
+        // runs of consecutive samples that shrink as the launch drains
+        uint32_t first = 0, last = 0;
+        if (lane == 0) {
+            const uint32_t left = seen < count ? count - seen : 0u;
+            const uint32_t want = max(1u, min(kLeafRun, left / (4u * gridDim.x)));
+            first = atomicAdd(a.next, want);
+            last = min(first + want, count);
+        }
+        first = __builtin_amdgcn_readfirstlane(first);
+        last = __builtin_amdgcn_readfirstlane(last);
+        if (first >= last) break;
+        seen = last;
+        for (uint32_t idx = first; idx < last; ++idx) {
+            uint32_t inst = 0, j = idx;
+            if (a.sample_list) {
+                j = __builtin_amdgcn_readfirstlane(a.sample_list[idx]);
+                if (kMulti) inst = __builtin_amdgcn_readfirstlane(a.sample_inst[idx]);
+            } else if (kMulti) {
+                inst = cur;
+                if (cur == 0xFFFFFFFFu || idx < cur_lo || idx >= cur_hi) {
+                    int lo = 0, hi = a.ninst - 1;
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (a.inst[mid].sample_base <= idx) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    inst = __builtin_amdgcn_readfirstlane(lo);
+                }
+            }
+            if (inst != cur) {
+                if (cur != 0xFFFFFFFFu) flush_stats();
+                cur = inst;
+                const InstanceDesc &I = a.inst[inst];
+                const unsigned long long key =
+                    (((unsigned long long)I.seed_hi << 32) | I.seed_lo) + a.round;
+                c = TreeCall{scalar(I.row_ptr), scalar(I.tedge), scalar(I.code), scalar(I.thr4),
+                             scalar(I.tl), scalar(I.seeds), scalar(I.rid_vtx),
+                             scalar(I.nseeds), scalar(I.nclaim), scalar(I.nreach),
+                             scalar((uint32_t)key), scalar((uint32_t)(key >> 32)), scalar(I.D),
+                             scalar(I.stats), scalar(I.rec ? 0 : 1)};
+                if (kMulti) {
+                    ctrl = scalar(I.ctrl);
+                    cur_lo = scalar(I.sample_base);
+                    cur_hi = cur_lo + scalar(I.theta);
+                    // an instance that handed most samples of an earlier round over skips this
+                    // kernel; the samples of one whose run has ended are dropped
+                    skip = __builtin_amdgcn_readfirstlane(ld(&ctrl[kCtrlSkipWave])) != 0u;
+                    done = __builtin_amdgcn_readfirstlane(ld(&ctrl[kCtrlDone])) != 0u;
+                }
+            }
+            if (kMulti && !a.sample_list) j = idx - cur_lo;
+            if (kMulti && done) continue;
+            uint32_t scanned = 0, live = 0;
+            int reached = 0;
+            if (!(kMulti && skip) &&
+                leaf_sample<kLT>(c, sm, rng, extra, a.reach_only != 0, j, scanned, live, reached)) {
+                t_samples += 1;
+                t_reached += (unsigned long long)reached;
+                t_scanned += scanned;
+                t_live += live;
+            } else {
+                hand_over(j);
+                if (kMulti && !skip && lane == 0) atomicAdd(&ctrl[kCtrlWaveHanded], 1u);
+            }
+        }
+    }
+    if (cur != 0xFFFFFFFFu) flush_stats();
+}
+
+// D[v] += the sizes by reach id (Dr) and the bit-sliced reach counts of every slot that kept
+// some (used), which go back to 0.
 // A workgroup takes 16 bitmap words (512 reach ids) and shares the slots of its part (grid y)
 // among 16 thread rows; each thread adds its slots' planes into a bit-sliced sum and the rows
 // meet in LDS counters, so D is touched once per vertex and part.
@@ -898,7 +1179,7 @@ constexpr int kDrainBits = 20;  // 63 samples in each of at most 4096 slots
 
 __global__ __launch_bounds__(kDrainWords *kDrainRows) void drain_planes_kernel(
     uint32_t *planes, const uint32_t *used, int32_t slots, int64_t words, const int32_t *rid_vtx,
-    int32_t nreach, unsigned long long *D)
+    int32_t nreach, const unsigned long long *Dr, unsigned long long *D)
 {
     __shared__ uint32_t sum[kDrainWords * 32];
     const int wd = threadIdx.x % kDrainWords, row = threadIdx.x / kDrainWords;
@@ -937,8 +1218,10 @@ __global__ __launch_bounds__(kDrainWords *kDrainRows) void drain_planes_kernel(
     }
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * kDrainWords * 32;
-    for (int i = threadIdx.x; i < kDrainWords * 32; i += kDrainWords * kDrainRows)
-        if (sum[i] && r0 + i < nreach) atomicAdd(&D[rid_vtx[r0 + i]], (unsigned long long)sum[i]);
+    for (int i = threadIdx.x; i < kDrainWords * 32 && r0 + i < nreach; i += kDrainWords * kDrainRows) {
+        const unsigned long long v = sum[i] + (blockIdx.y == 0 && Dr ? Dr[r0 + i] : 0ull);
+        if (v) atomicAdd(&D[rid_vtx[r0 + i]], v);
+    }
 }
 
 // Per edge: the target's row range, its reach id and the edge's threshold; the threshold's
@@ -1004,6 +1287,23 @@ hipError_t launch_shape(const TreeArgs &a, const TreeShape &s, hipStream_t strea
 
 }  // namespace
 
+int leaf_slots(int num_cus) { return 16 * std::max(1, num_cus); }
+
+size_t leaf_slot_bytes() { return kLeafV * sizeof(int2) + kLeafX * sizeof(int4); }
+
+hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, bool multi, bool lt,
+                       hipStream_t stream)
+{
+    if (slots <= 0 || !scratch) return hipErrorInvalidValue;
+    LeafArgs a = args;
+    a.extra = reinterpret_cast<int4 *>(scratch);
+    a.rng = reinterpret_cast<int2 *>(scratch + (size_t)slots * kLeafX * sizeof(int4));
+    void (*k)(LeafArgs) = multi ? (lt ? leaf_kernel<true, true> : leaf_kernel<true, false>)
+                                : (lt ? leaf_kernel<false, true> : leaf_kernel<false, false>);
+    hipLaunchKernelGGL(k, dim3(slots), dim3(64), 0, stream, a);
+    return hipGetLastError();
+}
+
 bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
                 int num_cus, TreeShape &out)
 {
@@ -1032,13 +1332,14 @@ hipError_t launch_tree(const TreeArgs &args, const TreeShape &s, bool lt, hipStr
 }
 
 hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *rid_vtx,
-                               int32_t nreach, unsigned long long *D, hipStream_t stream)
+                               int32_t nreach, const unsigned long long *Dr, unsigned long long *D,
+                               hipStream_t stream)
 {
     if (slots <= 0 || nreach <= 0) return hipSuccess;
     const int64_t bx = (ws.words + kDrainWords - 1) / kDrainWords;
     const int by = (int)std::max<int64_t>(1, std::min<int64_t>(8, 512 / bx));
     hipLaunchKernelGGL(drain_planes_kernel, dim3((uint32_t)bx, by), dim3(kDrainWords * kDrainRows), 0,
-                       stream, ws.planes, ws.used, slots, ws.words, rid_vtx, nreach, D);
+                       stream, ws.planes, ws.used, slots, ws.words, rid_vtx, nreach, Dr, D);
     return hipGetLastError();
 }
 

@@ -13,6 +13,15 @@ constexpr int kSeedCacheQuads = 64 * kSeedSlots;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+// A pointer to global memory whose origin the compiler cannot see (read from the instance
+// table): told so, it loads with global instructions. Flat ones also count as LDS accesses, so
+// that every wait for LDS would wait for them.
+template <class T>
+__device__ __forceinline__ T *glob(T *p)
+{
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+
 // Orders this wave's LDS accesses across lanes (the hardware runs one wave's LDS
 // instructions in order; this keeps the compiler from moving them across the point).
 __device__ __forceinline__ void wave_sync()

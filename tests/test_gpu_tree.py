@@ -19,10 +19,16 @@ def check(gpu, n, row_ptr, col, prob, seeds, blocked, theta, key, label, slots=0
     D, st = g.decrease(seeds, blocked, theta, key)
     Do, so = orc.decrease(n, row_ptr, col, prob, seeds, blocked, theta, key,
                           **(dict(model=orc.LT) if lt else {}))
+    assert np.array_equal(D, Do), (label, np.nonzero(D != Do)[0][:10])
+    for k in ("samples", "reached", "edges_scanned", "live_edges"):
+        assert st[k] == so[k], (label, k)
+    g.set_small(0)  # no wavefront-level kernel
+    D, st = g.decrease(seeds, blocked, theta, key)
     assert st["wave_samples"] == 0
     assert np.array_equal(D, Do), (label, np.nonzero(D != Do)[0][:10])
     for k in ("samples", "reached", "edges_scanned", "live_edges"):
         assert st[k] == so[k], (label, k)
+    g.set_small(-1)
     spread, ss = g.spread(seeds, blocked, theta, key)
     assert ss["reached"] == so["reached"] and ss["live_edges"] == so["live_edges"]
     g.close()
@@ -102,12 +108,35 @@ def test_every_workgroup_size(gpu):
         check(gpu, t.n, t.row_ptr, t.col, t.prob, t.seeds, None, theta, theta, "tiny")
 
 
-def test_linear_threshold(gpu):
-    rng = np.random.default_rng(8)
-    n = 20000
+def lt_graph(n, seed, weight=None):
+    """Random in-edges; a vertex's weights sum to at most 1 (unequal ones unless weight)."""
+    rng = np.random.default_rng(seed)
     src, dst = rng.integers(0, n, 6 * n), rng.integers(0, n, 6 * n)
-    indeg = np.bincount(dst, minlength=n)
-    row_ptr, col, prob = csr(n, src, dst, 0.95 / indeg[dst])
-    seeds = list(range(50))
-    check(gpu, n, row_ptr, col, prob, seeds, None, 120, 4, "lt", lt=True)
-    check(gpu, n, row_ptr, col, prob, seeds, None, 200, 4, "lt", slots=2, lt=True)
+    w = np.full(src.size, 1.0) if weight else rng.random(src.size) ** 4
+    w[rng.random(src.size) < 0.05] = 0.0
+    total = np.bincount(dst, weights=w, minlength=n)
+    scale = np.where(rng.random(n) < 0.5, 0.999, 0.7) / np.maximum(total, 1e-9)
+    return csr(n, src, dst, w * scale[dst])
+
+
+# reach ids per workgroup: 4096, 8192, 16384, 32768, 65532 at most; beyond, the other kernel
+@pytest.mark.parametrize("n", [500, 4000, 4200, 8300, 17000, 33000, 64000, 67000])
+def test_linear_threshold(gpu, n):
+    row_ptr, col, prob = lt_graph(n, n)
+    rng = np.random.default_rng(n)
+    seeds = rng.choice(n, 40, replace=False).astype(np.int32)
+    blocked = np.zeros(n, np.uint8)
+    blocked[np.setdiff1d(rng.choice(n, 30, replace=False), seeds)] = 1
+    check(gpu, n, row_ptr, col, prob, seeds, blocked, 60, 4, f"lt {n}", lt=True)
+    check(gpu, n, row_ptr, col, prob, seeds, None, 150, 2**35 + 1, f"lt {n}", slots=2, lt=True)
+
+
+def test_linear_threshold_deep_and_equal_weights(gpu):
+    """A path of 3000 levels (deeper than the depth bins), and equal weights, whose draws fall
+    on interval edges as often as any."""
+    n = 3001
+    e = [(i, i + 1, 1.0) for i in range(n - 1)]
+    rp, c, p = H.csr_from_edges(n, e)
+    check(gpu, n, rp, c, p, [0], None, 20, 1, "lt path", lt=True)
+    row_ptr, col, prob = lt_graph(5000, 3, weight=True)
+    check(gpu, 5000, row_ptr, col, prob, list(range(30)), None, 100, 1, "lt equal", lt=True)
