@@ -620,6 +620,8 @@ void multi_free(MultiScratch &ms)
     ms.table_cap = ms.stages_cap = ms.stage_cap = ms.rounds_cap = ms.out_cap = 0;
     free_ws(ms.main_ws);
     free_ws(ms.big_ws);
+    free_tree(ms.main_tw);
+    free_tree(ms.big_tw);
     free_forest(ms.fws);
     free_forest(ms.low_ws);
     dfree(ms.leaf);
@@ -667,8 +669,27 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
             rc = alloc_forest(ms.low_ws, ms.low_shape.per_cu * cus, ms.low_shape, 0, stream);
         return rc;
     }
-    const int64_t lcap = max_n + 1;
     const int64_t xmax = max_m + 1;
+    ms.tree = !size.lt && imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus,
+                                           ms.shape);
+    if (ms.tree) {
+        int rc = ensure_leaf(ms.leaf, num_cus);
+        if (rc) return rc;
+        const int64_t lcap = size.nreach + 1;
+        const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
+        free_b += ms.main_tw.bytes;
+        imin::TreeWs one;
+        const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, size.nclaim, 0);
+        const int32_t slots = (int32_t)std::max<size_t>(
+            1, std::min<size_t>((size_t)ms.shape.per_cu * std::max(1, num_cus), (free_b / 4) / per));
+        rc = alloc_tree(ms.main_tw, slots, lcap, xcap, size.nclaim, 0, stream);
+        if (rc) return rc;
+        if (xcap < xmax)
+            return alloc_tree(ms.big_tw, (int32_t)kSpillSlots, lcap, xmax, size.nclaim, 0, stream);
+        free_tree(ms.big_tw);
+        return IMIN_OK;
+    }
+    const int64_t lcap = max_n + 1;
     const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
     free_b += ms.main_ws.bytes;
     const size_t per = slot_bytes(max_n, lcap, xcap, true);
@@ -801,15 +822,28 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
     s.spill_j = ms.sj;
     s.spill_count = ms.ctrl + 1;
     s.error = ms.ctrl + 2;
-    // Linear threshold on graphs that all fit the forest kernel: samples that stay small first,
-    // one per wavefront, then it, the smaller graphs' samples in workgroups sized for those.
-    const bool leaf = ms.forest && shape.pack_per_cu >= 0, split = leaf && ms.split;
+    // Samples that stay small go to the wave-per-sample kernel, one per wavefront: what the
+    // packed kernel hands over, and under linear threshold every sample. Then the kernel for the
+    // large ones; under linear threshold the smaller graphs' in workgroups sized for those.
+    // Hand-overs of the packed kernel that do not give each of its wavefronts one are better off
+    // in whole workgroups: with 750 a round (96 graphs, 2,000 samples each) the wave-per-sample
+    // kernel takes 130 us and saves 40 behind it. With 43,000 a round (48 queries on a 1M-vertex
+    // graph) it takes 0.98 ms and saves 1.68.
+    const bool leaf = (ms.forest || ms.tree) && shape.pack_per_cu >= 0;
+    const bool split = leaf && ms.forest && ms.split;
+    const uint32_t leave = pack ? (uint32_t)imin::leaf_slots(num_cus) : 0;
     if (leaf) {
         imin::LeafArgs f{};
         f.inst = inst;
         f.ninst = ninst;
         f.total = total;
         f.round = round;
+        if (pack) {
+            f.sample_list = ms.pj;
+            f.sample_inst = ms.pi;
+            f.sample_count = ms.ctrl + 7;
+            f.leave = leave;
+        }
         f.next = ms.ctrl + 0;
         f.out_inst = ms.si;
         f.out_j = ms.sj;
@@ -820,7 +854,7 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
             f.low_j = ms.pj;
             f.low_count = ms.ctrl + 7;
         }
-        if (!ok(imin::launch_leaf(f, ms.leaf, imin::leaf_slots(num_cus), true, true, stream)))
+        if (!ok(imin::launch_leaf(f, ms.leaf, imin::leaf_slots(num_cus), true, lt, stream)))
             return IMIN_EDEVICE;
     } else if (!pack && !ok(imin::launch_decrease_small(s, small_grid(num_cus, shape), stream))) {
         return IMIN_EDEVICE;
@@ -845,6 +879,39 @@ int multi_round(MultiScratch &ms, const imin::InstanceDesc *inst, int32_t ninst,
         f.next = ms.ctrl + 3;
         f.ws = ms.fws;
         if (!ok(imin::launch_forest(f, ms.fshape, ms.fws.slots, true, stream))) return IMIN_EDEVICE;
+    } else if (ms.tree) {
+        const bool spill = ms.big_tw.slots > 0;
+        imin::TreeArgs a{};
+        a.theta = total;
+        a.sample_list = ms.sj;
+        a.sample_inst = ms.si;
+        a.sample_count = ms.ctrl + 1;
+        if (leaf) {
+            a.alt_list = ms.pj;
+            a.alt_inst = ms.pi;
+            a.alt_count = ms.ctrl + 7;
+            a.alt_most = leave;
+        }
+        a.next = ms.ctrl + 3;
+        a.ovf_list = ms.oj;
+        a.ovf_count = ms.ctrl + 5;
+        a.error = ms.ctrl + 6;
+        a.spill_ok = spill ? 1 : 0;
+        a.ws = ms.main_tw;
+        a.inst = inst;
+        a.ovf_inst = ms.oi;
+        a.round = round;
+        if (!ok(imin::launch_tree(a, ms.shape, false, stream))) return IMIN_EDEVICE;
+        if (spill) {
+            a.alt_count = nullptr;
+            a.sample_list = ms.oj;
+            a.sample_inst = ms.oi;
+            a.sample_count = ms.ctrl + 5;
+            a.next = ms.ctrl + 4;
+            a.spill_ok = 0;
+            a.ws = ms.big_tw;
+            if (!ok(imin::launch_tree(a, ms.shape, false, stream))) return IMIN_EDEVICE;
+        }
     } else {
         const bool spill = ms.big_ws.slots > 0;
         DecreaseArgs a;
@@ -1832,7 +1899,11 @@ int imin_greedy_batch(imin_instance *inst, int32_t count, int mode, const imin_l
                                     (int64_t)(uintptr_t)ms.main_ws.map, ms.main_ws.slots,
                                     ms.main_ws.n, ms.main_ws.lcap, ms.main_ws.xcap,
                                     (int64_t)(uintptr_t)ms.big_ws.map, ms.big_ws.slots,
-                                    ms.forest ? 1 : 0, ms.split ? 1 : 0,
+                                    ms.tree ? 1 : 0, ms.forest ? 1 : 0, ms.split ? 1 : 0,
+                                    (int64_t)(uintptr_t)ms.main_tw.base, ms.main_tw.slots,
+                                    ms.main_tw.lcap, ms.main_tw.xcap, ms.main_tw.nclaim,
+                                    (int64_t)(uintptr_t)ms.big_tw.base, ms.big_tw.xcap,
+                                    ms.shape.block, (int64_t)ms.shape.lds,
                                     (int64_t)(uintptr_t)ms.leaf, (int64_t)(uintptr_t)ms.fws.base,
                                     ms.fws.entries, ms.fshape.block, ms.fws.slots,
                                     (int64_t)(uintptr_t)ms.low_ws.base, ms.low_ws.entries,

@@ -162,6 +162,9 @@ struct MultiScratch {
     int64_t n = 0, m = 0;      // largest instance it serves
     uint32_t cap = 0;          // samples of the largest round
     Workspace main_ws, big_ws;
+    bool tree = false;         // the LDS-claim kernel takes the hand-overs instead, in these
+    TreeShape shape;
+    TreeWs main_tw, big_tw;
     unsigned char *leaf = nullptr;  // the wave-per-sample form's scratch
     bool forest = false;            // linear threshold: the forest kernel takes the hand-overs,
     bool split = false;             // the smaller graphs' in launches of their own

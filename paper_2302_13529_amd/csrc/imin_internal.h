@@ -185,6 +185,9 @@ struct TreeArgs {
     const uint32_t *sample_inst;
     uint32_t *ovf_inst;
     uint32_t round;
+    // Another list, taken instead where it holds at most alt_most samples.
+    const uint32_t *alt_list, *alt_inst, *alt_count;
+    uint32_t alt_most;
 };
 
 // Linear threshold from the chosen in-edges (forest.hip), for graphs of fewer than 65,533
@@ -246,6 +249,7 @@ struct LeafArgs {
     uint32_t *low_inst;
     uint32_t *low_j;
     uint32_t *low_count;
+    uint32_t leave;            // does nothing where *sample_count is at most this
     int2 *rng;                 // set by launch_leaf
     int4 *extra;
 };

@@ -555,7 +555,13 @@ void tree_kernel(TreeArgs a)
     sv.extra = a.ws.extra + slot * (size_t)a.ws.xcap;
     sv.lid = a.ws.lid + slot * (size_t)a.ws.nclaim;
     sv.planes = a.ws.planes + slot * (size_t)(kTreePlanes * a.ws.words);
-    const uint32_t count = a.sample_list ? *a.sample_count : a.theta;
+    const uint32_t *list = a.sample_list, *insts = a.sample_inst;
+    uint32_t count = list ? *a.sample_count : a.theta;
+    if (kMulti && a.alt_count && *a.alt_count <= a.alt_most) {
+        list = a.alt_list;
+        insts = a.alt_inst;
+        count = *a.alt_count;
+    }
     // samples whose dominator and size steps run in LDS: 6 bytes a vertex over everything
     // behind the scalars
     unsigned char *const over = dyn + free_offset<B>();
@@ -595,9 +601,9 @@ void tree_kernel(TreeArgs a)
         __syncthreads();
         const uint32_t idx = sh.idx;
         if (idx >= count) break;
-        const uint32_t j = a.sample_list ? a.sample_list[idx] : idx;
+        const uint32_t j = list ? list[idx] : idx;
         if (kMulti) {
-            const uint32_t i = __builtin_amdgcn_readfirstlane(a.sample_inst[idx]);
+            const uint32_t i = __builtin_amdgcn_readfirstlane(insts[idx]);
             if (i != cur) {
                 if (cur != 0xFFFFFFFFu) flush_stats();
                 cur = i;
@@ -1068,6 +1074,7 @@ void leaf_kernel(LeafArgs a)
     int2 *rng = a.rng + (size_t)blockIdx.x * kLeafV;
     int4 *extra = a.extra + (size_t)blockIdx.x * kLeafX;
     const uint32_t count = a.sample_list ? *a.sample_count : a.total;
+    if (kMulti && count <= a.leave) return;
     uint32_t cur = 0xFFFFFFFFu, cur_lo = 0, cur_hi = 0;
     bool skip = false, done = false;
     TreeCall c{};
