@@ -1305,8 +1305,10 @@ hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, 
     LeafArgs a = args;
     a.extra = reinterpret_cast<int4 *>(scratch);
     a.rng = reinterpret_cast<int2 *>(scratch + (size_t)slots * kLeafX * sizeof(int4));
-    void (*k)(LeafArgs) = multi ? (lt ? leaf_kernel<true, true> : leaf_kernel<true, false>)
-                                : (lt ? leaf_kernel<false, true> : leaf_kernel<false, false>);
+    if (!multi && !lt) return hipErrorInvalidValue;  // single calls: linear threshold alone
+    void (*k)(LeafArgs) = !multi ? leaf_kernel<false, true>
+                          : lt   ? leaf_kernel<true, true>
+                                 : leaf_kernel<true, false>;
     hipLaunchKernelGGL(k, dim3(slots), dim3(64), 0, stream, a);
     return hipGetLastError();
 }

@@ -140,3 +140,33 @@ def test_linear_threshold_deep_and_equal_weights(gpu):
     check(gpu, n, rp, c, p, [0], None, 20, 1, "lt path", lt=True)
     row_ptr, col, prob = lt_graph(5000, 3, weight=True)
     check(gpu, 5000, row_ptr, col, prob, list(range(30)), None, 100, 1, "lt equal", lt=True)
+
+
+def test_noalloc_marks_of_every_in_degree(gpu):
+    """Blocked vertices with in-degrees around the 16 that one lane walks and the wavefront's
+    64, in runs of neighbours and alone, every call's masks undone by the next."""
+    import torch
+    degrees = [0, 1, 15, 16, 17, 63, 64, 65, 300] * 20
+    first = len(degrees)
+    src, dst = [], []
+    for v, d in enumerate(degrees):
+        src += list(range(first, first + d))
+        dst += [v] * d
+    n = first + 301
+    hub = n - 1
+    src += [hub] * 300 + list(range(first))
+    dst += list(range(first, first + 300)) + [(v + 1) % first for v in range(first)]
+    src, dst = np.array(src), np.array(dst)
+    row_ptr, col, prob = csr(n, src, dst, np.full(src.size, 0.04))
+    g = gpu.Graph(row_ptr, col, prob)
+    for label, marked in (("every one", range(first)), ("none", ()), ("one in 40", range(8, first, 40))):
+        print(f"[case] {label}", flush=True)
+        blocked = np.zeros(n, np.uint8)
+        blocked[list(marked)] = 1
+        out = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+        st = gpu.imin_decrease_noalloc(g.handle, n, [hub], blocked, 200, 5, out.data_ptr())
+        torch.cuda.synchronize()
+        Do, so = orc.decrease(n, row_ptr, col, prob, [hub], blocked, 200, 5)
+        assert np.array_equal(out.cpu().numpy().view(np.uint64), Do), label
+        assert st["reached"] == so["reached"] and st["live_edges"] == so["live_edges"]
+    g.close()
