@@ -237,6 +237,10 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
         int64_t xcap = g->force_xcap > 0 ? g->force_xcap : std::max<int64_t>(4096, lcap / 4);
         xcap = lt ? 1 : std::min(xcap, xmax);
         int32_t slots = g->force_slots;
+        const int32_t most = g->shape.per_cu * g->num_cus;
+        const imin::TreeWs &have = g->main_tw;
+        if (slots <= 0 && have.base && have.lcap == lcap && have.xcap == xcap && have.slots >= most)
+            slots = have.slots;  // as many as can run: the free memory does not matter
         if (slots <= 0) {
             size_t free_b = 0, total_b = 0;
             if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
@@ -244,7 +248,7 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
             imin::TreeWs one;
             const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, nclaim, words);
             const size_t by_mem = std::max<size_t>(1, (free_b / 2) / per);
-            slots = (int32_t)std::min<size_t>((size_t)g->shape.per_cu * g->num_cus, by_mem);
+            slots = (int32_t)std::min<size_t>((size_t)most, by_mem);
             if (max_slots > 0) slots = std::min(slots, max_slots);
             // an allocation that is at least as large stays
             if (g->main_tw.base && g->main_tw.lcap == lcap && g->main_tw.xcap == xcap)
@@ -435,51 +439,121 @@ void append_set_bits(const std::vector<uint32_t> &bits, std::vector<int32_t> &ou
     }
 }
 
-int upload_call_state(imin_graph *g, const std::vector<int32_t> &seeds,
-                      const std::vector<uint32_t> &inelig, uint64_t seed, uint32_t theta)
+// The pinned block of a call that sends so much and returns nb blockers and, if counted, n counts.
+int pin_call(imin_graph *g, size_t nseeds, size_t nundo, size_t nmask, int32_t nb, bool counted)
 {
-    if (!ok(hipMemcpyAsync(g->d_seeds, seeds.data(), seeds.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice, g->stream)) ||
-        !ok(hipMemcpyAsync(g->d_inelig, inelig.data(), inelig.size() * sizeof(uint32_t),
-                           hipMemcpyHostToDevice, g->stream)))
-        return IMIN_EDEVICE;
-    if (!ok(imin::launch_fill_u64(g->d_stats, kStats, 0, g->stream)) ||
-        !ok(imin::launch_fill_u32(g->d_ctrl, 4, 0, g->stream)))
-        return IMIN_EDEVICE;
-    describe(g, (int32_t)seeds.size(), seed, theta);
-    if (!ok(hipMemcpyAsync(g->d_inst, &g->h_inst, sizeof(imin::InstanceDesc),
-                           hipMemcpyHostToDevice, g->stream)))
-        return IMIN_EDEVICE;
+    if (g->in_flight) {  // a call that failed half-way: its kernels may still read the block
+        if (!ok(hipStreamSynchronize(g->stream))) return IMIN_EDEVICE;
+        g->in_flight = false;
+    }
+    auto carve = [&](unsigned char *base) {
+        size_t used = 0;
+        auto take = [&](size_t bytes) {
+            unsigned char *p = base + used;
+            used += (bytes + 255) / 256 * 256;
+            return p;
+        };
+        imin::host::CallPin &c = g->at;
+        c.inst = reinterpret_cast<imin::InstanceDesc *>(take(sizeof(imin::InstanceDesc)));
+        c.stats = reinterpret_cast<unsigned long long *>(take((kClock + 2) * 8));
+        c.ctrl = reinterpret_cast<uint32_t *>(take(16));
+        c.x = reinterpret_cast<int32_t *>(take(4));
+        c.seeds = reinterpret_cast<int32_t *>(take(nseeds * 4));
+        c.undo = reinterpret_cast<int32_t *>(take(nundo * 4));
+        c.mask = reinterpret_cast<int32_t *>(take(nmask * 4));
+        c.B = reinterpret_cast<int32_t *>(take((size_t)nb * 4));
+        c.inelig = reinterpret_cast<uint32_t *>(take((size_t)g->words * 4));
+        c.cand = reinterpret_cast<uint32_t *>(take((size_t)g->words * 4));
+        c.D = reinterpret_cast<unsigned long long *>(take(counted ? (size_t)g->n * 8 : 0));
+        return used;
+    };
+    const size_t need = carve(nullptr);
+    if (need > g->pin_cap) {
+        if (g->pin) (void)hipHostFree(g->pin);
+        g->pin = nullptr;
+        g->pin_cap = 0;
+        void *p = nullptr;
+        if (!ok(hipHostMalloc(&p, need + need / 4, hipHostMallocDefault))) {
+            (void)hipGetLastError();
+            return IMIN_ENOMEM;
+        }
+        g->pin = static_cast<unsigned char *>(p);
+        g->pin_cap = need + need / 4;
+    }
+    carve(g->pin);
+    return IMIN_OK;
+}
+
+// Counts of at most so many vertices return through the pinned block (64 MiB); more are copied
+// by the runtime.
+constexpr int32_t kPinnedCounts = 8 << 20;
+
+bool pinned_counts(const imin_graph *g) { return g->n <= kPinnedCounts; }
+
+// The call's inputs to the device. cand: GreedyReplace's candidates, or null.
+int upload_call_state(imin_graph *g, const std::vector<int32_t> &seeds,
+                      const std::vector<uint32_t> &inelig, const std::vector<uint32_t> *cand,
+                      uint64_t seed, uint32_t theta, int32_t nb, bool counted)
+{
     // Working thresholds: restore the in-edges the previous call masked (all of them when
     // that call stopped half-way), then mask the in-edges of this call's seeds and blocked
     // vertices.
     uint32_t *thr = reinterpret_cast<uint32_t *>(g->d_thr4);
     const uint32_t *orig = reinterpret_cast<const uint32_t *>(g->d_thr_orig);
     g->mask_prev.swap(g->masked);
-    if (!g->mask_known) {
+    const bool known = g->mask_known;
+    g->mask_known = false;
+    g->masked.clear();
+    append_set_bits(inelig, g->masked);
+    if (!known) {
         const int64_t quads = std::max<int64_t>(((int64_t)g->m + 3) / 4, 1);
         if (!ok(hipMemcpyAsync(g->d_thr4, g->d_thr_orig, (size_t)quads * sizeof(uint4),
                                hipMemcpyDeviceToDevice, g->stream)) ||
             (g->mask_rec() && !ok(imin::launch_edge_restore(orig, g->m, g->mask_rec(), g->stream))))
             return IMIN_EDEVICE;
-    } else if (!g->mask_prev.empty()) {
-        if (!ok(hipMemcpyAsync(g->d_list, g->mask_prev.data(),
-                               g->mask_prev.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                               g->stream)) ||
-            !ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge,
-                                       g->d_list, (int32_t)g->mask_prev.size(), 1, g->stream)))
-            return IMIN_EDEVICE;
+        g->mask_prev.clear();
     }
-    g->mask_known = false;
-    g->masked.clear();
-    append_set_bits(inelig, g->masked);
-    if (!g->masked.empty() &&
-        (!ok(hipMemcpyAsync(g->d_list + g->n, g->masked.data(), g->masked.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice, g->stream)) ||
-         !ok(imin::launch_mask_list(thr, g->mask_rec(), orig, g->d_in_ptr, g->d_in_edge,
-                                    g->d_list + g->n, (int32_t)g->masked.size(), 0, g->stream))))
-        return IMIN_EDEVICE;
-    return IMIN_OK;
+    const int rc = pin_call(g, seeds.size(), g->mask_prev.size(), g->masked.size(), nb,
+                            counted && pinned_counts(g));
+    if (rc) return rc;
+    describe(g, (int32_t)seeds.size(), seed, theta);
+    const imin::host::CallPin &c = g->at;
+    *c.inst = g->h_inst;
+    std::copy(seeds.begin(), seeds.end(), c.seeds);
+    std::copy(inelig.begin(), inelig.end(), c.inelig);
+    if (cand) std::copy(cand->begin(), cand->end(), c.cand);
+    std::fill(c.B, c.B + nb, -1);
+    std::copy(g->masked.begin(), g->masked.end(), c.mask);
+    // a vertex masked in both calls stays masked: the kernel's lists have no order
+    int32_t nundo = 0;
+    for (int32_t v : g->mask_prev)
+        if (!((inelig[v >> 5] >> (v & 31)) & 1u)) c.undo[nundo++] = v;
+    imin::CallSetup s{};
+    s.inst = c.inst;
+    s.seeds = c.seeds;
+    s.undo = c.undo;
+    s.mask = c.mask;
+    s.inelig = c.inelig;
+    s.cand = cand ? c.cand : nullptr;
+    s.nseeds = (int32_t)seeds.size();
+    s.nundo = nundo;
+    s.nmask = (int32_t)g->masked.size();
+    s.words = (int32_t)inelig.size();
+    s.nstats = kClock + 2;
+    s.nctrl = 4;
+    s.d_inst = g->d_inst;
+    s.d_seeds = g->d_seeds;
+    s.d_inelig = g->d_inelig;
+    s.d_cand = g->d_cand;
+    s.d_stats = g->d_stats;
+    s.d_ctrl = g->d_ctrl;
+    s.thr = thr;
+    s.rec = g->mask_rec();
+    s.thr_orig = orig;
+    s.in_ptr = g->d_in_ptr;
+    s.in_edge = g->d_in_edge;
+    g->in_flight = true;
+    return ok(imin::launch_call_setup(s, g->stream)) ? IMIN_OK : IMIN_EDEVICE;
 }
 
 // The call ended with the seeds and `blockers` masked.
@@ -490,6 +564,11 @@ void end_masks(imin_graph *g, const std::vector<int32_t> &blockers)
 }
 
 uint32_t *thr_w(imin_graph *g) { return reinterpret_cast<uint32_t *>(g->d_thr4); }
+
+// Rounds are timed on the device's clock, not by events.
+bool round_clock(const imin_graph *g) { return g->tree; }
+
+unsigned long long *clock_of(imin_graph *g) { return round_clock(g) ? g->d_stats + kClock : nullptr; }
 
 // A fresh pair of timing events for one round's decrease launches.
 int kernel_events(imin_graph *g, hipEvent_t *a, hipEvent_t *b)
@@ -513,7 +592,6 @@ int kernel_events(imin_graph *g, hipEvent_t *a, hipEvent_t *b)
 int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_t key,
                     const uint32_t *list, const uint32_t *count, bool reach_only)
 {
-    if (!ok(imin::launch_fill_u32(t.ctrl, 3, 0, g->stream))) return IMIN_EDEVICE;
     if (g->tree) {
         const bool lt = g->model == IMIN_LT;
         const bool spill = t.big_tw->slots > 0;
@@ -974,8 +1052,9 @@ int launch_large(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t key,
 // One call of Algorithm 2 with Philox key seed + call, leaving D on the device. With the
 // wave kernel on, it runs every sample first and leaves the ones that outgrow it to the
 // workgroup kernel, through a device-side list (no host round trip).
+// `restore`: a vertex whose in-edges are unmasked first, or -1.
 int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed, uint32_t call,
-                   bool reach_only = false)
+                   bool reach_only = false, int32_t restore = -1)
 {
     int rc = IMIN_OK;
     if (g->probe == 2) {
@@ -996,23 +1075,36 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         g->small_auto_off = without < with;
     }
     const bool small = small_enabled(g);
-    if ((!reach_only &&
-         !ok(imin::launch_fill_u64(g->d_D, (int64_t)g->n + g->nreach, 0, g->stream))) ||
-        (small && !ok(imin::launch_fill_u32(g->d_sctrl, 2, 0, g->stream))))
-        return IMIN_EDEVICE;
-    hipEvent_t k0, k1;
-    rc = kernel_events(g, &k0, &k1);
-    if (rc) return rc;
-    if (g->probe == 1 || g->probe == 2) {
-        g->probe_kev[g->probe - 1] = g->kev_used - 2;
-        ++g->probe;
+    imin::RoundSetup rs{};
+    rs.D = reach_only ? nullptr : g->d_D;
+    rs.count = (int64_t)g->n + g->nreach;
+    rs.ctrl = g->d_ctrl;
+    rs.sctrl = g->d_sctrl;
+    rs.clock = g->d_stats + kClock;
+    rs.restore = restore;
+    rs.inelig = g->d_inelig;
+    rs.thr = thr_w(g);
+    rs.rec = g->mask_rec();
+    rs.thr_orig = reinterpret_cast<const uint32_t *>(g->d_thr_orig);
+    rs.in_ptr = g->d_in_ptr;
+    rs.in_edge = g->d_in_edge;
+    if (!ok(imin::launch_round_setup(rs, g->stream))) return IMIN_EDEVICE;
+    // The round's time: from here to the next kernel behind the round, on the device's clock. A
+    // pair of events costs a round 15 us; only the choice between the forms needs them.
+    hipEvent_t k0 = nullptr, k1 = nullptr;
+    if (!round_clock(g)) {
+        rc = kernel_events(g, &k0, &k1);
+        if (rc) return rc;
+        if (g->probe == 1 || g->probe == 2) {
+            g->probe_kev[g->probe - 1] = g->kev_used - 2;
+            ++g->probe;
+        }
+        if (!ok(hipEventRecord(k0, g->stream))) return IMIN_EDEVICE;
     }
-    if (!ok(hipEventRecord(k0, g->stream))) return IMIN_EDEVICE;
     if (g->forest && !small) {
         // Linear threshold on a graph that fits the forest kernel: samples that stay small
         // first (automatic mode), then it.
         const bool leaf = g->small_mode == -1;
-        if (!ok(imin::launch_fill_u32(g->d_sctrl, 3, 0, g->stream))) return IMIN_EDEVICE;
         if (leaf) {
             imin::LeafArgs f{};
             f.inst = g->d_inst;
@@ -1050,7 +1142,6 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
                                               g->d_D, g->stream)))
                 return IMIN_EDEVICE;
         }
-        if (!ok(hipEventRecord(k1, g->stream))) return IMIN_EDEVICE;
         return IMIN_OK;
     }
     if (small) {
@@ -1101,20 +1192,22 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         rc = launch_large(g, nseeds, theta, seed + call, nullptr, nullptr, reach_only);
     }
     if (rc) return rc;
-    if (!ok(hipEventRecord(k1, g->stream))) return IMIN_EDEVICE;
+    if (k1 && !ok(hipEventRecord(k1, g->stream))) return IMIN_EDEVICE;
     return IMIN_OK;
 }
 
-// Copies the stats and the error flag back; returns IMIN_EDEVICE if a sample was lost.
-int finish_call(imin_graph *g, imin_stats *stats)
+// Returns the stats, the error flag and the counts (D: null, or the device's, which go to the
+// pinned block) and waits; IMIN_EDEVICE if a sample was lost. last_round: the call's last round
+// is still to be timed.
+int finish_call(imin_graph *g, imin_stats *stats, const unsigned long long *D, bool last_round)
 {
-    unsigned long long st[kStats];
-    uint32_t ctrl[4];
-    if (!ok(hipMemcpyAsync(st, g->d_stats, sizeof(st), hipMemcpyDeviceToHost, g->stream)) ||
-        !ok(hipMemcpyAsync(ctrl, g->d_ctrl, sizeof(ctrl), hipMemcpyDeviceToHost, g->stream)) ||
+    const unsigned long long *st = g->at.stats;
+    if (!ok(imin::launch_call_result(D, g->n, g->at.D, g->d_stats, kClock + 2, g->at.stats, g->d_ctrl,
+                                     4, g->at.ctrl, last_round ? clock_of(g) : nullptr, g->stream)) ||
         !ok(hipEventRecord(g->ev1, g->stream)) || !ok(hipEventSynchronize(g->ev1)))
         return IMIN_EDEVICE;
-    if (ctrl[3] != 0) return IMIN_EDEVICE;
+    g->in_flight = false;
+    if (g->at.ctrl[3] != 0) return IMIN_EDEVICE;
     if (stats) {
         float ms = 0.0f;
         if (!ok(hipEventElapsedTime(&ms, g->ev0, g->ev1))) return IMIN_EDEVICE;
@@ -1126,7 +1219,7 @@ int finish_call(imin_graph *g, imin_stats *stats)
         stats->wave_samples = st[5];
         stats->pack_samples = st[6];
         stats->device_ms = ms;
-        double kms = 0.0;
+        double kms = (double)st[kClock + 1] / (double)g->clock_khz;
         for (size_t i = 0; i + 1 < g->kev_used; i += 2) {
             float x = 0.0f;
             if (!ok(hipEventElapsedTime(&x, g->kev[i], g->kev[i + 1]))) return IMIN_EDEVICE;
@@ -1196,6 +1289,7 @@ void destroy(imin_graph *g)
     dfree(g->d_part_i);
     dfree(g->d_B);
     dfree(g->d_x);
+    if (g->pin) (void)hipHostFree(g->pin);
     for (hipEvent_t e : g->kev) (void)hipEventDestroy(e);
     if (g->ev0) (void)hipEventDestroy(g->ev0);
     if (g->ev1) (void)hipEventDestroy(g->ev1);
@@ -1329,6 +1423,11 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         return IMIN_EDEVICE;
     }
     g->num_cus = std::max(1, prop.multiProcessorCount);
+    if (!ok(hipDeviceGetAttribute(&g->clock_khz, hipDeviceAttributeWallClockRate, g->device)) ||
+        g->clock_khz <= 0) {
+        delete g;
+        return IMIN_EDEVICE;
+    }
     try {
         g->row_ptr.assign(row_ptr, row_ptr + n + 1);
         g->col.assign(col ? col : row_ptr, col ? col + m : row_ptr);
@@ -1469,7 +1568,7 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         ok(hipMalloc(&g->d_seeds, (size_t)n * sizeof(int32_t))) &&
         ok(hipMalloc(&g->d_list, 2 * (size_t)n * sizeof(int32_t))) &&
         ok(hipMalloc(&g->d_D, ((size_t)n + rid_vtx.size()) * sizeof(unsigned long long))) &&
-        ok(hipMalloc(&g->d_stats, kStats * sizeof(unsigned long long))) &&
+        ok(hipMalloc(&g->d_stats, (kClock + 2) * sizeof(unsigned long long))) &&
         ok(hipMalloc(&g->d_ctrl, imin::kCtrlWords * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_sctrl, 3 * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_inst, sizeof(imin::InstanceDesc))) &&
@@ -1595,22 +1694,24 @@ int one_call(imin_graph *g, const int32_t *S, int32_t nS, const uint8_t *blocked
     if (rc) return rc;
     rc = ensure_sj(g, theta);
     if (rc) return rc;
-    rc = upload_call_state(g, seeds, inelig, seed, theta);
+    rc = upload_call_state(g, seeds, inelig, nullptr, seed, theta, 0, !reach_only);
     if (rc) return rc;
     rc = decrease_round(g, (int32_t)seeds.size(), theta, seed, 0, reach_only);
     if (rc) return rc;
+    const bool pinned = pinned_counts(g);
     std::vector<unsigned long long> D;
-    if (!reach_only) {
+    if (!reach_only && !pinned) {
         D.resize((size_t)g->n);
         if (!ok(hipMemcpyAsync(D.data(), g->d_D, (size_t)g->n * sizeof(unsigned long long),
                                hipMemcpyDeviceToHost, g->stream)))
             return IMIN_EDEVICE;
     }
     imin_stats st;
-    rc = finish_call(g, &st);
+    rc = finish_call(g, &st, !reach_only && pinned ? g->d_D : nullptr, true);
     if (rc) return rc;
     end_masks(g, {});
-    if (!reach_only) std::memcpy(counts, D.data(), (size_t)g->n * sizeof(uint64_t));
+    if (!reach_only)
+        std::memcpy(counts, pinned ? g->at.D : D.data(), (size_t)g->n * sizeof(uint64_t));
     if (stats) *stats = st;
     *n_seeds = (int32_t)seeds.size();
     return IMIN_OK;
@@ -1661,55 +1762,44 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
     if (rc) return rc;
     rc = ensure_sj(g, theta);
     if (rc) return rc;
-    rc = ensure_B(g, b);
+    // AG: the rounds; GR: the out-neighbours of the merged seed, seeds excluded (Algorithm 4), and
+    // its first phase's rounds.
+    std::vector<uint32_t> cand;
+    const int32_t most = mode == IMIN_AG ? g->n - ns : gr_candidates(g, seeds, inelig, cand);
+    const int32_t rounds = std::min(b, most);
+    rc = upload_call_state(g, seeds, inelig, mode == IMIN_GR ? &cand : nullptr, seed, theta, rounds,
+                           false);
     if (rc) return rc;
-    rc = upload_call_state(g, seeds, inelig, seed, theta);
-    if (rc) return rc;
+    // the kernels write the blockers, and the last one chosen, into the pinned block
+    const imin::host::CallPin &at = g->at;
 
     std::vector<int32_t> B;
     uint64_t call = 0;
     if (mode == IMIN_AG) {
-        const int32_t rounds = std::min<int32_t>(b, g->n - ns);
         for (int32_t r = 0; r < rounds; ++r) {
             rc = decrease_round(g, ns, theta, seed, call);
             if (rc) return rc;
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_inelig, 0, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, nullptr,
-                                              g->d_B, r, g->d_x, thr_w(g), g->mask_rec(),
-                                              g->d_in_ptr, g->d_in_edge, g->stream)))
+                                              at.B, r, at.x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, clock_of(g), g->stream)))
                 return IMIN_EDEVICE;
         }
-        B.assign((size_t)rounds, -1);
-        if (rounds > 0 &&
-            !ok(hipMemcpyAsync(B.data(), g->d_B, (size_t)rounds * sizeof(int32_t),
-                               hipMemcpyDeviceToHost, g->stream)))
-            return IMIN_EDEVICE;
     } else {
-        // CB: out-neighbours of the merged seed, seeds excluded (Algorithm 4).
-        std::vector<uint32_t> cand;
-        const int32_t ncb = gr_candidates(g, seeds, inelig, cand);
-        if (!ok(hipMemcpyAsync(g->d_cand, cand.data(), cand.size() * sizeof(uint32_t),
-                               hipMemcpyHostToDevice, g->stream)))
-            return IMIN_EDEVICE;
-        const int32_t k = std::min(ncb, b);
+        const int32_t k = rounds;
         for (int32_t r = 0; r < k; ++r) {
             rc = decrease_round(g, ns, theta, seed, call);
             if (rc) return rc;
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_cand, 1, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, g->d_cand,
-                                              g->d_B, r, g->d_x, thr_w(g), g->mask_rec(),
-                                              g->d_in_ptr, g->d_in_edge, g->stream)))
+                                              at.B, r, at.x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, clock_of(g), g->stream)))
                 return IMIN_EDEVICE;
         }
-        B.assign((size_t)k, -1);
-        if (k > 0) {
-            if (!ok(hipMemcpyAsync(B.data(), g->d_B, (size_t)k * sizeof(int32_t),
-                                   hipMemcpyDeviceToHost, g->stream)) ||
-                !ok(hipStreamSynchronize(g->stream)))
-                return IMIN_EDEVICE;
-        }
+        if (k > 0 && !ok(hipStreamSynchronize(g->stream))) return IMIN_EDEVICE;
+        B.assign(at.B, at.B + k);
         for (int32_t v : B)
             if (v < 0) return IMIN_EDEVICE;
         const std::vector<int32_t> snapshot = B;
@@ -1717,33 +1807,25 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
             const int32_t u = snapshot[(size_t)i];
             const int32_t slot =
                 (int32_t)(std::find(B.begin(), B.end(), u) - B.begin());
-            if (!ok(imin::launch_set_bit(g->d_inelig, u, 0, g->stream)) ||
-                !ok(imin::launch_mask_vertex(thr_w(g), g->mask_rec(),
-                                             reinterpret_cast<const uint32_t *>(g->d_thr_orig),
-                                             g->d_in_ptr, g->d_in_edge, u, nullptr, 1,
-                                             g->stream)))
-                return IMIN_EDEVICE;
-            rc = decrease_round(g, ns, theta, seed, call);
+            rc = decrease_round(g, ns, theta, seed, call, false, u);
             if (rc) return rc;
             ++call;
             if (!ok(imin::launch_argmax_apply(g->d_D, g->d_inelig, 0, g->n, g->d_part_d,
                                               g->d_part_i, g->parts, g->d_inelig, nullptr,
-                                              g->d_B, slot, g->d_x, thr_w(g), g->mask_rec(),
-                                              g->d_in_ptr, g->d_in_edge, g->stream)))
-                return IMIN_EDEVICE;
-            int32_t x = -1;
-            if (!ok(hipMemcpyAsync(&x, g->d_x, sizeof(int32_t), hipMemcpyDeviceToHost,
-                                   g->stream)) ||
+                                              at.B, slot, at.x, thr_w(g), g->mask_rec(),
+                                              g->d_in_ptr, g->d_in_edge, clock_of(g), g->stream)) ||
                 !ok(hipStreamSynchronize(g->stream)))
                 return IMIN_EDEVICE;
+            const int32_t x = *at.x;
             if (x < 0) return IMIN_EDEVICE;
             B[(size_t)slot] = x;
             if (x == u) break;
         }
     }
     imin_stats st;
-    rc = finish_call(g, &st);
+    rc = finish_call(g, &st, nullptr, false);
     if (rc) return rc;
+    if (mode == IMIN_AG) B.assign(at.B, at.B + rounds);
     for (int32_t v : B)
         if (v < 0) return IMIN_EDEVICE;
     end_masks(g, B);

@@ -10,6 +10,16 @@
 namespace imin {
 namespace host {
 struct MultiScratch;
+
+// A call's share of the graph's pinned block.
+struct CallPin {
+    imin::InstanceDesc *inst = nullptr;  // sent
+    int32_t *seeds = nullptr, *undo = nullptr, *mask = nullptr;
+    uint32_t *inelig = nullptr, *cand = nullptr;
+    unsigned long long *stats = nullptr, *D = nullptr;  // written by kernels
+    uint32_t *ctrl = nullptr;
+    int32_t *x = nullptr, *B = nullptr;
+};
 }  // namespace host
 }  // namespace imin
 
@@ -58,7 +68,13 @@ struct imin_graph {
                                              // spilled, wave-kernel samples
     uint32_t *d_ctrl = nullptr;              // kCtrlWords: next main, next spill, spill count,
                                              // error (in batched calls: the instance's words)
-    uint32_t *d_sctrl = nullptr;             // 2: wave-kernel work counter, samples it left
+    uint32_t *d_sctrl = nullptr;             // 3: wave-kernel work counter, samples it left,
+                                             // the next kernel's work counter
+    unsigned char *pin = nullptr;            // pinned: what a call sends and what comes back
+    size_t pin_cap = 0;
+    imin::host::CallPin at;                  // the current call's share of it
+    bool in_flight = false;                  // a call's end was not waited for
+    int clock_khz = 0;                       // of the device's wall clock
     uint32_t *d_sj = nullptr;                // samples the wave kernel left to the large one
     uint32_t sj_cap = 0;
     imin::InstanceDesc *d_inst = nullptr;    // this graph as the one instance of a wave launch
@@ -85,7 +101,7 @@ struct imin_graph {
     unsigned char *leaf = nullptr;     // the wave-per-sample form's scratch
     imin::ForestWs fws;
     std::vector<int32_t> masked;       // vertices whose in-edges have threshold 0 in d_thr4
-    std::vector<int32_t> mask_prev;    // the previous call's list, kept while copies run
+    std::vector<int32_t> mask_prev;    // the previous call's list
     bool mask_known = true;            // false while a call runs, and after one that failed
     int32_t *d_list = nullptr;         // 2n: device copies of the two lists above
     std::vector<hipEvent_t> kev;  // pairs around each decrease launch of the current call
@@ -101,6 +117,7 @@ struct imin_graph {
 namespace imin {
 namespace host {
 
+constexpr int kClock = 7;  // behind the stats: a round's start, the rounds' time (clock ticks)
 constexpr int kStats = 7;  // samples, reached, scanned, live, spilled, wave-level kernel
                            // samples, packed-kernel samples
 // The per-launch work counter is 32-bit and every workgroup takes one index past the end.

@@ -401,14 +401,58 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t count, uint32_t value, hipStream
 // Argmax of D over candidates (mode 0: bit of `bits` clear; mode 1: bit of `bits` set),
 // ties to the smallest id. Then: set the winner's bit in `inelig`, clear it in `cand`
 // (if non-null), store it in B[slot] and *out_x, and give its in-edges threshold 0 in `thr`.
-// *out_x = -1 when there is no candidate.
+// *out_x = -1 when there is no candidate. The time since clock[0] is added to clock[1] first
+// (clock null: it is not). B and out_x may lie in pinned host memory.
 hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits, int mode,
                                int32_t n, unsigned long long *part_d, int32_t *part_i,
                                int32_t parts, uint32_t *inelig, uint32_t *cand, int32_t *B,
                                int32_t slot, int32_t *out_x, uint32_t *thr, uint4 *rec,
                                const int32_t *in_ptr, const int32_t *in_edge,
-                               hipStream_t stream);
-hipError_t launch_set_bit(uint32_t *bits, int32_t v, int value, hipStream_t stream);
+                               unsigned long long *clock, hipStream_t stream);
+// What a call sends, read from pinned host memory by one kernel: the graph as an instance, the
+// seeds, the bitmaps (cand: or null), the vertices whose in-edges' thresholds are restored and
+// those whose are 0 in this call (no vertex in both). stats and ctrl start at 0.
+struct CallSetup {
+    const InstanceDesc *inst;
+    const int32_t *seeds, *undo, *mask;
+    const uint32_t *inelig, *cand;
+    int32_t nseeds, nundo, nmask, words, nstats, nctrl;
+    InstanceDesc *d_inst;
+    int32_t *d_seeds;
+    uint32_t *d_inelig, *d_cand;
+    unsigned long long *d_stats;
+    uint32_t *d_ctrl;
+    uint32_t *thr;
+    uint4 *rec;
+    const uint32_t *thr_orig;
+    const int32_t *in_ptr, *in_edge;
+};
+hipError_t launch_call_setup(const CallSetup &s, hipStream_t stream);
+
+// One round's counters at 0 (D: null, or count of them; three words of ctrl and sctrl), its
+// start in clock[0], and the in-edges of vertex `restore` (-1: none) back as created, its bit
+// cleared in inelig.
+struct RoundSetup {
+    unsigned long long *D;
+    int64_t count;
+    uint32_t *ctrl, *sctrl;
+    unsigned long long *clock;
+    int32_t restore;
+    uint32_t *inelig;
+    uint32_t *thr;
+    uint4 *rec;
+    const uint32_t *thr_orig;
+    const int32_t *in_ptr, *in_edge;
+};
+hipError_t launch_round_setup(const RoundSetup &s, hipStream_t stream);
+
+// What a call returns, written to pinned host memory: n counts (D null: none), the stats and
+// control words. Adds the time since clock[0] to clock[1] first (clock null: does not); clock
+// lies among the stats.
+hipError_t launch_call_result(const unsigned long long *D, int64_t n, unsigned long long *out,
+                              unsigned long long *stats, int32_t nstats,
+                              unsigned long long *out_stats, const uint32_t *ctrl, int32_t nctrl,
+                              uint32_t *out_ctrl, unsigned long long *clock, hipStream_t stream);
 // Thresholds of the in-edges of the vertices list[0..count) (device list), or of the one
 // vertex v (host value; or the device-resident id at v_dev when v_dev is non-null, ignored
 // when negative): set to 0 (restore == 0) or copied back from thr_orig (restore != 0).
@@ -416,9 +460,6 @@ hipError_t launch_set_bit(uint32_t *bits, int32_t v, int value, hipStream_t stre
 hipError_t launch_mask_list(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                             const int32_t *in_edge, const int32_t *list, int32_t count,
                             int restore, hipStream_t stream);
-hipError_t launch_mask_vertex(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
-                              const int32_t *in_edge, int32_t v, const int32_t *v_dev,
-                              int restore, hipStream_t stream);
 // Batched greedy over instances inst[0..ninst): zero every instance's D; and per instance,
 // the AdvancedGreedy selection (argmax of D over vertices whose inelig bit is clear, ties to
 // the smallest id), applied as launch_argmax_apply does, with the winner in B[slot] and *x

@@ -56,8 +56,10 @@ __device__ void block_best(unsigned long long &bd, int &bi)
 }
 
 __global__ void argmax_partial_kernel(const unsigned long long *D, const uint32_t *bits, int mode,
-                                      int32_t n, unsigned long long *part_d, int32_t *part_i)
+                                      int32_t n, unsigned long long *part_d, int32_t *part_i,
+                                      unsigned long long *clock)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && clock) clock[1] += wall_clock64() - clock[0];
     unsigned long long bd = 0;
     int bi = -1;
     for (int64_t v = blockIdx.x * (int64_t)kSelBlock + threadIdx.x; v < n;
@@ -104,12 +106,6 @@ __global__ void argmax_final_kernel(const unsigned long long *part_d, const int3
     if (bi >= 0) mask_in_edges(thr, rec, in_ptr, in_edge, bi);
 }
 
-__global__ void set_bit_kernel(uint32_t *bits, int32_t v, int value)
-{
-    if (value) bits[v >> 5] |= 1u << (v & 31);
-    else bits[v >> 5] &= ~(1u << (v & 31));
-}
-
 // In-edge thresholds of list[blockIdx.x ...] (grid-stride over the list): 0, or restored.
 __global__ void mask_list_kernel(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
                                  const int32_t *in_edge, const int32_t *list, int32_t count,
@@ -126,19 +122,86 @@ __global__ void mask_list_kernel(uint32_t *thr, uint4 *rec, const uint32_t *thr_
     }
 }
 
-__global__ void mask_vertex_kernel(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
-                                   const int32_t *in_edge, int32_t v, const int32_t *v_dev,
-                                   int restore)
+// In-edges [first, last) of a vertex: thresholds 0, or as created.
+__device__ __forceinline__ void set_in_edges(uint32_t *thr, uint4 *rec, const uint32_t *orig,
+                                             const int32_t *in_edge, int32_t first, int32_t last,
+                                             int32_t step)
 {
-    const int32_t x = v_dev ? *v_dev : v;
-    if (x < 0) return;
-    for (int64_t k = in_ptr[x] + blockIdx.x * (int64_t)kSelBlock + threadIdx.x; k < in_ptr[x + 1];
-         k += (int64_t)gridDim.x * kSelBlock) {
+#pragma unroll 4
+    for (int32_t k = first; k < last; k += step) {
         const int32_t e = in_edge[k];
-        const uint32_t t = restore ? thr_orig[e] : 0u;
+        const uint32_t t = orig ? orig[e] : 0u;
         thr[e] = t;
         if (rec) rec[e].w = t;
     }
+}
+
+// The call's inputs lie in pinned host memory: one kernel that reads them there replaces five
+// copies and four fills, 10 us of host time each. Blocks take the bitmaps' words and the lists'
+// vertices by turns.
+__global__ void call_setup_kernel(CallSetup s)
+{
+    const int32_t at = blockIdx.x * kSelBlock + threadIdx.x, all = gridDim.x * kSelBlock;
+    if (blockIdx.x == 0) {
+        constexpr int kInst = sizeof(InstanceDesc) / 8;
+        static_assert(sizeof(InstanceDesc) % 8 == 0 && kInst <= kSelBlock, "one thread a word");
+        if (threadIdx.x < kInst)
+            reinterpret_cast<unsigned long long *>(s.d_inst)[threadIdx.x] =
+                reinterpret_cast<const unsigned long long *>(s.inst)[threadIdx.x];
+        if ((int)threadIdx.x < s.nstats) s.d_stats[threadIdx.x] = 0ull;
+        if ((int)threadIdx.x < s.nctrl) s.d_ctrl[threadIdx.x] = 0u;
+    }
+    for (int32_t i = at; i < s.nseeds; i += all) s.d_seeds[i] = s.seeds[i];
+    for (int32_t i = at; i < s.words; i += all) {
+        s.d_inelig[i] = s.inelig[i];
+        if (s.cand) s.d_cand[i] = s.cand[i];
+    }
+    for (int32_t i = blockIdx.x; i < s.nundo + s.nmask; i += gridDim.x) {
+        const bool undo = i < s.nundo;
+        const int32_t v = undo ? s.undo[i] : s.mask[i - s.nundo];
+        set_in_edges(s.thr, s.rec, undo ? s.thr_orig : nullptr, s.in_edge,
+                     s.in_ptr[v] + (int32_t)threadIdx.x, s.in_ptr[v + 1], kSelBlock);
+    }
+}
+
+__global__ void round_setup_kernel(RoundSetup s)
+{
+    const int64_t at = blockIdx.x * (int64_t)kSelBlock + threadIdx.x;
+    const int32_t all = gridDim.x * kSelBlock;
+    if (at < 3) {
+        s.ctrl[at] = 0u;
+        s.sctrl[at] = 0u;
+    }
+    if (at == 0) {
+        s.clock[0] = wall_clock64();
+        if (s.restore >= 0) s.inelig[s.restore >> 5] &= ~(1u << (s.restore & 31));
+    }
+    if (s.D)
+        for (int64_t i = at; i < s.count; i += all) s.D[i] = 0ull;
+    if (s.restore >= 0)
+        set_in_edges(s.thr, s.rec, s.thr_orig, s.in_edge, s.in_ptr[s.restore] + (int32_t)at,
+                     s.in_ptr[s.restore + 1], all);
+}
+
+__global__ void call_result_kernel(const unsigned long long *D, int64_t n, unsigned long long *out,
+                                   unsigned long long *stats, int32_t nstats,
+                                   unsigned long long *out_stats, const uint32_t *ctrl,
+                                   int32_t nctrl, uint32_t *out_ctrl, unsigned long long *clock)
+{
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0 && clock) clock[1] += wall_clock64() - clock[0];
+        __syncthreads();
+        if ((int)threadIdx.x < nstats) out_stats[threadIdx.x] = stats[threadIdx.x];
+        if ((int)threadIdx.x < nctrl) out_ctrl[threadIdx.x] = ctrl[threadIdx.x];
+    }
+    if (!D) return;
+    // 16 bytes a lane: D and out are aligned
+    const ulonglong2 *D2 = reinterpret_cast<const ulonglong2 *>(D);
+    ulonglong2 *out2 = reinterpret_cast<ulonglong2 *>(out);
+    for (int64_t i = blockIdx.x * (int64_t)kSelBlock + threadIdx.x; i < n / 2;
+         i += (int64_t)gridDim.x * kSelBlock)
+        out2[i] = D2[i];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (n & 1)) out[n - 1] = D[n - 1];
 }
 
 __global__ void batch_zero_kernel(const InstanceDesc *inst)
@@ -351,12 +414,12 @@ hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits
                                int32_t parts, uint32_t *inelig, uint32_t *cand, int32_t *B,
                                int32_t slot, int32_t *out_x, uint32_t *thr, uint4 *rec,
                                const int32_t *in_ptr, const int32_t *in_edge,
-                               hipStream_t stream)
+                               unsigned long long *clock, hipStream_t stream)
 {
     int g = grid_for(n);
     if (g > parts) g = parts;
     hipLaunchKernelGGL(argmax_partial_kernel, dim3(g), dim3(kSelBlock), 0, stream, D, bits, mode,
-                       n, part_d, part_i);
+                       n, part_d, part_i, clock);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(argmax_final_kernel, dim3(1), dim3(kSelBlock), 0, stream, part_d, part_i, g,
@@ -364,9 +427,30 @@ hipError_t launch_argmax_apply(const unsigned long long *D, const uint32_t *bits
     return hipGetLastError();
 }
 
-hipError_t launch_set_bit(uint32_t *bits, int32_t v, int value, hipStream_t stream)
+hipError_t launch_call_setup(const CallSetup &s, hipStream_t stream)
 {
-    hipLaunchKernelGGL(set_bit_kernel, dim3(1), dim3(1), 0, stream, bits, v, value);
+    const int64_t items = std::max<int64_t>(std::max(s.nseeds, s.words) / kSelBlock,
+                                            (int64_t)s.nundo + s.nmask);
+    hipLaunchKernelGGL(call_setup_kernel, dim3((uint32_t)std::max<int64_t>(1, std::min<int64_t>(items, 1024))),
+                       dim3(kSelBlock), 0, stream, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_round_setup(const RoundSetup &s, hipStream_t stream)
+{
+    const int grid = std::max(s.D ? std::min(grid_for(s.count), 1024) : 1, s.restore >= 0 ? 16 : 1);
+    hipLaunchKernelGGL(round_setup_kernel, dim3(grid), dim3(kSelBlock), 0, stream, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_call_result(const unsigned long long *D, int64_t n, unsigned long long *out,
+                              unsigned long long *stats, int32_t nstats,
+                              unsigned long long *out_stats, const uint32_t *ctrl, int32_t nctrl,
+                              uint32_t *out_ctrl, unsigned long long *clock, hipStream_t stream)
+{
+    const int grid = D ? std::min(grid_for(n / 2), 1024) : 1;
+    hipLaunchKernelGGL(call_result_kernel, dim3(grid), dim3(kSelBlock), 0, stream, D, n, out, stats,
+                       nstats, out_stats, ctrl, nctrl, out_ctrl, clock);
     return hipGetLastError();
 }
 
@@ -377,15 +461,6 @@ hipError_t launch_mask_list(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig,
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(mask_list_kernel, dim3(std::min<int32_t>(count, 4096)), dim3(kSelBlock), 0,
                        stream, thr, rec, thr_orig, in_ptr, in_edge, list, count, restore);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_vertex(uint32_t *thr, uint4 *rec, const uint32_t *thr_orig, const int32_t *in_ptr,
-                              const int32_t *in_edge, int32_t v, const int32_t *v_dev,
-                              int restore, hipStream_t stream)
-{
-    hipLaunchKernelGGL(mask_vertex_kernel, dim3(16), dim3(kSelBlock), 0, stream, thr, rec, thr_orig,
-                       in_ptr, in_edge, v, v_dev, restore);
     return hipGetLastError();
 }
 
