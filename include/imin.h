@@ -226,7 +226,9 @@ typedef struct {
  * more than 255 vertices, keeps more than 256 non-tree live edges, or meets a frontier
  * chunk over the quad limit is left, with nothing accumulated, to the one-workgroup-per-
  * sample kernel in the same call.
- *   enable  -1 automatic (the default: on for the first round of every call, and off for
+ *   enable  -1 automatic (the default: off for graphs that the LDS-claim kernel or the forest
+ *           kernel takes, which run small samples as well; else on for the first round of
+ *           every call, and off for
  *           the call's later rounds when fewer than half of the first round's samples
  *           finished in the wave kernel; otherwise the second round is timed with it, the
  *           third runs without it as a timed trial, and later rounds keep whichever of the

@@ -728,6 +728,13 @@ void MultiSize::add(const imin_graph *g)
     lt = g->model == IMIN_LT;
 }
 
+// Many-instance rounds on graphs with more reach ids than this hand their larger samples to the
+// LDS-claim kernels: a workgroup of 512 threads pays where samples of 10^4 vertices carry the
+// round. 48 queries on a 1M-vertex graph: 211 ms without, 153 with. On smaller graphs the 2048
+// smaller slots of the other kernel keep more of the short samples in flight: 96 graphs of at
+// most 100,000 vertices 13.2 ms against 13.6, 32 queries on an 8k-vertex graph 10.8 against 12.7.
+constexpr int64_t kMultiTreeReach = 1 << 17;
+
 // The workgroup kernel's slots for many-instance rounds: as many as a compute unit holds,
 // within a quarter of the free memory.
 int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_t stream)
@@ -748,8 +755,8 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
         return rc;
     }
     const int64_t xmax = max_m + 1;
-    ms.tree = !size.lt && imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus,
-                                           ms.shape);
+    ms.tree = !size.lt && size.nreach > kMultiTreeReach &&
+              imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus, ms.shape);
     if (ms.tree) {
         int rc = ensure_leaf(ms.leaf, num_cus);
         if (rc) return rc;

@@ -170,3 +170,31 @@ def test_noalloc_marks_of_every_in_degree(gpu):
         assert np.array_equal(out.cpu().numpy().view(np.uint64), Do), label
         assert st["reached"] == so["reached"] and st["live_edges"] == so["live_edges"]
     g.close()
+
+
+@pytest.mark.parametrize("theta", [400, 5000])
+def test_large_graphs_in_one_batch(gpu, theta):
+    """Problems on a graph with more reach ids than the many-instance rule's 2^17, with fewer and
+    with more hand-overs than there are wavefronts: chains of a few hundred vertices with
+    shortcuts, beyond the packed kernel, on both sides of what one wavefront takes. Each problem
+    equals its own call."""
+    n = 140_001
+    rng = np.random.default_rng(3)
+    v = np.arange(n)
+    src = np.concatenate([v, v])
+    dst = np.concatenate([(v + 1) % n, (v + rng.integers(2, 400, n)) % n])
+    p = np.concatenate([np.full(n, 0.99), np.full(n, 0.006)])
+    row_ptr, col, prob = csr(n, src, dst, p)
+    calls = (([5, 70_000], 1), ([99], 2), ([1000, 1001, 139_999], 3))
+    gs = [gpu.Graph(row_ptr, col, prob) for _ in calls]
+    for mode in (gpu.IMIN_AG, gpu.IMIN_GR):
+        got = gpu.imin_greedy_batch([(g.handle, seeds, 2, theta, key)
+                                     for g, (seeds, key) in zip(gs, calls)], mode, None)
+        for (B, st), g, (seeds, key) in zip(got, gs, calls):
+            Bo, so = g.greedy(seeds, 2, theta, key, mode)
+            assert list(B) == list(Bo)
+            for k in ("samples", "reached", "edges_scanned", "live_edges"):
+                assert st[k] == so[k], (mode, k)
+            assert st["wave_samples"] < st["samples"]
+    for g in gs:
+        g.close()
