@@ -378,8 +378,8 @@ def bench_headline(args) -> dict:
     alg = algorithmic_bytes(st, len(inst.seeds))
     kernel_s = st["kernel_ms"] / 1e3
     achieved = alg / kernel_s / 1e9
-    prof = os.path.join("profiles", "decrease_kernel_rmat22_pmc.txt")
-    src = os.path.join("paper_2302_13529_amd", "csrc", "decrease.hip")
+    prof = os.path.join("profiles", "tree_kernel_rmat22_pmc.txt")
+    src = os.path.join("paper_2302_13529_amd", "csrc", "tree.hip")
     traffic = traffic_from_profile(os.path.join(ROOT, prof), os.path.join(ROOT, src))
     out = line(samples / dt, "samples/s", args.steps, args.warmup, dt * 1e3 / args.steps,
                {"workload": inst.name + ("_lt" if args.model == "lt" else ""),
@@ -394,7 +394,7 @@ def bench_headline(args) -> dict:
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_source": (f"{prof} (rocprofv3 FETCH_SIZE/WRITE_SIZE of this "
                                         f"kernel source, sha256 match)") if traffic else None,
-                     "kernel": "decrease_kernel",
+                     "kernel": "tree_kernel",
                      "algorithmic_bytes_per_launch": alg / launches,
                      "avg_launch_ms": st["kernel_ms"] / launches},
     })
