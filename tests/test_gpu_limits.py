@@ -1,0 +1,69 @@
+"""What a call accepts and what its scratch holds, where the kernels' own sizes could narrow it:
+extra edges that a quarter of the vertices covers, though a quarter of the reachable ones does
+not."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("samples", "reached", "edges_scanned", "live_edges")
+
+
+def csr(n, src, dst, p):
+    order = np.lexsort((dst, src))
+    row_ptr = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(src, minlength=n), out=row_ptr[1:])
+    return row_ptr, dst[order].astype(np.int32), p[order].astype(np.float32)
+
+
+def core_graph(n, core, extra, seed):
+    """Vertices 0..core-1 hang from vertex 0 in a random tree of edges that are always live, with
+    `extra` more such edges among them; the other vertices have no edges."""
+    rng = np.random.default_rng(seed)
+    child = np.arange(1, core)
+    src = np.concatenate([(child * rng.random(core - 1)).astype(np.int64),
+                          rng.integers(1, core, extra)])
+    dst = np.concatenate([child, rng.integers(1, core, extra)])
+    return csr(n, src, dst, np.ones(src.size))
+
+
+def noalloc(gpu, g, n, seeds, blocked, theta, key):
+    import torch
+    out = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+    st = gpu.imin_decrease_noalloc(g.handle, n, seeds, blocked, theta, key, out.data_ptr())
+    torch.cuda.synchronize()
+    return out.cpu().numpy().view(np.uint64), st
+
+
+def test_extra_edges_of_a_quarter_of_the_vertices_do_not_spill(gpu):
+    """17,000 extra edges a sample: more than a quarter of the 6,000 reachable vertices (and than
+    the least capacity, 4,096), fewer than a quarter of the 80,000 there are."""
+    n, theta = 80_000, 20
+    row_ptr, col, prob = core_graph(n, 6000, 17_000, 1)
+    Do, so = orc.decrease(n, row_ptr, col, prob, [0], None, theta, 3)
+    g = gpu.Graph(row_ptr, col, prob)
+    print("[case] extra edges, decrease", flush=True)
+    D, st = g.decrease([0], None, theta, 3)
+    assert np.array_equal(D, Do) and st["spilled"] == 0
+    print("[case] extra edges, noalloc", flush=True)
+    D, st = noalloc(gpu, g, n, [0], None, theta, 3)
+    assert np.array_equal(D, Do) and st["spilled"] == 0
+    assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
+
+
+def test_extra_edges_in_a_batch_do_not_spill(gpu):
+    """The same for a batch on a graph of more than 2^17 reach ids."""
+    n, theta = 500_000, 6
+    row_ptr, col, prob = core_graph(n, 140_000, 90_000, 2)
+    g, h = gpu.Graph(row_ptr, col, prob), gpu.Graph(row_ptr, col, prob)
+    print("[case] extra edges, batch", flush=True)
+    got = gpu.imin_greedy_batch([(g.handle, [0], 1, theta, 3), (h.handle, [0], 1, theta, 4)])
+    for (B, st), key in zip(got, (3, 4)):
+        Bo, so = g.greedy([0], 1, theta, key, gpu.IMIN_AG)
+        assert list(B) == list(Bo) and st["spilled"] == 0 == so["spilled"]
+        assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
+    h.close()
