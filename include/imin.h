@@ -240,6 +240,18 @@ typedef struct {
 IMIN_API int imin_set_small(imin_graph *g, int32_t enable, const imin_launch *launch);
 
 /*
+ * imin_set_workgroup -- the one-workgroup-per-sample kernel of later single calls on g
+ * (imin_decrease, imin_spread, imin_greedy, imin_decrease_noalloc).
+ *   threads  0 the automatic choice (the default); 64, 128, 256, 512 or 1024 the kernel that
+ *            claims vertices in LDS, in workgroups of that size (the forest kernel of
+ *            linear-threshold graphs is left out); -1 under IC the kernel that claims in device
+ *            memory and serves the graphs whose claims do not fit LDS (no effect under LT).
+ * Results never depend on it; it exists so tests can check that. Errors: IMIN_EINVAL for NULL g
+ * or other values, IMIN_ERANGE when the graph's claims do not fit that size.
+ */
+IMIN_API int imin_set_workgroup(imin_graph *g, int32_t threads);
+
+/*
  * One problem of a batched greedy call (imin_greedy_batch); the fields mean what the
  * arguments of imin_greedy mean. Outputs are written only when the whole batch succeeds.
  */

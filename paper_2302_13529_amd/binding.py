@@ -2,9 +2,8 @@
 
 The functions keep the C names (``imin_graph_create``, ``imin_decrease``, ``imin_spread``,
 ``imin_greedy``, ``imin_greedy_batch``, ``imin_set_launch``, ``imin_set_small``,
-``imin_graph_destroy``, ``imin_server_*``, ``imin_strerror``); ``Graph`` and ``Server`` wrap
-them for convenience. Every step
-of the estimate runs in the library's HIP kernels; if the library is missing this module
+``imin_set_workgroup``, ``imin_graph_destroy``, ``imin_server_*``, ``imin_strerror``); ``Graph``
+and ``Server`` wrap them for convenience. Every step of the estimate runs in the library's HIP kernels; if the library is missing this module
 raises instead of computing anything itself.
 """
 from __future__ import annotations
@@ -102,6 +101,8 @@ def load() -> ctypes.CDLL:
     lib.imin_set_launch.restype = ctypes.c_int
     lib.imin_set_small.argtypes = [P, ctypes.c_int32, P]
     lib.imin_set_small.restype = ctypes.c_int
+    lib.imin_set_workgroup.argtypes = [P, ctypes.c_int32]
+    lib.imin_set_workgroup.restype = ctypes.c_int
     lib.imin_greedy_batch.argtypes = [ctypes.POINTER(imin_instance), ctypes.c_int32,
                                       ctypes.c_int, P]
     lib.imin_greedy_batch.restype = ctypes.c_int
@@ -172,6 +173,12 @@ def imin_set_small(handle: int, enable: int = -1, launch=None) -> None:
     rc = load().imin_set_small(ctypes.c_void_p(handle), int(enable), _launch(launch))
     if rc != IMIN_OK:
         raise IminError("imin_set_small", rc)
+
+
+def imin_set_workgroup(handle: int, threads: int = 0) -> None:
+    rc = load().imin_set_workgroup(ctypes.c_void_p(handle), int(threads))
+    if rc != IMIN_OK:
+        raise IminError("imin_set_workgroup", rc)
 
 
 def imin_decrease(handle: int, n: int, seeds, blocked, theta: int, seed: int):
@@ -288,6 +295,9 @@ class Graph:
 
     def set_small(self, enable: int = -1, launch=None) -> None:
         imin_set_small(self.handle, enable, launch)
+
+    def set_workgroup(self, threads: int = 0) -> None:
+        imin_set_workgroup(self.handle, threads)
 
     def close(self) -> None:
         if self.handle:

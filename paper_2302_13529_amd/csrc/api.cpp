@@ -221,14 +221,14 @@ bool small_enabled(const imin_graph *g);
 // max_slots > 0 caps a new allocation (an existing one of the right shape is kept).
 int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach_only)
 {
-    if (g->forest && !small_enabled(g)) {
+    if (forest_on(g) && !small_enabled(g)) {
         const int32_t slots = g->force_slots > 0 ? g->force_slots : g->fshape.per_cu * g->num_cus;
         const int rc = alloc_forest(g->fws, slots, g->fshape, ((int64_t)g->nreach + 31) / 32, g->stream);
         return rc ? rc : ensure_leaf(g->leaf, g->num_cus);
     }
-    if (g->tree) {
+    if (tree_on(g)) {
         imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT, reach_only, theta, g->num_cus,
-                         g->shape);
+                         std::max(g->force_block, 0), g->shape);
         // every reachable vertex and the root fit; only the extra-edge list can overflow (its
         // capacity follows n, not the reach ids: see extra_cap)
         const int64_t lcap = (int64_t)g->nreach + 1, xmax = (int64_t)g->m + 1;
@@ -330,7 +330,7 @@ bool small_enabled(const imin_graph *g)
     if (g->small_mode == 0) return false;
     if (g->small_mode == 1) return true;
     // automatic: the LDS-claim kernel takes small samples as well as large ones
-    return !g->tree && !g->small_auto_off;
+    return !tree_on(g) && !g->small_auto_off;
 }
 
 int small_grid(int num_cus, const imin_launch &l)
@@ -567,7 +567,7 @@ void end_masks(imin_graph *g, const std::vector<int32_t> &blockers)
 uint32_t *thr_w(imin_graph *g) { return reinterpret_cast<uint32_t *>(g->d_thr4); }
 
 // Rounds are timed on the device's clock, not by events.
-bool round_clock(const imin_graph *g) { return g->tree; }
+bool round_clock(const imin_graph *g) { return tree_on(g); }
 
 unsigned long long *clock_of(imin_graph *g) { return round_clock(g) ? g->d_stats + kClock : nullptr; }
 
@@ -593,7 +593,7 @@ int kernel_events(imin_graph *g, hipEvent_t *a, hipEvent_t *b)
 int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_t key,
                     const uint32_t *list, const uint32_t *count, bool reach_only)
 {
-    if (g->tree) {
+    if (tree_on(g)) {
         const bool lt = g->model == IMIN_LT;
         const bool spill = t.big_tw->slots > 0;
         imin::TreeArgs a{};
@@ -757,7 +757,7 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
     }
     const int64_t xmax = max_m + 1;
     ms.tree = !size.lt && size.nreach > kMultiTreeReach &&
-              imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus, ms.shape);
+              imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus, 0, ms.shape);
     if (ms.tree) {
         int rc = ensure_leaf(ms.leaf, num_cus);
         if (rc) return rc;
@@ -1109,7 +1109,7 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         }
         if (!ok(hipEventRecord(k0, g->stream))) return IMIN_EDEVICE;
     }
-    if (g->forest && !small) {
+    if (forest_on(g) && !small) {
         // Linear threshold on a graph that fits the forest kernel: samples that stay small
         // first (automatic mode), then it.
         const bool leaf = g->small_mode == -1;
@@ -1557,7 +1557,7 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     g->nclaim = nclaim;
     g->nreach = (int32_t)rid_vtx.size();
     g->tree = imin::tree_shape(g->nclaim, g->nreach, model == IMIN_LT, false, 1, g->num_cus,
-                               g->shape);
+                               0, g->shape);
     g->forest = g->tree && forest;
     g->fshape = fshape;
     g->nsrc = nsrc;
@@ -1849,6 +1849,19 @@ int imin_set_small(imin_graph *g, int32_t enable, const imin_launch *launch)
     g->small_mode = enable;
     g->small_auto_off = false;
     g->small_launch = launch ? *launch : imin_launch{0, 0, 0, 0, 0};
+    return IMIN_OK;
+}
+
+int imin_set_workgroup(imin_graph *g, int32_t threads)
+{
+    if (!g || (threads != -1 && threads != 0 && threads != 64 && threads != 128 &&
+               threads != 256 && threads != 512 && threads != 1024))
+        return IMIN_EINVAL;
+    imin::TreeShape s;
+    if (threads > 0 && (!g->tree || !imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT,
+                                                      false, 1, g->num_cus, threads, s)))
+        return IMIN_ERANGE;
+    g->force_block = threads;
     return IMIN_OK;
 }
 

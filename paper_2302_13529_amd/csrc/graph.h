@@ -113,6 +113,7 @@ struct imin_graph {
     uint4 *mask_rec() const { return model == IMIN_IC ? d_tedge : nullptr; }
     int32_t force_slots = 0;
     int64_t force_xcap = 0;
+    int32_t force_block = 0;           // imin_set_workgroup
 };
 
 namespace imin {
@@ -125,6 +126,13 @@ constexpr int kStats = 7;  // samples, reached, scanned, live, spilled, wave-lev
 constexpr uint32_t kMaxTheta = 1u << 31;
 
 inline bool ok(hipError_t e) { return e == hipSuccess; }
+
+// The LDS-claim kernel, and before it the forest kernel, run this graph's single calls.
+inline bool tree_on(const imin_graph *g)
+{
+    return g->tree && (g->force_block >= 0 || g->model == IMIN_LT);
+}
+inline bool forest_on(const imin_graph *g) { return g->forest && g->force_block <= 0; }
 
 template <class T>
 void dfree(T *&p)

@@ -265,8 +265,9 @@ hipError_t launch_leaf(const LeafArgs &a, unsigned char *scratch, int slots, boo
 // With dominators 512 threads are preferred: their LDS holds the dominator and size steps of
 // samples up to 13,600 vertices (10,000 samples of that graph, 11,800 vertices each: 8.4 ms
 // with 512 threads, 8.7 with 256, 9.9 with 64).
+// block: that size alone (0: any).
 bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
-                int num_cus, TreeShape &out);
+                int num_cus, int32_t block, TreeShape &out);
 hipError_t launch_tree(const TreeArgs &a, const TreeShape &s, bool lt, hipStream_t stream);
 // D += the sizes Dr by reach id and the counts of the first `slots` slots, which go back to
 // zero.

@@ -191,7 +191,8 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     const bool rng = g->model == IMIN_IC;
     imin::Workspace main_ws, big_ws;
     imin::TreeWs main_tw, big_tw;
-    if (g->tree) {
+    const bool tree = tree_on(g);
+    if (tree) {
         // every reachable vertex and the root fit a slot; as many slots as the array holds,
         // up to the usual count
         const bool lt = g->model == IMIN_LT;
@@ -201,7 +202,8 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         if (!lt && xc < xmax && !carve_tree_ws(c, big_tw, 2, cap, xmax, nclaim, 0))
             return IMIN_ERANGE;
         if (!c.fits) return IMIN_ERANGE;
-        imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus, g->shape);
+        imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus,
+                         std::max(g->force_block, 0), g->shape);
         imin::TreeWs one;
         const size_t per_slot = carve_tree(one, nullptr, 1, cap, xc, nclaim, words);
         const int32_t slots = (int32_t)std::max<size_t>(
@@ -275,7 +277,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
             !ok(imin::launch_fill_u32(w->dirty, w->slots, 0u, st)))
             return IMIN_EDEVICE;
     }
-    if (g->tree && (!ok(imin::launch_fill_u32(main_tw.planes,
+    if (tree && (!ok(imin::launch_fill_u32(main_tw.planes,
                                               (int64_t)main_tw.slots * imin::kTreePlanes *
                                                   main_tw.words, 0u, st)) ||
                     !ok(imin::launch_fill_u64(g->d_D + n, g->nreach, 0ull, st))))
@@ -320,7 +322,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     // the LDS-claim kernel takes every sample itself; the other workgroup kernel those that
     // the wave kernel leaves
     const uint32_t *list = nullptr, *list_count = nullptr;
-    if (!g->tree) {
+    if (!tree) {
         imin::SmallArgs s;
         std::memset(&s, 0, sizeof(s));
         s.inst = g->d_inst;

@@ -1259,9 +1259,12 @@ __global__ void edge_restore_kernel(const uint32_t *thr, int64_t m, uint4 *edge)
 // The shape with workgroups of B threads, if it has more threads at work on `theta` samples
 // than the best so far.
 template <int B>
-void shape_for(int64_t bits, int64_t theta, int num_cus, TreeShape &best, int64_t &best_threads)
+void shape_for(int64_t bits, int64_t theta, int num_cus, int32_t block, TreeShape &best,
+               int64_t &best_threads)
 {
-    const size_t need = head_bytes<B>() + (size_t)((bits + 31) / 32) * 4;
+    if (block && block != B) return;
+    // whole shares of LDS are multiples of 16 bytes
+    const size_t need = head_bytes<B>() + ((size_t)((bits + 31) / 32) * 4 + 15) / 16 * 16;
     if (need > kTreeLds) return;
     const int wgs = (int)std::min<size_t>(256 * kTreeWaves / B, kTreeLds / need);
     const int64_t threads = std::min<int64_t>(theta, (int64_t)wgs * num_cus) * B;
@@ -1314,19 +1317,19 @@ hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, 
 }
 
 bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
-                int num_cus, TreeShape &out)
+                int num_cus, int32_t block, TreeShape &out)
 {
     int64_t threads = 0;
     out = TreeShape{};
     // linear threshold: the bitmap only counts, a part of the reach ids at a time
     const int64_t cap = (int64_t)(kTreeLds - head_bytes<1024>()) * 8;
     const int64_t bits = lt ? std::min((nreach + 3) / 4, cap) : nclaim;
-    if (!reach_only) shape_for<512>(bits, theta, num_cus, out, threads);
-    shape_for<64>(bits, theta, num_cus, out, threads);
-    shape_for<128>(bits, theta, num_cus, out, threads);
-    shape_for<256>(bits, theta, num_cus, out, threads);
-    shape_for<512>(bits, theta, num_cus, out, threads);
-    shape_for<1024>(bits, theta, num_cus, out, threads);
+    if (!reach_only) shape_for<512>(bits, theta, num_cus, block, out, threads);
+    shape_for<64>(bits, theta, num_cus, block, out, threads);
+    shape_for<128>(bits, theta, num_cus, block, out, threads);
+    shape_for<256>(bits, theta, num_cus, block, out, threads);
+    shape_for<512>(bits, theta, num_cus, block, out, threads);
+    shape_for<1024>(bits, theta, num_cus, block, out, threads);
     return threads > 0;
 }
 
