@@ -377,13 +377,18 @@ IMIN_API int imin_server_result(imin_server *s, uint64_t ticket, int32_t *blocke
  *             (written only by the kernels; its contents are undefined if the call fails).
  *   stats     optional host struct, as for imin_decrease (device_ms and kernel_ms are both
  *             the whole call).
- * Limits: the graph's scratch must fit the array -- per workgroup slot about 30 * (n + 1)
- * bytes (38 * (n + 1) under IC, whose slots also keep each reached vertex's row range),
- * plus two large-capacity slots of about that much plus 8 * m bytes when a slot's
- * extra-edge list cannot hold m edges, plus 8 * theta + 8 * nS bytes of lists and n / 8 + n
- * bytes of seed bits and blocked marks -- else IMIN_ERANGE (for example a 2^17-vertex,
- * 10^6-edge graph fits; a 2^22-vertex one does not). Fewer slots than imin_decrease uses
- * may fit, which costs speed, never results.
+ * Limits: the graph's scratch must fit the array, else IMIN_ERANGE (for example a 2^17-vertex,
+ * 10^6-edge graph fits; a 2^22-vertex, 35 * 10^6-edge one does not). With r vertices that have an
+ * in-edge, and x = max(4096, n / 4) extra (non-tree live) edges in a slot, or m where m is less:
+ *   - a workgroup slot takes about 33 * r + 16 * x bytes under IC, 29 * r under LT; the array
+ *     holds at least one (where only that fits, x may be smaller: more samples are re-run);
+ *   - where x < m under IC, one or two large slots of about 32 * r + 16 * m bytes take the
+ *     samples that a slot cannot hold;
+ *   - lists take 8 * theta + 8 * nS bytes, seed bits and blocked marks n / 8 + n.
+ * IC graphs whose vertices of two or more in-edges number more than 1.2 to 1.3 million claim in
+ * device memory: about 38 * (n + 1) + 8 * x bytes a slot, and where x < m two large slots of
+ * 38 * (n + 1) + 8 * m. Fewer slots than imin_decrease uses may fit, which costs speed, never
+ * results.
  * Every call on one GPU shares that GPU's array, so calls that overlap on one GPU race;
  * the call clears what must start at zero and leaves the graph's thresholds as created.
  * Errors: IMIN_EINVAL (as imin_decrease, or d_counts NULL), IMIN_ERANGE, IMIN_EDEVICE.

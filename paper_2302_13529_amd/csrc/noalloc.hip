@@ -132,6 +132,45 @@ bool carve_tree_ws(Carve &c, imin::TreeWs &ws, int32_t slots, int64_t lcap, int6
     return true;
 }
 
+// The LDS-claim kernel's scratch: every reachable vertex and the root fit a slot, and there are
+// as many slots as the rest of the array holds, up to the usual count. An extra edge takes 16
+// bytes here and 8 in the kernel of large claim sets, and a large slot holds all m of them: so
+// there are two only where that costs no slot, and where not even one ordinary slot is left
+// beside a single large one, it holds fewer extra edges. With that, what fits the other kernel's
+// layout fits this one.
+bool carve_tree_call(Carve &c, const imin_graph *g, uint32_t theta, imin::TreeShape &shape,
+                     imin::TreeWs &main_tw, imin::TreeWs &big_tw)
+{
+    const bool lt = g->model == IMIN_LT;
+    const int64_t cap = (int64_t)g->nreach + 1, nclaim = lt ? 0 : g->nclaim;
+    const int64_t words = ((int64_t)g->nreach + 31) / 32, xmax = (int64_t)g->m + 1;
+    int64_t xcap = lt ? 1 : imin::host::extra_cap(g->n, g->m);
+    imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus,
+                     std::max(g->force_block, 0), shape);
+    const int64_t full = (int64_t)shape.per_cu * g->num_cus;
+    auto room = [&](int64_t x) {  // slots of x extra edges in what is left
+        imin::TreeWs one;
+        const size_t per = imin::host::carve_tree(one, nullptr, 1, cap, x, nclaim, words);
+        const size_t used = (c.used + 255) & ~size_t(255);
+        return used > kScratchBytes ? 0 : (int64_t)((kScratchBytes - used) / per);
+    };
+    const Carve start = c;
+    for (int32_t large = lt || xcap >= xmax ? 0 : 2; large >= 0; --large) {
+        c = start;
+        big_tw = imin::TreeWs();
+        if (large > 0 && !carve_tree_ws(c, big_tw, large, cap, xmax, nclaim, 0)) {
+            if (large > 1) continue;
+            return false;
+        }
+        if (large > 1 && room(xcap) < full) continue;
+        if (large == 1)
+            while (xcap > 1 && room(xcap) == 0) xcap /= 2;
+        const int32_t slots = (int32_t)std::max<int64_t>(1, std::min(full, room(xcap)));
+        return carve_tree_ws(c, main_tw, slots, cap, xcap, nclaim, words);
+    }
+    return false;
+}
+
 // Slot-major workgroup-kernel scratch of `slots` slots in the carve.
 bool carve_ws(Carve &c, imin::Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap,
               bool rng)
@@ -193,23 +232,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     imin::TreeWs main_tw, big_tw;
     const bool tree = tree_on(g);
     if (tree) {
-        // every reachable vertex and the root fit a slot; as many slots as the array holds,
-        // up to the usual count
-        const bool lt = g->model == IMIN_LT;
-        const int64_t cap = (int64_t)g->nreach + 1, nclaim = lt ? 0 : g->nclaim;
-        const int64_t words = ((int64_t)g->nreach + 31) / 32;
-        const int64_t xc = lt ? 1 : xcap;
-        if (!lt && xc < xmax && !carve_tree_ws(c, big_tw, 2, cap, xmax, nclaim, 0))
-            return IMIN_ERANGE;
-        if (!c.fits) return IMIN_ERANGE;
-        imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus,
-                         std::max(g->force_block, 0), g->shape);
-        imin::TreeWs one;
-        const size_t per_slot = carve_tree(one, nullptr, 1, cap, xc, nclaim, words);
-        const int32_t slots = (int32_t)std::max<size_t>(
-            1, std::min<size_t>((size_t)g->shape.per_cu * g->num_cus,
-                                (kScratchBytes - c.used) / per_slot));
-        if (!carve_tree_ws(c, main_tw, slots, cap, xc, nclaim, words)) return IMIN_ERANGE;
+        if (!c.fits || !carve_tree_call(c, g, theta, g->shape, main_tw, big_tw)) return IMIN_ERANGE;
     } else {
         if (xcap < xmax && !carve_ws(c, big_ws, n, 2, lcap, xmax, rng)) return IMIN_ERANGE;
         if (!c.fits) return IMIN_ERANGE;

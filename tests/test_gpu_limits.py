@@ -1,6 +1,6 @@
 """What a call accepts and what its scratch holds, where the kernels' own sizes could narrow it:
 extra edges that a quarter of the vertices covers, though a quarter of the reachable ones does
-not."""
+not, and graphs of many edges through the no-allocation call."""
 import numpy as np
 import pytest
 
@@ -67,3 +67,20 @@ def test_extra_edges_in_a_batch_do_not_spill(gpu):
         assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
     g.close()
     h.close()
+
+
+@pytest.mark.parametrize("n, m", [(1 << 18, 8_000_000), (200_000, 10_000_000)])
+def test_noalloc_takes_graphs_of_many_edges(gpu, n, m):
+    """A large slot of all m extra edges takes 16 m bytes, of which one fits the array beside the
+    ordinary slots and two do not."""
+    rng = np.random.default_rng(n)
+    src, dst = rng.integers(0, n, m), rng.integers(0, n, m)
+    row_ptr, col, prob = csr(n, src, dst, 1.0 / np.bincount(dst, minlength=n)[dst])
+    g = gpu.Graph(row_ptr, col, prob)
+    seeds = np.arange(40, dtype=np.int32)
+    print(f"[case] n={n} m={m}", flush=True)
+    D, st = noalloc(gpu, g, n, seeds, None, 300, 3)
+    Do, so = g.decrease(seeds, None, 300, 3)
+    assert np.array_equal(D, Do)
+    assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
