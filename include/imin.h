@@ -385,7 +385,7 @@ IMIN_API int imin_server_result(imin_server *s, uint64_t ticket, int32_t *blocke
  *   - where x < m under IC, one or two large slots of about 32 * r + 16 * m bytes take the
  *     samples that a slot cannot hold;
  *   - lists take 8 * theta + 8 * nS bytes, seed bits and blocked marks n / 8 + n.
- * IC graphs whose vertices of two or more in-edges number more than 1.2 to 1.3 million claim in
+ * IC graphs whose vertices of two or more in-edges number more than 1.2 million claim in
  * device memory: about 38 * (n + 1) + 8 * x bytes a slot, and where x < m two large slots of
  * 38 * (n + 1) + 8 * m. Fewer slots than imin_decrease uses may fit, which costs speed, never
  * results.

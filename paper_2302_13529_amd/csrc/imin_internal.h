@@ -120,6 +120,7 @@ hipError_t launch_flush_counts(const Workspace &ws, int32_t slots, unsigned long
 // samples, slot-major like Workspace's; local id 0 is the merged seed.
 constexpr size_t kTreeLds = 160 * 1024;      // LDS of one compute unit
 constexpr int kTreeWaves = 4;                // waves per SIMD its registers allow
+constexpr int kTreeLeast = 512;              // threads on a compute unit, at least
 constexpr int kTreePlanes = 6;               // bit-sliced reach counters of a slot:
 constexpr uint32_t kTreePlaneMax = 63;       // that many samples before they are drained
 
@@ -258,7 +259,11 @@ size_t leaf_slot_bytes();
 hipError_t launch_leaf(const LeafArgs &a, unsigned char *scratch, int slots, bool multi, bool lt,
                        hipStream_t stream);
 
-// False when nclaim vertices do not fit LDS (independent cascade). The workgroup is the
+// False when nclaim vertices do not fit LDS (independent cascade), or only beside fewer than
+// kTreeLeast threads: from 1,212,033 claims on, one workgroup of 256 threads or less is all that a
+// compute unit could run. On a 4M-vertex R-MAT graph of 1,244,071 claims that takes 79 ms for 1,000
+// samples of 397,000 vertices, 50 for their reachability and 13.4 for 20,000 small samples; the
+// kernel that claims in device memory 82, 41 and 11.8. The workgroup is the
 // smallest with the most threads at work: all sizes run kTreeWaves waves per SIMD where the
 // claims leave room, and smaller workgroups wait less for each other at level ends (20,000
 // reachability samples of a 131k-vertex R-MAT graph: 7.0 ms with 64 threads, 11.2 with 512).

@@ -1330,7 +1330,8 @@ bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_
     shape_for<256>(bits, theta, num_cus, block, out, threads);
     shape_for<512>(bits, theta, num_cus, block, out, threads);
     shape_for<1024>(bits, theta, num_cus, block, out, threads);
-    return threads > 0;
+    if (block == 0 && out.per_cu * out.block < kTreeLeast) out = TreeShape{};
+    return out.block > 0;
 }
 
 hipError_t launch_tree(const TreeArgs &args, const TreeShape &s, bool lt, hipStream_t stream)

@@ -34,3 +34,8 @@ def run_host(tmp_path, program, sources):
 @needs_hipcc
 def test_noalloc_plans(tmp_path):
     assert "plans ok" in run_host(tmp_path, "plan_check.cpp", ["api.cpp", "tree.hip"])
+
+
+@needs_hipcc
+def test_tree_shapes(tmp_path):
+    assert "shapes ok" in run_host(tmp_path, "shape_check.cpp", [])
