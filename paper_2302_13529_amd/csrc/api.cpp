@@ -227,8 +227,7 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
         return rc ? rc : ensure_leaf(g->leaf, g->num_cus);
     }
     if (tree_on(g)) {
-        imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT, reach_only, theta, g->num_cus,
-                         std::max(g->force_block, 0), g->shape);
+        imin::tree_shape(tree_fit(g, theta, reach_only), g->shape);
         // every reachable vertex and the root fit; only the extra-edge list can overflow (its
         // capacity follows n, not the reach ids: see extra_cap)
         const int64_t lcap = (int64_t)g->nreach + 1, xmax = (int64_t)g->m + 1;
@@ -756,8 +755,12 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
         return rc;
     }
     const int64_t xmax = max_m + 1;
-    ms.tree = !size.lt && size.nreach > kMultiTreeReach &&
-              imin::tree_shape(size.nclaim, size.nreach, false, false, 1 << 20, num_cus, 0, ms.shape);
+    imin::TreeFit fit;
+    fit.nclaim = size.nclaim;
+    fit.nreach = size.nreach;
+    fit.theta = 1 << 20;
+    fit.num_cus = num_cus;
+    ms.tree = !size.lt && size.nreach > kMultiTreeReach && imin::tree_shape(fit, ms.shape);
     if (ms.tree) {
         int rc = ensure_leaf(ms.leaf, num_cus);
         if (rc) return rc;
@@ -1238,13 +1241,14 @@ int finish_call(imin_graph *g, imin_stats *stats, const unsigned long long *D, b
     return IMIN_OK;
 }
 
-int begin_call(imin_graph *g)
+int begin_call(imin_graph *g, const std::vector<int32_t> &seeds)
 {
     if (!ok(hipSetDevice(g->device))) return IMIN_EDEVICE;
     g->kev_used = 0;
     g->small_auto_off = false;  // every call tries the wave kernel in its first round
     g->auto_pending = true;
     g->probe = 0;
+    g->seed_edges = out_edges(g, seeds.data(), seeds.size());
     if (!ok(hipEventRecord(g->ev0, g->stream))) return IMIN_EDEVICE;
     return IMIN_OK;
 }
@@ -1556,8 +1560,7 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     g->words = (n + 31) / 32;
     g->nclaim = nclaim;
     g->nreach = (int32_t)rid_vtx.size();
-    g->tree = imin::tree_shape(g->nclaim, g->nreach, model == IMIN_LT, false, 1, g->num_cus,
-                               0, g->shape);
+    g->tree = imin::tree_shape(tree_fit(g, 1, false), g->shape);
     g->forest = g->tree && forest;
     g->fshape = fshape;
     g->nsrc = nsrc;
@@ -1694,7 +1697,7 @@ int one_call(imin_graph *g, const int32_t *S, int32_t nS, const uint8_t *blocked
             inelig[v >> 5] |= 1u << (v & 31);
         }
     }
-    rc = begin_call(g);
+    rc = begin_call(g, seeds);
     if (rc) return rc;
     rc = prepare_workspaces(g, theta, reach_only);
     if (rc) return rc;
@@ -1762,7 +1765,7 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
     int rc = seed_setup(g, S, nS, seeds, inelig);
     if (rc) return rc;
     const int32_t ns = (int32_t)seeds.size();
-    rc = begin_call(g);
+    rc = begin_call(g, seeds);
     if (rc) return rc;
     rc = prepare_workspaces(g, theta);
     if (rc) return rc;
@@ -1857,10 +1860,10 @@ int imin_set_workgroup(imin_graph *g, int32_t threads)
     if (!g || (threads != -1 && threads != 0 && threads != 64 && threads != 128 &&
                threads != 256 && threads != 512 && threads != 1024))
         return IMIN_EINVAL;
+    imin::TreeFit fit = tree_fit(g, 1, false);
+    fit.block = threads;
     imin::TreeShape s;
-    if (threads > 0 && (!g->tree || !imin::tree_shape(g->nclaim, g->nreach, g->model == IMIN_LT,
-                                                      false, 1, g->num_cus, threads, s)))
-        return IMIN_ERANGE;
+    if (threads > 0 && (!g->tree || !imin::tree_shape(fit, s))) return IMIN_ERANGE;
     g->force_block = threads;
     return IMIN_OK;
 }

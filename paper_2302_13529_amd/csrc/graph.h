@@ -114,6 +114,7 @@ struct imin_graph {
     int32_t force_slots = 0;
     int64_t force_xcap = 0;
     int32_t force_block = 0;           // imin_set_workgroup
+    int64_t seed_edges = -1;           // out-edges of the current call's seeds
 };
 
 namespace imin {
@@ -131,6 +132,26 @@ inline bool ok(hipError_t e) { return e == hipSuccess; }
 inline bool tree_on(const imin_graph *g)
 {
     return g->tree && (g->force_block >= 0 || g->model == IMIN_LT);
+}
+// The shape of its launches over theta samples.
+inline TreeFit tree_fit(const imin_graph *g, int64_t theta, bool reach_only)
+{
+    TreeFit f;
+    f.nclaim = g->nclaim;
+    f.nreach = g->nreach;
+    f.lt = g->model == IMIN_LT;
+    f.reach_only = reach_only;
+    f.theta = theta;
+    f.num_cus = g->num_cus;
+    f.seed_edges = g->seed_edges;
+    f.block = std::max(g->force_block, 0);
+    return f;
+}
+inline int64_t out_edges(const imin_graph *g, const int32_t *S, size_t nS)
+{
+    int64_t sum = 0;
+    for (size_t i = 0; i < nS; ++i) sum += g->row_ptr[(size_t)S[i] + 1] - g->row_ptr[(size_t)S[i]];
+    return sum;
 }
 inline bool forest_on(const imin_graph *g) { return g->forest && g->force_block <= 0; }
 

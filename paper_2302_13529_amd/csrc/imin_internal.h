@@ -259,20 +259,27 @@ size_t leaf_slot_bytes();
 hipError_t launch_leaf(const LeafArgs &a, unsigned char *scratch, int slots, bool multi, bool lt,
                        hipStream_t stream);
 
-// False when nclaim vertices do not fit LDS (independent cascade), or only beside fewer than
+// What the launch shape depends on.
+struct TreeFit {
+    int64_t nclaim = 0, nreach = 0;
+    bool lt = false, reach_only = false;
+    int64_t theta = 0;
+    int num_cus = 1;
+    int64_t seed_edges = -1;  // out-edges of the seeds (-1: not known)
+    int32_t block = 0;        // threads of a workgroup (0: any)
+};
+// False when the claims do not fit LDS (independent cascade), or only beside fewer than
 // kTreeLeast threads: from 1,212,033 claims on, one workgroup of 256 threads or less is all that a
 // compute unit could run. On a 4M-vertex R-MAT graph of 1,244,071 claims that takes 79 ms for 1,000
 // samples of 397,000 vertices, 50 for their reachability and 13.4 for 20,000 small samples; the
-// kernel that claims in device memory 82, 41 and 11.8. The workgroup is the
-// smallest with the most threads at work: all sizes run kTreeWaves waves per SIMD where the
+// kernel that claims in device memory 82, 41 and 11.8. Of the sizes with the most threads at work
+// the preferred one is taken, else the smallest: all sizes run kTreeWaves waves per SIMD where the
 // claims leave room, and smaller workgroups wait less for each other at level ends (20,000
 // reachability samples of a 131k-vertex R-MAT graph: 7.0 ms with 64 threads, 11.2 with 512).
 // With dominators 512 threads are preferred: their LDS holds the dominator and size steps of
 // samples up to 13,600 vertices (10,000 samples of that graph, 11,800 vertices each: 8.4 ms
 // with 512 threads, 8.7 with 256, 9.9 with 64).
-// block: that size alone (0: any).
-bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
-                int num_cus, int32_t block, TreeShape &out);
+bool tree_shape(const TreeFit &fit, TreeShape &out);
 hipError_t launch_tree(const TreeArgs &a, const TreeShape &s, bool lt, hipStream_t stream);
 // D += the sizes Dr by reach id and the counts of the first `slots` slots, which go back to
 // zero.

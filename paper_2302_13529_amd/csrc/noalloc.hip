@@ -145,8 +145,7 @@ bool carve_tree_call(Carve &c, const imin_graph *g, uint32_t theta, imin::TreeSh
     const int64_t cap = (int64_t)g->nreach + 1, nclaim = lt ? 0 : g->nclaim;
     const int64_t words = ((int64_t)g->nreach + 31) / 32, xmax = (int64_t)g->m + 1;
     int64_t xcap = lt ? 1 : imin::host::extra_cap(g->n, g->m);
-    imin::tree_shape(g->nclaim, g->nreach, lt, false, theta, g->num_cus,
-                     std::max(g->force_block, 0), shape);
+    imin::tree_shape(imin::host::tree_fit(g, theta, false), shape);
     const int64_t full = (int64_t)shape.per_cu * g->num_cus;
     auto room = [&](int64_t x) {  // slots of x extra edges in what is left
         imin::TreeWs one;
@@ -209,6 +208,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         if (S[i] < 0 || S[i] >= g->n) return IMIN_EINVAL;
         if (blocked && blocked[S[i]]) return IMIN_EINVAL;  // B is a subset of V \ S
     }
+    g->seed_edges = out_edges(g, S, (size_t)nS);
     if (!ok(hipSetDevice(g->device))) return IMIN_EDEVICE;
     unsigned char *base = nullptr;
     int rc = scratch_on(g->device, &base);

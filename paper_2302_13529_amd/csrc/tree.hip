@@ -1256,18 +1256,59 @@ __global__ void edge_restore_kernel(const uint32_t *thr, int64_t m, uint4 *edge)
         edge[e].w = thr[e];
 }
 
-// The shape with workgroups of B threads, if it has more threads at work on `theta` samples
-// than the best so far.
-template <int B>
-void shape_for(int64_t bits, int64_t theta, int num_cus, int32_t block, TreeShape &best,
-               int64_t &best_threads)
+// The workgroup size to take where several keep all the waves at work that the registers allow.
+// A small workgroup waits less for itself at level ends and runs more samples at once; a large
+// one ends the launch's largest sample sooner, and that is what a launch of few or of very
+// different samples waits for. What is known before the call is the samples per slot of 512
+// threads, the size of the graph, and the seeds' out-edges, which bound nothing but go with the
+// samples' sizes (few: most samples end at once, some reach thousands). Kernel times in ms, by
+// threads; 2^n: R-MAT graphs of so many vertices, their seeds drawn at random unless said.
+//   * Linear threshold, reachability too, where 128 was taken once: 10,000 samples from 20 seeds
+//     of 2^20 25.7 with 128, 8.8 with 512; from 100 seeds of a 262k-vertex Chung-Lu graph 7.9 and
+//     6.0. Few samples a slot and few seeds: 2,000 from 20 seeds of 2^20 9.1 with 512, 7.2 with
+//     1024; on graphs as large also 10,000 from one seed, 1.82 and 1.52.
+//   * Reachability: 64, but 256 from few seeds of a graph with large samples: 10,000 from 20 seeds
+//     of 2^17 1.17 and 0.82, but from its 10 largest vertices 4.5 and 5.2; and 512 from few seeds
+//     of the next larger graphs: 10,000 from one of 2^19 1.15 with 256, 0.83 with 512, but 20,000
+//     from 20 2.7 and 3.4.
+//   * Dominators: 512. Few samples a slot from few seeds of a large graph: 1024; 2,000 from 20
+//     seeds of 2^19 1.65 and 1.37, from 100 of 2^18 1.26 and 1.25, from 100 of 2^17 1.04 and 1.33.
+//     Many samples a slot: 256; 10,000 from 100 seeds of 2^17 3.6 and 3.0, of 2^19 7.2 and 5.9, of
+//     a 40k-vertex trivalency graph 0.49 and 0.38, but from 20 seeds of 2^17 0.94 and 1.16, and
+//     from its 10 largest vertices 9.3 and 9.5. From 64 a slot on also from fewer seeds: 50,000
+//     from 20 of 2^17 2.4 and 1.9, but from one 0.92 and 1.24. Graphs of a few thousand vertices
+//     have no large samples: from 20 seeds of 1,000 vertices 10,000 take 0.87 and 0.59, 50,000
+//     3.8, 2.1 and, with 128, 1.4.
+int32_t preferred_block(const TreeFit &f)
 {
-    if (block && block != B) return;
+    const int64_t slots = 2 * (int64_t)std::max(1, f.num_cus), e = f.seed_edges;
+    if (f.lt) {
+        const bool few = f.nreach > (1 << 16) && e <= 4096 && f.theta <= 4 * slots;
+        const bool one = f.nreach > (1 << 18) && e <= 512 && f.theta <= 64 * slots;
+        return e >= 0 && (few || one) ? 1024 : 512;
+    }
+    if (f.reach_only) {
+        if (e < 0 || e > 512 || f.nreach <= (1 << 15)) return 64;
+        return f.nreach > 3 * (1 << 16) && f.theta <= 32 * slots ? 512 : 256;
+    }
+    if (e < 0 || e > 16384) return 512;
+    if (f.nreach > (1 << 16) && e <= (f.nreach > (1 << 17) ? 1024 : 512) && f.theta <= 4 * slots)
+        return 1024;
+    const bool tiny = f.nreach <= 4096;
+    if (f.theta >= 64 * slots && e >= 32) return tiny ? 128 : 256;
+    return f.theta >= 16 * slots && e >= (tiny ? 64 : 512) ? 256 : 512;
+}
+
+// The shape with workgroups of B threads, if it has more threads at work on the samples than the
+// best so far.
+template <int B>
+void shape_for(int64_t bits, const TreeFit &f, TreeShape &best, int64_t &best_threads)
+{
     // whole shares of LDS are multiples of 16 bytes
     const size_t need = head_bytes<B>() + ((size_t)((bits + 31) / 32) * 4 + 15) / 16 * 16;
     if (need > kTreeLds) return;
     const int wgs = (int)std::min<size_t>(256 * kTreeWaves / B, kTreeLds / need);
-    const int64_t threads = std::min<int64_t>(theta, (int64_t)wgs * num_cus) * B;
+    const int64_t threads = std::min<int64_t>(f.theta, (int64_t)wgs * f.num_cus) * B;
     if (threads <= best_threads) return;
     best_threads = threads;
     best.block = B;
@@ -1316,21 +1357,22 @@ hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, 
     return hipGetLastError();
 }
 
-bool tree_shape(int64_t nclaim, int64_t nreach, bool lt, bool reach_only, int64_t theta,
-                int num_cus, int32_t block, TreeShape &out)
+bool tree_shape(const TreeFit &f, TreeShape &out)
 {
     int64_t threads = 0;
     out = TreeShape{};
     // linear threshold: the bitmap only counts, a part of the reach ids at a time
     const int64_t cap = (int64_t)(kTreeLds - head_bytes<1024>()) * 8;
-    const int64_t bits = lt ? std::min((nreach + 3) / 4, cap) : nclaim;
-    if (!reach_only) shape_for<512>(bits, theta, num_cus, block, out, threads);
-    shape_for<64>(bits, theta, num_cus, block, out, threads);
-    shape_for<128>(bits, theta, num_cus, block, out, threads);
-    shape_for<256>(bits, theta, num_cus, block, out, threads);
-    shape_for<512>(bits, theta, num_cus, block, out, threads);
-    shape_for<1024>(bits, theta, num_cus, block, out, threads);
-    if (block == 0 && out.per_cu * out.block < kTreeLeast) out = TreeShape{};
+    const int64_t bits = f.lt ? std::min((f.nreach + 3) / 4, cap) : f.nclaim;
+    for (int32_t b : {preferred_block(f), 64, 128, 256, 512, 1024}) {
+        if (f.block && b != f.block) continue;
+        if (b == 64) shape_for<64>(bits, f, out, threads);
+        else if (b == 128) shape_for<128>(bits, f, out, threads);
+        else if (b == 256) shape_for<256>(bits, f, out, threads);
+        else if (b == 512) shape_for<512>(bits, f, out, threads);
+        else shape_for<1024>(bits, f, out, threads);
+    }
+    if (f.block == 0 && out.per_cu * out.block < kTreeLeast) out = TreeShape{};
     return out.block > 0;
 }
 

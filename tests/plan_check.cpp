@@ -51,7 +51,8 @@ int main()
         g.nreach = (int32_t)(std::min(g.n, g.m) * (u(rng) < 0.5 ? 1.0 : u(rng)));
         g.nclaim = std::min((int32_t)(g.nreach * u(rng)), g.m / 2);
         const uint32_t theta = (uint32_t)log_int(1, 1e6);
-        if (!imin::tree_shape(g.nclaim, g.nreach, g.model == IMIN_LT, false, 1, g.num_cus, 0, g.shape)) continue;
+        g.seed_edges = log_int(1, 1e5);
+        if (!imin::tree_shape(tree_fit(&g, 1, false), g.shape)) continue;
         const Carve start = call_arrays(g, theta, (int32_t)log_int(1, 1e4), u(rng) < 0.5);
         imin::TreeWs main_tw, big_tw;
         Carve c = start;

@@ -10,12 +10,21 @@ using namespace imin;
 int main()
 {
     long taken = 0;
-    for (int64_t nclaim = 0; nclaim <= 1400000; nclaim += nclaim < 5000 ? 1 : 31)
+    for (int64_t nclaim = 0; nclaim <= 1400000; nclaim += nclaim < 2000 ? 1 : 63)
         for (int reach_only = 0; reach_only < 2; ++reach_only)
             for (int64_t theta : {1, 300, 700, 2000, 10000, 1000000})
+                for (int64_t seed_edges : {-1, 40, 1000, 50000})
                 for (int32_t block : {0, 64, 128, 256, 512, 1024}) {
                     TreeShape s;
-                    if (!tree_shape(nclaim, nclaim + nclaim / 2, false, reach_only, theta, 256, block, s)) {
+                    TreeFit f;
+                    f.nclaim = nclaim;
+                    f.nreach = nclaim + nclaim / 2;
+                    f.reach_only = reach_only != 0;
+                    f.theta = theta;
+                    f.num_cus = 256;
+                    f.seed_edges = seed_edges;
+                    f.block = block;
+                    if (!tree_shape(f, s)) {
                         if (block == 0 && nclaim <= 1200000) return std::printf("refused %ld\n", (long)nclaim), 1;
                         continue;
                     }

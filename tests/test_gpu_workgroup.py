@@ -110,3 +110,26 @@ def test_device_claims_automatic_policy(gpu):
         assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
         assert st["wave_samples"] > 0
     g.close()
+
+
+@pytest.mark.parametrize("n, seeds, theta", [(3000, 3, 9000), (3000, 60, 9000), (3000, 60, 33000),
+                                             (70_000, 2, 600), (150_000, 2, 600),
+                                             (40_000, 2, 9000), (280_000, 2, 600)])
+def test_preferred_sizes(gpu, n, seeds, theta):
+    """Each workgroup size that is preferred by samples per slot, graph and seeds' out-edges: the
+    counts are those of 512 threads, spread's too."""
+    rng = np.random.default_rng(n + seeds)
+    src = np.concatenate([np.arange(n), rng.integers(0, n, 4 * n)])
+    dst = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, 4 * n)])
+    for lt in (False, True):
+        p = (0.99 if lt else 0.8) / np.bincount(dst, minlength=n)[dst]
+        g = gpu.Graph(*csr(n, src, dst, p), model=gpu.IMIN_LT if lt else gpu.IMIN_IC)
+        S = rng.choice(n, seeds, replace=False).astype(np.int32)
+        print(f"[case] n {n} seeds {seeds} theta {theta} lt {lt}", flush=True)
+        got = [g.decrease(S, None, theta, 5), g.spread(S, None, theta, 5)]
+        g.set_workgroup(512)
+        want = [g.decrease(S, None, theta, 5), g.spread(S, None, theta, 5)]
+        assert np.array_equal(got[0][0], want[0][0]) and got[1][0] == want[1][0]
+        for (_, a), (_, b) in zip(got, want):
+            assert {k: a[k] for k in KEYS} == {k: b[k] for k in KEYS}
+        g.close()
