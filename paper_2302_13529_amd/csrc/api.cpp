@@ -297,7 +297,11 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
 
 int prepare_workspaces(imin_graph *g, uint32_t theta, bool reach_only = false)
 {
-    return size_workspaces(g, small_enabled(g) ? kSmallModeSlots : 0, theta, reach_only);
+    const int rc = size_workspaces(g, small_enabled(g) ? kSmallModeSlots : 0, theta, reach_only);
+    if (!rc && g->small_mode == -1 && tree_on(g) && !forest_on(g))
+        g->wave_first = many_small(
+            g, theta, std::min(g->main_tw.slots, g->shape.per_cu * g->num_cus), reach_only);
+    return rc;
 }
 
 int ensure_ovf(imin_graph *g, uint32_t theta)
@@ -328,8 +332,9 @@ bool small_enabled(const imin_graph *g)
 {
     if (g->small_mode == 0) return false;
     if (g->small_mode == 1) return true;
-    // automatic: the LDS-claim kernel takes small samples as well as large ones
-    return !tree_on(g) && !g->small_auto_off;
+    // automatic: the LDS-claim kernel takes small samples as well as large ones, unless there are
+    // very many
+    return tree_on(g) ? g->wave_first : !g->small_auto_off;
 }
 
 int small_grid(int num_cus, const imin_launch &l)
@@ -1170,6 +1175,7 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
         s.spill_j = g->d_sj;
         s.spill_count = g->d_sctrl + 1;
         s.error = g->d_ctrl + 3;
+        s.give_up = g->wave_first ? 1 : 0;
         if (!ok(imin::launch_decrease_small(s, small_grid(g->num_cus, g->small_launch),
                                             g->stream)))
             return IMIN_EDEVICE;
@@ -1188,7 +1194,8 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
             const bool drop = g->small_mode == -1 &&
                               (double)handed > (1.0 - kSmallKeepShare) * (double)theta;
             if (drop) g->small_auto_off = true;
-            if (g->small_mode == -1 && !drop && !reach_only) {
+            if (drop) g->wave_first = false;
+            if (g->small_mode == -1 && !drop && !reach_only && !tree_on(g)) {
                 // kept: the next round is timed with the wave kernel (this one waited for
                 // the host), the one after it without
                 g->probe = 1;
@@ -1248,6 +1255,7 @@ int begin_call(imin_graph *g, const std::vector<int32_t> &seeds)
     g->small_auto_off = false;  // every call tries the wave kernel in its first round
     g->auto_pending = true;
     g->probe = 0;
+    g->wave_first = false;
     g->seed_edges = out_edges(g, seeds.data(), seeds.size());
     if (!ok(hipEventRecord(g->ev0, g->stream))) return IMIN_EDEVICE;
     return IMIN_OK;
@@ -1707,6 +1715,7 @@ int one_call(imin_graph *g, const int32_t *S, int32_t nS, const uint8_t *blocked
     if (rc) return rc;
     rc = upload_call_state(g, seeds, inelig, nullptr, seed, theta, 0, !reach_only);
     if (rc) return rc;
+    if (g->wave_first) g->auto_pending = false;  // no later round to judge the first one for
     rc = decrease_round(g, (int32_t)seeds.size(), theta, seed, 0, reach_only);
     if (rc) return rc;
     const bool pinned = pinned_counts(g);

@@ -115,6 +115,7 @@ struct imin_graph {
     int64_t force_xcap = 0;
     int32_t force_block = 0;           // imin_set_workgroup
     int64_t seed_edges = -1;           // out-edges of the current call's seeds
+    bool wave_first = false;           // automatic mode, LDS-claim kernel: many_small's choice
 };
 
 namespace imin {
@@ -152,6 +153,25 @@ inline int64_t out_edges(const imin_graph *g, const int32_t *S, size_t nS)
     int64_t sum = 0;
     for (size_t i = 0; i < nS; ++i) sum += g->row_ptr[(size_t)S[i] + 1] - g->row_ptr[(size_t)S[i]];
     return sum;
+}
+// Calls of the LDS-claim kernel with so many samples that the wave kernel takes the small ones
+// first. 5,120 of those run at once in it, and in the other as many as there are slots; but it
+// costs 0.25 ms at the least, and where most samples are large, a few of them on each wave before
+// it gives up (many out-edges of the seeds make that likely). In ms without and with it:
+//   * claims that leave one slot a compute unit: from 64 samples a slot on. 50,000 samples of a
+//     1M-vertex Chung-Lu graph from one seed 4.1 and 3.3, from 20 13.6 and 10.7, from 100 (all
+//     large) 35.9 and 36.9; 10,000 (39 a slot) from one 1.28 and 1.42;
+//   * more slots: from 131,072 samples on. 200,000 of a 1M-vertex R-MAT graph from one seed 7.2
+//     and 5.7, from 20 23.0 and 20.5; 50,000 of a 131k-vertex Chung-Lu graph 0.91 and 1.17. On
+//     graphs of a few thousand vertices, whose smaller workgroups run 2,048 at once, and for
+//     reachability (up to 4,096) only from seeds of hardly any out-edges: 200,000 samples of a
+//     1,000-vertex graph from one seed 3.2 and 2.2, reachability on 2^17 R-MAT vertices 2.9 and 2.2.
+inline bool many_small(const imin_graph *g, int64_t theta, int64_t slots, bool reach_only)
+{
+    const int64_t e = g->seed_edges;
+    if (g->model != IMIN_IC || e < 0 || e > 4096) return false;
+    if (slots <= g->num_cus) return theta >= 64 * slots;
+    return theta >= 512 * (int64_t)g->num_cus && (e <= 64 || (!reach_only && g->nreach > 4096));
 }
 inline bool forest_on(const imin_graph *g) { return g->forest && g->force_block <= 0; }
 

@@ -267,6 +267,7 @@ struct TreeFit {
     int num_cus = 1;
     int64_t seed_edges = -1;  // out-edges of the seeds (-1: not known)
     int32_t block = 0;        // threads of a workgroup (0: any)
+    int64_t most = 0;         // workgroups there is scratch for (0: any number)
 };
 // False when the claims do not fit LDS (independent cascade), or only beside fewer than
 // kTreeLeast threads: from 1,212,033 claims on, one workgroup of 256 threads or less is all that a
@@ -372,6 +373,8 @@ struct SmallArgs {
     int32_t pick_div;         // runs of samples: about remaining / (pick_div * waves)
     int32_t lt;               // every instance uses the linear-threshold model
     int32_t reach_only;       // count reached vertices only (spread estimates)
+    int32_t give_up;          // single calls: a wave that hands over most of its samples lists
+                              // the others untried
     uint32_t *next;           // work counter
     uint32_t *spill_inst;     // samples left to the large kernel: instance, sample index
     uint32_t *spill_j;

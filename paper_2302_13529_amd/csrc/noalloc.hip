@@ -165,6 +165,11 @@ bool carve_tree_call(Carve &c, const imin_graph *g, uint32_t theta, imin::TreeSh
         if (large == 1)
             while (xcap > 1 && room(xcap) == 0) xcap /= 2;
         const int32_t slots = (int32_t)std::max<int64_t>(1, std::min(full, room(xcap)));
+        if (slots <= g->num_cus) {  // at most one a compute unit: the largest workgroup
+            imin::TreeFit fit = imin::host::tree_fit(g, theta, false);
+            fit.most = slots;
+            imin::tree_shape(fit, shape);
+        }
         return carve_tree_ws(c, main_tw, slots, cap, xcap, nclaim, words);
     }
     return false;
@@ -342,10 +347,15 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     if (!ok(hipEventRecord(g->ev0, st)) ||
         !ok(hipMemcpyAsync(g->d_inst, &I, sizeof(I), hipMemcpyHostToDevice, st)))
         return IMIN_EDEVICE;
-    // the LDS-claim kernel takes every sample itself; the other workgroup kernel those that
-    // the wave kernel leaves
+    // The LDS-claim kernel takes every sample itself, unless there are very many, or 16 and more a
+    // slot on graphs whose slots in the array are fewer than the compute units (where the wave
+    // kernel alone fills the chip: 10,000 samples of a 131k-vertex trivalency graph, 67 slots, 1.80 ms
+    // without it and 0.37 with it; 2,000 from one seed of a 524k-vertex graph, 9 slots, 2.33 and
+    // 0.54; with 8 a slot, 500 from one seed of a 131k-vertex R-MAT graph, 0.18 and 0.30). The
+    // kernel of large claim sets takes those that the wave kernel leaves.
     const uint32_t *list = nullptr, *list_count = nullptr;
-    if (!tree) {
+    const bool few = main_tw.slots < g->num_cus && theta / 16 >= (uint32_t)main_tw.slots;
+    if (!tree || few || many_small(g, theta, main_tw.slots, false)) {
         imin::SmallArgs s;
         std::memset(&s, 0, sizeof(s));
         s.inst = g->d_inst;
@@ -358,6 +368,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         s.spill_j = sj;
         s.spill_count = g->d_sctrl + 1;
         s.error = g->d_ctrl + 3;
+        s.give_up = tree ? 1 : 0;
         if (!ok(imin::launch_decrease_small(s, small_grid(g->num_cus, g->small_launch), st)))
             return IMIN_EDEVICE;
         list = sj;

@@ -345,6 +345,7 @@ __global__ __launch_bounds__(kSmallBlock) void decrease_small_kernel(SmallArgs a
     uint32_t cur_lo = 0, cur_hi = 0;
     bool skip = false;  // the current instance's samples go straight to the large kernel
     bool done = false;  // many-instance launches: the instance's greedy run has ended
+    uint32_t tried = 0, handed = 0;  // this wave's samples
     SeedCache sc;
     sc.total = -1;
     Tally tally{0, 0, 0, 0};
@@ -413,13 +414,17 @@ __global__ __launch_bounds__(kSmallBlock) void decrease_small_kernel(SmallArgs a
                 if (lane == 0) pos = atomicAdd(a.spill_count, cnt);
                 pos = __builtin_amdgcn_readfirstlane(__shfl(pos, 0, 64));
                 for (uint32_t k = (uint32_t)lane; k < cnt; k += 64) {
-                    a.spill_inst[pos + k] = (uint32_t)cur;
+                    if (a.spill_inst) a.spill_inst[pos + k] = (uint32_t)cur;
                     a.spill_j[pos + k] = j + k;
                 }
                 idx += cnt - 1;
                 continue;
             }
-            if (!run_sample<kLT>(a, I, sc, ws, j, tally) && lane == 0) {
+            const bool over = !run_sample<kLT>(a, I, sc, ws, j, tally);
+            tried += 1;
+            handed += over ? 1 : 0;
+            if (a.give_up && handed >= 4 && 4 * handed > 3 * tried) skip = true;
+            if (over && lane == 0) {
                 const uint32_t pos = atomicAdd(a.spill_count, 1u);
                 if (a.spill_inst) {
                     a.spill_inst[pos] = (uint32_t)cur;

@@ -1308,7 +1308,9 @@ void shape_for(int64_t bits, const TreeFit &f, TreeShape &best, int64_t &best_th
     const size_t need = head_bytes<B>() + ((size_t)((bits + 31) / 32) * 4 + 15) / 16 * 16;
     if (need > kTreeLds) return;
     const int wgs = (int)std::min<size_t>(256 * kTreeWaves / B, kTreeLds / need);
-    const int64_t threads = std::min<int64_t>(f.theta, (int64_t)wgs * f.num_cus) * B;
+    int64_t at_work = std::min<int64_t>(f.theta, (int64_t)wgs * f.num_cus);
+    if (f.most > 0) at_work = std::min(at_work, f.most);
+    const int64_t threads = at_work * B;
     if (threads <= best_threads) return;
     best_threads = threads;
     best.block = B;

@@ -80,7 +80,45 @@ def test_noalloc_takes_graphs_of_many_edges(gpu, n, m):
     seeds = np.arange(40, dtype=np.int32)
     print(f"[case] n={n} m={m}", flush=True)
     D, st = noalloc(gpu, g, n, seeds, None, 300, 3)
+    assert st["wave_samples"] > 0  # few slots: the wave kernel takes the small samples
     Do, so = g.decrease(seeds, None, 300, 3)
     assert np.array_equal(D, Do)
     assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
+
+
+def test_noalloc_wave_kernel_gives_up(gpu):
+    """Few slots and only large samples: every wave lists the rest of its samples untried."""
+    n, theta = 300_000, 600
+    row_ptr, col, prob = core_graph(n, 262_000, 1000, 5)
+    g = gpu.Graph(row_ptr, col, prob)
+    print("[case] gives up", flush=True)
+    D, st = noalloc(gpu, g, n, [0], None, theta, 3)
+    Do, so = g.decrease([0], None, theta, 3)
+    assert np.array_equal(D, Do) and st["wave_samples"] == 0
+    assert {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
+
+
+def test_many_small_samples_in_single_calls(gpu):
+    """Claims that leave one slot a compute unit, and 64 samples and more for each: the wave kernel
+    takes the small samples of decrease, spread and a greedy run's rounds."""
+    n, m, theta = 1_000_000, 7_000_000, 17_000
+    rng = np.random.default_rng(8)
+    src, dst = rng.integers(0, n, m), rng.integers(0, n, m)
+    p = 0.9 / np.bincount(dst, minlength=n)[dst]
+    g = gpu.Graph(*csr(n, src, dst, p))
+    seeds = [5, 77, 123_456]
+    print("[case] many small samples", flush=True)
+    got = g.decrease(seeds, None, theta, 3), g.spread(seeds, None, theta, 3)
+    assert got[0][1]["wave_samples"] > theta // 2 and got[1][1]["wave_samples"] > theta // 2
+    B, st = g.greedy(seeds, 3, theta, 3, gpu.IMIN_AG)
+    assert st["wave_samples"] > theta
+    g.set_small(0)
+    want = g.decrease(seeds, None, theta, 3), g.spread(seeds, None, theta, 3)
+    assert np.array_equal(got[0][0], want[0][0]) and got[1][0] == want[1][0]
+    for (_, a), (_, b) in zip(got, want):
+        assert {k: a[k] for k in KEYS} == {k: b[k] for k in KEYS} and b["wave_samples"] == 0
+    Bo, so = g.greedy(seeds, 3, theta, 3, gpu.IMIN_AG)
+    assert list(B) == list(Bo) and {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
     g.close()
