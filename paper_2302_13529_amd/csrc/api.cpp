@@ -460,7 +460,7 @@ int pin_call(imin_graph *g, size_t nseeds, size_t nundo, size_t nmask, int32_t n
         };
         imin::host::CallPin &c = g->at;
         c.inst = reinterpret_cast<imin::InstanceDesc *>(take(sizeof(imin::InstanceDesc)));
-        c.stats = reinterpret_cast<unsigned long long *>(take((kClock + 2) * 8));
+        c.stats = reinterpret_cast<unsigned long long *>(take(kCallStats * 8));
         c.ctrl = reinterpret_cast<uint32_t *>(take(16));
         c.x = reinterpret_cast<int32_t *>(take(4));
         c.seeds = reinterpret_cast<int32_t *>(take(nseeds * 4));
@@ -544,7 +544,7 @@ int upload_call_state(imin_graph *g, const std::vector<int32_t> &seeds,
     s.nundo = nundo;
     s.nmask = (int32_t)g->masked.size();
     s.words = (int32_t)inelig.size();
-    s.nstats = kClock + 2;
+    s.nstats = kCallStats;
     s.nctrl = 4;
     s.d_inst = g->d_inst;
     s.d_seeds = g->d_seeds;
@@ -1220,7 +1220,7 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
 int finish_call(imin_graph *g, imin_stats *stats, const unsigned long long *D, bool last_round)
 {
     const unsigned long long *st = g->at.stats;
-    if (!ok(imin::launch_call_result(D, g->n, g->at.D, g->d_stats, kClock + 2, g->at.stats, g->d_ctrl,
+    if (!ok(imin::launch_call_result(D, g->n, g->at.D, g->d_stats, kCallStats, g->at.stats, g->d_ctrl,
                                      4, g->at.ctrl, last_round ? clock_of(g) : nullptr, g->stream)) ||
         !ok(hipEventRecord(g->ev1, g->stream)) || !ok(hipEventSynchronize(g->ev1)))
         return IMIN_EDEVICE;
@@ -1256,9 +1256,31 @@ int begin_call(imin_graph *g, const std::vector<int32_t> &seeds)
     g->auto_pending = true;
     g->probe = 0;
     g->wave_first = false;
+    g->prefer = 0;
     g->seed_edges = out_edges(g, seeds.data(), seeds.size());
     if (!ok(hipEventRecord(g->ev0, g->stream))) return IMIN_EDEVICE;
     return IMIN_OK;
+}
+
+// A greedy call's first two rounds are on their way: the later ones' workgroup size by the first
+// one's samples, whose counters come back while the second runs.
+int fit_rounds(imin_graph *g, int32_t round, uint32_t theta)
+{
+    if (round > 1 || !tree_on(g) || g->model == IMIN_LT || g->force_block || small_enabled(g))
+        return IMIN_OK;
+    if (round == 0)
+        return ok(imin::launch_call_result(nullptr, 0, nullptr, g->d_stats, kCallStats, g->at.stats,
+                                           g->d_ctrl, 4, g->at.ctrl, nullptr, g->stream)) &&
+                       ok(hipEventRecord(g->ev1, g->stream))
+                   ? IMIN_OK
+                   : IMIN_EDEVICE;
+    if (!ok(hipEventSynchronize(g->ev1))) return IMIN_EDEVICE;
+    g->prefer = imin::block_after(tree_fit(g, theta, false), (double)g->at.stats[1] / (double)theta,
+                                  g->at.stats[imin::kStatLargest]);
+    if (!g->prefer) return IMIN_OK;
+    // the second round still runs in the scratch that this may replace
+    if (!ok(hipStreamSynchronize(g->stream))) return IMIN_EDEVICE;
+    return size_workspaces(g, 0, theta, false);
 }
 
 void destroy(imin_graph *g)
@@ -1587,7 +1609,7 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         ok(hipMalloc(&g->d_seeds, (size_t)n * sizeof(int32_t))) &&
         ok(hipMalloc(&g->d_list, 2 * (size_t)n * sizeof(int32_t))) &&
         ok(hipMalloc(&g->d_D, ((size_t)n + rid_vtx.size()) * sizeof(unsigned long long))) &&
-        ok(hipMalloc(&g->d_stats, (kClock + 2) * sizeof(unsigned long long))) &&
+        ok(hipMalloc(&g->d_stats, kCallStats * sizeof(unsigned long long))) &&
         ok(hipMalloc(&g->d_ctrl, imin::kCtrlWords * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_sctrl, 3 * sizeof(uint32_t))) &&
         ok(hipMalloc(&g->d_inst, sizeof(imin::InstanceDesc))) &&
@@ -1805,6 +1827,7 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
                                               at.B, r, at.x, thr_w(g), g->mask_rec(),
                                               g->d_in_ptr, g->d_in_edge, clock_of(g), g->stream)))
                 return IMIN_EDEVICE;
+            if (rounds >= 4 && (rc = fit_rounds(g, r, theta))) return rc;
         }
     } else {
         const int32_t k = rounds;
@@ -1817,6 +1840,7 @@ int imin_greedy(imin_graph *g, const int32_t *S, int32_t nS, int32_t b, uint32_t
                                               at.B, r, at.x, thr_w(g), g->mask_rec(),
                                               g->d_in_ptr, g->d_in_edge, clock_of(g), g->stream)))
                 return IMIN_EDEVICE;
+            if (k >= 3 && (rc = fit_rounds(g, r, theta))) return rc;
         }
         if (k > 0 && !ok(hipStreamSynchronize(g->stream))) return IMIN_EDEVICE;
         B.assign(at.B, at.B + k);

@@ -115,13 +115,17 @@ struct imin_graph {
     int64_t force_xcap = 0;
     int32_t force_block = 0;           // imin_set_workgroup
     int64_t seed_edges = -1;           // out-edges of the current call's seeds
+    int32_t prefer = 0;                // TreeFit::prefer, for the current call's later rounds
     bool wave_first = false;           // automatic mode, LDS-claim kernel: many_small's choice
 };
 
 namespace imin {
 namespace host {
 
-constexpr int kClock = 7;  // behind the stats: a round's start, the rounds' time (clock ticks)
+constexpr int kClock = 7;  // behind the stats: a round's start, the rounds' time (clock ticks),
+                           // kStatLargest
+constexpr int kCallStats = kStatLargest + 1;
+static_assert(kStatLargest == kClock + 2, "behind the clock");
 constexpr int kStats = 7;  // samples, reached, scanned, live, spilled, wave-level kernel
                            // samples, packed-kernel samples
 // The per-launch work counter is 32-bit and every workgroup takes one index past the end.
@@ -146,6 +150,7 @@ inline TreeFit tree_fit(const imin_graph *g, int64_t theta, bool reach_only)
     f.num_cus = g->num_cus;
     f.seed_edges = g->seed_edges;
     f.block = std::max(g->force_block, 0);
+    f.prefer = g->prefer;
     return f;
 }
 inline int64_t out_edges(const imin_graph *g, const int32_t *S, size_t nS)

@@ -153,6 +153,8 @@ struct TreeShape {
     int32_t bm_words = 0;  // of those, bitmap words
 };
 
+constexpr int kStatLargest = 9;  // of a single call's stats: the largest sample
+
 struct TreeArgs {
     const int32_t *row_ptr;
     const uint4 *edge;       // per edge: the target's row start, row end and reach id, and the
@@ -268,7 +270,11 @@ struct TreeFit {
     int64_t seed_edges = -1;  // out-edges of the seeds (-1: not known)
     int32_t block = 0;        // threads of a workgroup (0: any)
     int64_t most = 0;         // workgroups there is scratch for (0: any number)
+    int32_t prefer = 0;       // the size that block_after gave (0: none)
 };
+// The workgroup size for the rounds after one whose samples reached `mean` vertices and `largest`
+// at most (0: what the other rules give).
+int32_t block_after(const TreeFit &fit, double mean, uint64_t largest);
 // False when the claims do not fit LDS (independent cascade), or only beside fewer than
 // kTreeLeast threads: from 1,212,033 claims on, one workgroup of 256 threads or less is all that a
 // compute unit could run. On a 4M-vertex R-MAT graph of 1,244,071 claims that takes 79 ms for 1,000

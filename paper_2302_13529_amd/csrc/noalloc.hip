@@ -214,6 +214,7 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         if (blocked && blocked[S[i]]) return IMIN_EINVAL;  // B is a subset of V \ S
     }
     g->seed_edges = out_edges(g, S, (size_t)nS);
+    g->prefer = 0;
     if (!ok(hipSetDevice(g->device))) return IMIN_EDEVICE;
     unsigned char *base = nullptr;
     int rc = scratch_on(g->device, &base);

@@ -568,6 +568,7 @@ void tree_kernel(TreeArgs a)
     const int lds_v = min(65535, (int)((a.lds_bytes - free_offset<B>()) / 6));
 
     uint32_t counted = 0;  // samples in the slot's planes
+    int largest = 0;       // sample
     unsigned long long t_samples = 0, t_reached = 0, t_scanned = 0, t_live = 0;
     uint32_t cur = 0xFFFFFFFFu;
     TreeCall c{a.row_ptr, a.edge, a.code, a.thr4, a.tl, a.seeds, a.rid_vtx, a.nseeds, a.nclaim,
@@ -662,6 +663,7 @@ void tree_kernel(TreeArgs a)
         if (tid == 0) {
             t_samples += 1;
             t_reached += (unsigned long long)(nV - 1);
+            largest = max(largest, nV - 1);
         }
         if (a.reach_only || nV == 1) {
             __syncthreads();
@@ -892,7 +894,10 @@ void tree_kernel(TreeArgs a)
         }
     }
     if (!kMulti || cur != 0xFFFFFFFFu) flush_stats();
-    if (!kMulti && tid == 0 && a.count_reach) a.ws.used[slot] = counted;
+    if (!kMulti && tid == 0) {
+        if (a.count_reach) a.ws.used[slot] = counted;
+        if (largest > 0) atomicMax(&a.stats[kStatLargest], (unsigned long long)largest);
+    }
 }
 
 // The same for samples of at most kLeafV vertices: one wavefront per sample, sixteen samples
@@ -1359,6 +1364,22 @@ hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, 
     return hipGetLastError();
 }
 
+// A greedy run's later rounds know the first one's samples. Where none is large, small workgroups
+// do them all, and the threads at work count for less. Eight rounds, in ms, trivalency graphs:
+// 2,000 samples of 222 vertices 1.48 with 64 threads, 2.04 with 512; of 758 (1,000 at the most) 2.31
+// with 256, 2.72 with 512, and 500 of those 1.16 with 256, 1.63 with 1024, 1,000 1.57 with 128, 1.79
+// with 256; 10,000 of 28 2.85 with 64, 2.45 with 128, 3.10 with 512; of 12 2.15 with 256, 2.38 with
+// 512, but of one 1.79 and 1.46.
+int32_t block_after(const TreeFit &f, double mean, uint64_t largest)
+{
+    const int64_t slots = 2 * (int64_t)std::max(1, f.num_cus);
+    if (largest > 4096) return 0;
+    if (largest > 512)
+        return mean < 48.0 ? 0 : mean < 1024.0 && f.theta > slots && f.theta <= 2 * slots ? 128 : 256;
+    if (f.theta >= 16 * slots && mean < 64.0) return mean >= 16.0 ? 128 : mean >= 6.0 ? 256 : 0;
+    return mean >= 16.0 ? 64 : 0;
+}
+
 bool tree_shape(const TreeFit &f, TreeShape &out)
 {
     int64_t threads = 0;
@@ -1366,14 +1387,27 @@ bool tree_shape(const TreeFit &f, TreeShape &out)
     // linear threshold: the bitmap only counts, a part of the reach ids at a time
     const int64_t cap = (int64_t)(kTreeLds - head_bytes<1024>()) * 8;
     const int64_t bits = f.lt ? std::min((f.nreach + 3) / 4, cap) : f.nclaim;
-    for (int32_t b : {preferred_block(f), 64, 128, 256, 512, 1024}) {
-        if (f.block && b != f.block) continue;
+    auto consider = [&](int32_t b) {
         if (b == 64) shape_for<64>(bits, f, out, threads);
         else if (b == 128) shape_for<128>(bits, f, out, threads);
         else if (b == 256) shape_for<256>(bits, f, out, threads);
         else if (b == 512) shape_for<512>(bits, f, out, threads);
         else shape_for<1024>(bits, f, out, threads);
+    };
+    // A size that block_after gave. And 512 where that many slots take the samples at once, and 1024
+    // threads would have to take them in turns on as many compute units: 500 samples from the 10
+    // largest of 40,111 vertices (weighted cascade, 9,770 vertices each) 0.47 ms with 512, 0.58
+    // with 1024; not for samples of few seeds (50: 0.12 and 0.09, trivalency), nor on larger graphs
+    // (500 from 100 seeds of 2^18 R-MAT vertices 0.98 and 0.73).
+    const int64_t slots = 2 * (int64_t)std::max(1, f.num_cus);
+    const bool at_once = !f.lt && !f.reach_only && f.theta <= slots && f.theta > slots / 2 &&
+                         f.seed_edges >= 2048 && f.nreach <= (1 << 16);
+    if (!f.block && (f.prefer || at_once)) {
+        consider(f.prefer ? f.prefer : 512);
+        if (out.per_cu * out.block >= kTreeLeast) return true;
     }
+    for (int32_t b : {preferred_block(f), 64, 128, 256, 512, 1024})
+        if (!f.block || b == f.block) consider(b);
     if (f.block == 0 && out.per_cu * out.block < kTreeLeast) out = TreeShape{};
     return out.block > 0;
 }

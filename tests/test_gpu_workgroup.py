@@ -133,3 +133,28 @@ def test_preferred_sizes(gpu, n, seeds, theta):
         for (_, a), (_, b) in zip(got, want):
             assert {k: a[k] for k in KEYS} == {k: b[k] for k in KEYS}
         g.close()
+
+
+@pytest.mark.parametrize("n, p, seeds, theta", [(2000, 0.25, 20, 300), (2000, 0.32, 20, 1000),
+                                                (4000, 0.9, 3, 300), (4000, 0.9, 3, 1000),
+                                                (2000, 0.1, 6, 9000), (2000, 0.15, 12, 9000)])
+def test_rounds_after_small_samples(gpu, n, p, seeds, theta):
+    """A greedy run whose first round's samples are small changes its workgroup size: the rounds
+    after it are the oracle's, and those of one size."""
+    rng = np.random.default_rng(int(1000 * p) + theta)
+    src = np.concatenate([np.arange(n), rng.integers(0, n, 2 * n)])
+    dst = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, 2 * n)])
+    graph = csr(n, src, dst, np.full(src.size, p))
+    S = rng.choice(n, seeds, replace=False).astype(np.int32)
+    g = gpu.Graph(*graph)
+    for mode in (gpu.IMIN_AG, gpu.IMIN_GR):
+        print(f"[case] n {n} p {p} theta {theta} mode {mode}", flush=True)
+        g.set_workgroup(0)
+        B, st = g.greedy(S, 5, theta, 3, mode)
+        g.set_workgroup(512)
+        B5, s5 = g.greedy(S, 5, theta, 3, mode)
+        assert list(B) == list(B5) and {k: st[k] for k in KEYS} == {k: s5[k] for k in KEYS}
+        if theta <= 300:
+            Bo, _, so = orc.greedy(n, *graph, S, 5, theta, 3, mode)
+            assert list(B) == list(Bo) and {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
+    g.close()
