@@ -380,9 +380,9 @@ IMIN_API int imin_server_result(imin_server *s, uint64_t ticket, int32_t *blocke
  * Limits: the graph's scratch must fit the array, else IMIN_ERANGE (for example a 2^17-vertex,
  * 10^6-edge graph fits; a 2^22-vertex, 35 * 10^6-edge one does not). With r vertices that have an
  * in-edge, and x = max(4096, n / 4) extra (non-tree live) edges in a slot, or m where m is less:
- *   - a workgroup slot takes about 33 * r + 16 * x bytes under IC, 29 * r under LT; the array
+ *   - a workgroup slot takes about 25 * r + 16 * x bytes; the array
  *     holds at least one (where only that fits, x may be smaller: more samples are re-run);
- *   - where x < m under IC, one or two large slots of about 32 * r + 16 * m bytes take the
+ *   - where x < m under IC, one or two large slots of about 24 * r + 16 * m bytes take the
  *     samples that a slot cannot hold;
  *   - lists take 8 * theta + 8 * nS bytes, seed bits and blocked marks n / 8 + n.
  * IC graphs whose vertices of two or more in-edges number more than 1.2 million claim in

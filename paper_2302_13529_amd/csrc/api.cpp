@@ -129,16 +129,14 @@ size_t carve_tree(imin::TreeWs &ws, unsigned char *base, int32_t slots, int64_t 
     ws.xcap = xcap;
     ws.nclaim = nclaim;
     ws.words = words;
+    take(ws.planes, imin::kTreePlanes * words);
+    take(ws.used, 1);
     take(ws.rng, lcap);
-    take(ws.dom, lcap);
     take(ws.rid, lcap);
     take(ws.par, lcap);
     take(ws.acc, lcap);
     take(ws.lvl, lcap + 1);
-    take(ws.lid, nclaim);
     take(ws.extra, xcap);
-    take(ws.planes, imin::kTreePlanes * words);
-    take(ws.used, 1);
     return at;
 }
 
@@ -186,27 +184,33 @@ int ensure_leaf(unsigned char *&leaf, int num_cus)
     return IMIN_OK;
 }
 
+// reach_bytes: space from the row ranges on, at least.
 int alloc_tree(imin::TreeWs &ws, int32_t slots, int64_t lcap, int64_t xcap, int64_t nclaim,
-               int64_t words, hipStream_t stream)
+               int64_t words, hipStream_t stream, size_t reach_bytes = 0)
 {
     if (ws.base && ws.slots == slots && ws.lcap == lcap && ws.xcap == xcap &&
-        ws.nclaim == nclaim && ws.words == words)
+        ws.nclaim == nclaim && ws.words == words && ws.reach_bytes >= reach_bytes)
         return IMIN_OK;
+    reach_bytes = std::max(reach_bytes, ws.reach_bytes);
     free_tree(ws);
     imin::TreeWs w;
-    const size_t bytes = carve_tree(w, nullptr, slots, lcap, xcap, nclaim, words);
+    size_t bytes = carve_tree(w, nullptr, slots, lcap, xcap, nclaim, words);
     unsigned char *base = nullptr;
-    if (!ok(hipMalloc(&base, bytes))) {
+    // the arrays ahead of the row ranges end here
+    const size_t ahead = carve_tree(w, nullptr, slots, 0, 0, 0, words);
+    bytes = std::max(bytes, ahead + reach_bytes);
+    if (!ok(hipMalloc(&base, std::max<size_t>(bytes, 256)))) {
         (void)hipGetLastError();
         return IMIN_ENOMEM;
     }
     carve_tree(w, base, slots, lcap, xcap, nclaim, words);
     w.base = base;
     w.bytes = bytes;
+    w.reach_bytes = reach_bytes;
     ws = w;
     // the planes start at zero; every launch leaves them so once they are drained
-    if (!ok(hipMemsetAsync(ws.planes, 0, (size_t)slots * imin::kTreePlanes * (size_t)words * 4,
-                           stream))) {
+    if (slots > 0 && !ok(hipMemsetAsync(ws.planes, 0,
+                                        (size_t)slots * imin::kTreePlanes * (size_t)words * 4, stream))) {
         free_tree(ws);
         return IMIN_EDEVICE;
     }
@@ -237,9 +241,41 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
         const int64_t xcap = lt                    ? 1
                              : g->force_xcap > 0 ? std::min(g->force_xcap, xmax)
                                                  : extra_cap(g->n, g->m);
-        int32_t slots = g->force_slots;
-        const int32_t most = g->shape.per_cu * g->num_cus;
+        // as many slots as can run, and no more than a call of about so many samples fills
+        int64_t filled = 2 * (int64_t)g->num_cus;
+        while (filled < (int64_t)theta) filled *= 2;
+        const int32_t most = (int32_t)std::min<int64_t>((int64_t)g->shape.per_cu * g->num_cus, filled);
         const imin::TreeWs &have = g->main_tw;
+        if (reach_only) {
+            // The row ranges are all that reachability needs: a slot takes 8 bytes a reach id
+            // where dominators take 25, and the many small workgroups share the space of the
+            // fewer large ones of the other calls. More than two a compute unit take a sixteenth
+            // of the device's memory at most.
+            const size_t per = (size_t)lcap * sizeof(int2);
+            const int64_t there =
+                have.base ? (int64_t)((size_t)(have.base + have.bytes -
+                                               reinterpret_cast<unsigned char *>(have.rng)) / per) : 0;
+            int64_t want = g->force_slots > 0 ? g->force_slots : most;
+            if (there < want && g->force_slots <= 0) {
+                size_t free_b = 0, total_b = 0;
+                if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
+                want = std::min<int64_t>(want, std::max<size_t>(1, ((free_b + have.bytes) / 2) / per));
+                want = std::min<int64_t>(want, std::max<size_t>(2 * (size_t)g->num_cus, total_b / 16 / per));
+                if (max_slots > 0) want = std::min<int64_t>(want, max_slots);
+                want = std::max(want, there);
+            }
+            if (there < want) {
+                const int rc = alloc_tree(g->main_tw, have.slots, lcap, have.slots > 0 ? have.xcap : xcap,
+                                          nclaim, words, g->stream, (size_t)want * per);
+                if (rc) return rc;
+            }
+            g->reach_tw = imin::TreeWs();
+            g->reach_tw.slots = (int32_t)want;
+            g->reach_tw.lcap = lcap;
+            g->reach_tw.rng = g->main_tw.rng;
+            return IMIN_OK;
+        }
+        int32_t slots = g->force_slots;
         if (slots <= 0 && have.base && have.lcap == lcap && have.xcap == xcap && have.slots >= most)
             slots = have.slots;  // as many as can run: the free memory does not matter
         if (slots <= 0) {
@@ -300,7 +336,9 @@ int prepare_workspaces(imin_graph *g, uint32_t theta, bool reach_only = false)
     const int rc = size_workspaces(g, small_enabled(g) ? kSmallModeSlots : 0, theta, reach_only);
     if (!rc && g->small_mode == -1 && tree_on(g) && !forest_on(g))
         g->wave_first = many_small(
-            g, theta, std::min(g->main_tw.slots, g->shape.per_cu * g->num_cus), reach_only);
+            g, theta,
+            std::min((reach_only ? g->reach_tw : g->main_tw).slots, g->shape.per_cu * g->num_cus),
+            reach_only);
     return rc;
 }
 
@@ -1061,7 +1099,8 @@ int launch_large(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t key,
                  const uint32_t *list, const uint32_t *count, bool reach_only = false)
 {
     LargeTarget t{g->d_thr4, g->d_seeds, nseeds, g->d_D, g->d_stats, g->d_ctrl, g->d_ovf,
-                  &g->main_ws, &g->big_ws, &g->main_tw, &g->big_tw, g->d_D + g->n};
+                  &g->main_ws, &g->big_ws, reach_only ? &g->reach_tw : &g->main_tw, &g->big_tw,
+                  g->d_D + g->n};
     return launch_large_on(g, t, theta, key, list, count, reach_only);
 }
 

@@ -130,19 +130,20 @@ struct TreeWs {
     int64_t xcap = 0;          // non-tree live edges per sample
     int64_t nclaim = 0;        // vertices that need a claim, at most
     int64_t words = 0;         // bitmap words of the reach ids (0: the slots never count)
-    int2 *rng = nullptr;       // slots * lcap: row range of each local vertex
-    int32_t *dom = nullptr;    // slots * lcap: dominators that are not BFS parents
+    int2 *rng = nullptr;       // slots * lcap: row range of each local vertex; once a sample's BFS
+                               // is over, its dominators that are not BFS parents (lcap), then
+                               // local ids by reach id (extra edges' targets: nclaim < lcap)
     int32_t *rid = nullptr;    // slots * lcap: reach id
     int32_t *par = nullptr;    // slots * lcap: BFS parent
     int32_t *acc = nullptr;    // slots * lcap: sum of the sizes below the vertex
     int32_t *lvl = nullptr;    // slots * (lcap + 1): first local id of each BFS level
-    int32_t *lid = nullptr;    // slots * nclaim: local id by reach id (extra edges' targets)
     int4 *extra = nullptr;     // slots * xcap: source, target (reach id, then local id), the
                                // target's BFS parent, its dominator
     uint32_t *planes = nullptr; // slots * kTreePlanes * words
     uint32_t *used = nullptr;  // slots: samples counted in the planes by the last launch
     unsigned char *base = nullptr;  // the allocation
     size_t bytes = 0;
+    size_t reach_bytes = 0;    // of it, from rng on, at least: what reachability alone asked for
 };
 
 // Launch shape by the number of vertices that need a claim and the samples at hand.

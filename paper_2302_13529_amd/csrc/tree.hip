@@ -547,13 +547,13 @@ void tree_kernel(TreeArgs a)
     const size_t slot = blockIdx.x;
     TreeSlot sv;
     sv.rng = a.ws.rng + slot * (size_t)a.ws.lcap;
-    sv.dom = a.ws.dom + slot * (size_t)a.ws.lcap;
+    sv.dom = reinterpret_cast<int32_t *>(sv.rng);
+    sv.lid = sv.dom + a.ws.lcap;
     sv.rid = a.ws.rid + slot * (size_t)a.ws.lcap;
     sv.par = a.ws.par + slot * (size_t)a.ws.lcap;
     sv.acc = a.ws.acc + slot * (size_t)a.ws.lcap;
     sv.lvl = a.ws.lvl + slot * (size_t)(a.ws.lcap + 1);
     sv.extra = a.ws.extra + slot * (size_t)a.ws.xcap;
-    sv.lid = a.ws.lid + slot * (size_t)a.ws.nclaim;
     sv.planes = a.ws.planes + slot * (size_t)(kTreePlanes * a.ws.words);
     const uint32_t *list = a.sample_list, *insts = a.sample_inst;
     uint32_t count = list ? *a.sample_count : a.theta;
@@ -620,7 +620,7 @@ void tree_kernel(TreeArgs a)
         }
         const int cwords = kLT ? 0 : (c.nclaim + 31) >> 5;
         for (int w = tid; w < cwords; w += B) bm[w] = 0u;
-        if (tid == 0) {
+        if (tid == 0 && !a.reach_only) {
             sv.lvl[0] = 0;
             sv.lvl[1] = 1;
         }
@@ -629,7 +629,7 @@ void tree_kernel(TreeArgs a)
         uint32_t p_scanned = 0, p_live = 0;
         int L = 0, lo = 0, hi = c.nseeds, base = 1, lset = 0;
         do {
-            if (tid == 0 && L > 0) sv.lvl[L + 1] = hi;
+            if (tid == 0 && L > 0 && !a.reach_only) sv.lvl[L + 1] = hi;
             GroupSink<kLT> sink{c, sv, a.ws.xcap, a.reach_only != 0, bm, &sh.nextra, base,
                                 &sh.grown[lset], false};
             const int grown = expand_level<B, kLT>(c, sv.rng, sh, sink, L == 0, lo, hi, lset, j,

@@ -73,11 +73,11 @@ int main()
         unsigned char *end = start.base + start.used;
         for (const imin::TreeWs *w : {&big_tw, &main_tw}) {
             if (w->slots == 0) continue;
-            if (reinterpret_cast<unsigned char *>(w->rng) < end) {
+            if (reinterpret_cast<unsigned char *>(w->planes) < end) {
                 std::printf("overlap: n %d m %d\n", g.n, g.m);
                 return 1;
             }
-            end = reinterpret_cast<unsigned char *>(w->used + w->slots);
+            end = reinterpret_cast<unsigned char *>(w->extra + w->slots * w->xcap);
         }
         if (end > start.base + kScratchBytes) {
             std::printf("beyond the scratch: n %d m %d\n", g.n, g.m);

@@ -122,3 +122,37 @@ def test_many_small_samples_in_single_calls(gpu):
     Bo, so = g.greedy(seeds, 3, theta, 3, gpu.IMIN_AG)
     assert list(B) == list(Bo) and {k: st[k] for k in KEYS} == {k: so[k] for k in KEYS}
     g.close()
+
+
+@pytest.mark.parametrize("lt", [False, True])
+def test_spread_scratch_is_row_ranges(gpu, lt):
+    """A reachability-only call keeps 8 bytes a reach id for each of at most 16 slots a compute
+    unit, or 28 bytes for two; a decrease call beside it shares that space, and both are right."""
+    import torch
+    n = 150_000
+    rng = np.random.default_rng(9)
+    src = np.concatenate([np.arange(n), rng.integers(0, n, 3 * n)])
+    dst = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, 3 * n)])
+    p = 0.9 / np.bincount(dst, minlength=n)[dst]
+    graph = csr(n, src, dst, p)
+    g = gpu.Graph(*graph, model=gpu.IMIN_LT if lt else gpu.IMIN_IC)
+    # many seeds: the smallest workgroups
+    seeds = rng.choice(n, 400, replace=False).astype(np.int32)
+    print(f"[case] scratch, lt {lt}", flush=True)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    s1, st = g.spread(seeds, None, 5000, 3)
+    held = before - torch.cuda.mem_get_info()[0]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert held <= cus * n * max(16 * 8, 2 * 28) + (64 << 20), held
+    D, sd = g.decrease(seeds, None, 5000, 3)
+    s2, su = g.spread(seeds, None, 5000, 3)
+    assert s1 == s2 and {k: st[k] for k in KEYS} == {k: sd[k] for k in KEYS}
+    assert int(D.max()) > 0 and {k: st[k] for k in KEYS} == {k: su[k] for k in KEYS}
+    D2, _ = g.decrease(seeds, None, 5000, 3)
+    assert np.array_equal(D, D2)
+    g.close()
+    h = gpu.Graph(*graph, model=gpu.IMIN_LT if lt else gpu.IMIN_IC)
+    D3, _ = h.decrease(seeds, None, 5000, 3)
+    assert np.array_equal(D, D3)
+    h.close()
