@@ -1365,11 +1365,12 @@ hipError_t launch_leaf(const LeafArgs &args, unsigned char *scratch, int slots, 
 }
 
 // A greedy run's later rounds know the first one's samples. Where none is large, small workgroups
-// do them all, and the threads at work count for less. Eight rounds, in ms, trivalency graphs:
-// 2,000 samples of 222 vertices 1.48 with 64 threads, 2.04 with 512; of 758 (1,000 at the most) 2.31
-// with 256, 2.72 with 512, and 500 of those 1.16 with 256, 1.63 with 1024, 1,000 1.57 with 128, 1.79
-// with 256; 10,000 of 28 2.85 with 64, 2.45 with 128, 3.10 with 512; of 12 2.15 with 256, 2.38 with
-// 512, but of one 1.79 and 1.46.
+// do them all, and the threads at work count for less. Eight rounds, kernel times in ms, trivalency
+// graphs: 2,000 samples of 222 vertices 1.48 with 64 threads, 2.04 with 512; of 758 (1,000 at the
+// most) 2.31 with 256, 2.72 with 512, 500 of those 1.16 with 256, 1.63 with 1024, and 1,000 1.57 with
+// 128, 1.79 with 256; 10,000 of 28 2.85 with 64, 2.45 with 128, 3.10 with 512; of 12 2.15 with 256,
+// 2.38 with 512, but of one 1.79 and 1.46. Twelve rounds, whole calls: 1,000 samples of 19 1.25 with
+// 64, 1.82 with 512, but 2,000 of 25 1.97 and 1.66.
 int32_t block_after(const TreeFit &f, double mean, uint64_t largest)
 {
     const int64_t slots = 2 * (int64_t)std::max(1, f.num_cus);
@@ -1377,7 +1378,7 @@ int32_t block_after(const TreeFit &f, double mean, uint64_t largest)
     if (largest > 512)
         return mean < 48.0 ? 0 : mean < 1024.0 && f.theta > slots && f.theta <= 2 * slots ? 128 : 256;
     if (f.theta >= 16 * slots && mean < 64.0) return mean >= 16.0 ? 128 : mean >= 6.0 ? 256 : 0;
-    return mean >= 16.0 ? 64 : 0;
+    return mean >= (f.theta > 2 * slots ? 32.0 : 16.0) ? 64 : 0;
 }
 
 bool tree_shape(const TreeFit &f, TreeShape &out)
