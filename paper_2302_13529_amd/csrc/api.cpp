@@ -1337,39 +1337,11 @@ void destroy(imin_graph *g)
     free_tree(g->main_tw);
     free_tree(g->big_tw);
     free_forest(g->fws);
-    dfree(g->d_fnode);
-    dfree(g->d_fin16);
-    dfree(g->d_fbound);
-    dfree(g->d_fsrc);
-    dfree(g->d_rid_of);
     dfree(g->leaf);
-    dfree(g->d_rid_vtx);
-    dfree(g->d_tedge);
-    dfree(g->d_code);
-    dfree(g->d_row_ptr);
-    dfree(g->d_col4);
-    dfree(g->d_edge);
-    dfree(g->d_thr4);
-    dfree(g->d_thr_orig);
-    dfree(g->d_lo4);
-    dfree(g->d_tl);
-    dfree(g->d_in_ptr);
-    dfree(g->d_in_edge);
-    dfree(g->d_inelig);
-    dfree(g->d_cand);
-    dfree(g->d_seeds);
-    dfree(g->d_list);
-    dfree(g->d_D);
-    dfree(g->d_stats);
-    dfree(g->d_ctrl);
-    dfree(g->d_sctrl);
+    dfree(g->block);
     dfree(g->d_sj);
-    dfree(g->d_inst);
     dfree(g->d_ovf);
-    dfree(g->d_part_d);
-    dfree(g->d_part_i);
     dfree(g->d_B);
-    dfree(g->d_x);
     if (g->pin) (void)hipHostFree(g->pin);
     for (hipEvent_t e : g->kev) (void)hipEventDestroy(e);
     if (g->ev0) (void)hipEventDestroy(g->ev0);
@@ -1516,216 +1488,172 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         delete g;
         return IMIN_ENOMEM;
     }
-    const int64_t quads = std::max<int64_t>(((int64_t)m + 3) / 4, 1);
-    std::vector<uint32_t> hcol, hthr;
-    try {
-        hcol.assign((size_t)quads * 4, 0u);
-        hthr.assign((size_t)quads * 4, 0u);  // padding edges have threshold 0: never live
-    } catch (...) {
-        delete g;
-        return IMIN_ENOMEM;
-    }
-    for (int32_t e = 0; e < m; ++e) {
-        hcol[(size_t)e] = (uint32_t)col[e];
-        hthr[(size_t)e] = live_threshold(prob[e]);
-    }
-    // in-edge index: edge ids grouped by target, ascending (counting sort)
-    std::vector<int32_t> in_ptr, in_edge;
-    try {
-        in_ptr.assign((size_t)n + 1, 0);
-        in_edge.assign((size_t)std::max(m, 1), 0);
-    } catch (...) {
-        delete g;
-        return IMIN_ENOMEM;
-    }
-    for (int32_t e = 0; e < m; ++e) ++in_ptr[(size_t)col[e] + 1];
-    for (int32_t v = 0; v < n; ++v) in_ptr[(size_t)v + 1] += in_ptr[(size_t)v];
-    {
-        std::vector<int32_t> fill(in_ptr.begin(), in_ptr.end() - 1);
-        for (int32_t e = 0; e < m; ++e) in_edge[(size_t)fill[(size_t)col[e]]++] = e;
-    }
-    // Reach ids: the vertices that need a claim (two or more in-edges), then those with one.
-    std::vector<int32_t> rid, rid_vtx;
-    int32_t nclaim = 0;
-    try {
-        rid.assign((size_t)n, 0);
-        rid_vtx.reserve((size_t)n);
-        for (int32_t v = 0; v < n; ++v)
-            if (in_ptr[(size_t)v + 1] - in_ptr[(size_t)v] > 1) rid_vtx.push_back(v);
-        nclaim = (int32_t)rid_vtx.size();
-        for (int32_t v = 0; v < n; ++v)
-            if (in_ptr[(size_t)v + 1] - in_ptr[(size_t)v] == 1) rid_vtx.push_back(v);
-    } catch (...) {
-        delete g;
-        return IMIN_ENOMEM;
-    }
-    for (size_t r = 0; r < rid_vtx.size(); ++r) rid[(size_t)rid_vtx[r]] = (int32_t)r;
-    // Linear threshold, few enough reachable vertices: the in-edges by reach id.
-    imin::ForestShape fshape;
-    int32_t nsrc = 0;
-    for (int32_t v = 0; v < n; ++v)
-        if (in_ptr[(size_t)v + 1] == in_ptr[(size_t)v]) rid[(size_t)v] = -1 - nsrc++;
-    const bool forest =
-        model == IMIN_LT && imin::forest_shape((int64_t)rid_vtx.size(), nsrc, fshape);
+    const bool lt = model == IMIN_LT;
+    const size_t quads = (size_t)std::max<int64_t>(((int64_t)m + 3) / 4, 1);
+    const size_t edges = quads * 4;
+    // What the host fills lies in one block, laid out as on the device, and goes there in one copy:
+    // an allocation, a copy or a free costs a small graph 10 us each.
+    size_t staged = 0;
+    auto stage = [&](size_t words) {
+        const size_t at = staged;
+        staged += (words + 63) / 64 * 64;
+        return at;
+    };
+    const size_t o_row = stage((size_t)n + 1), o_col = stage(edges), o_thr = stage(edges);
+    const size_t o_in = stage((size_t)n + 1), o_ine = stage((size_t)std::max(m, 1));
+    const size_t o_lo = lt ? stage(edges) : 0, o_rid = stage((size_t)n), o_vtx = stage((size_t)n);
+    std::vector<uint32_t> host;
+    std::vector<int32_t> fill;
     std::vector<uint4> fnode;
-    std::vector<uint32_t> fin16, fbound;
-    std::vector<int32_t> fsrc;
-    // Linear-threshold model: the in-edges of v split [0, 2^24) into consecutive intervals,
-    // edge k of v (ascending id) getting [bound_{k-1}, bound_k) with
-    // bound_k = min(2^24, ceil(2^24 * (w_1 + ... + w_k))) from fp64 running sums.
-    std::vector<uint32_t> hlo;
-    if (model == IMIN_LT) {
-        try {
-            hlo.assign(hthr.size(), 0u);
-        } catch (...) {
-            delete g;
-            return IMIN_ENOMEM;
-        }
+    int32_t nclaim = 0, nreach = 0, nsrc = 0;
+    imin::ForestShape fshape;
+    bool forest = false;
+    try {
+        host.assign(staged, 0u);  // padding edges have threshold 0: never live
+        std::copy(row_ptr, row_ptr + n + 1, host.begin() + o_row);
+        if (m > 0) std::copy(col, col + m, host.begin() + o_col);
+        uint32_t *const thr = host.data() + o_thr;
+        int32_t *const in_ptr = reinterpret_cast<int32_t *>(host.data() + o_in);
+        int32_t *const in_edge = reinterpret_cast<int32_t *>(host.data() + o_ine);
+        if (!lt)
+            for (int32_t e = 0; e < m; ++e) thr[e] = live_threshold(prob[e]);
+        // in-edge index: edge ids grouped by target, ascending (counting sort)
+        for (int32_t e = 0; e < m; ++e) ++in_ptr[(size_t)col[e] + 1];
+        for (int32_t v = 0; v < n; ++v) in_ptr[(size_t)v + 1] += in_ptr[v];
+        fill.assign(in_ptr, in_ptr + n);
+        for (int32_t e = 0; e < m; ++e) in_edge[fill[(size_t)col[e]]++] = e;
+        // Reach ids: the vertices that need a claim (two or more in-edges), then those with one;
+        // the vertices without are numbered below -1.
+        int32_t *const rid = reinterpret_cast<int32_t *>(host.data() + o_rid);
+        int32_t *const vtx = reinterpret_cast<int32_t *>(host.data() + o_vtx);
         for (int32_t v = 0; v < n; ++v) {
-            double sum = 0.0;
-            uint32_t prev = 0;
-            for (int32_t k = in_ptr[(size_t)v]; k < in_ptr[(size_t)v + 1]; ++k) {
-                const int32_t e = in_edge[(size_t)k];
-                sum += (double)prob[e];
-                const double bound = std::min(16777216.0, std::ceil(sum * 16777216.0));
-                hlo[(size_t)e] = prev;
-                hthr[(size_t)e] = (uint32_t)bound;
-                prev = (uint32_t)bound;
-            }
-            if (sum > 1.0 + 1e-5) {
-                delete g;
-                return IMIN_EINVAL;
+            const int32_t deg = in_ptr[(size_t)v + 1] - in_ptr[v];
+            if (deg > 1) {
+                rid[v] = nclaim;
+                vtx[nclaim++] = v;
+            } else if (deg == 0) {
+                rid[v] = -1 - nsrc++;
             }
         }
-    }
-    if (forest) {
-        try {
-            fnode.reserve(rid_vtx.size());
-            fin16.reserve((size_t)m);
-            fbound.reserve((size_t)m);
-            fsrc.reserve((size_t)m);
-            std::vector<int32_t> src((size_t)m);
-            for (int32_t v = 0; v < n; ++v)
-                std::fill(src.begin() + row_ptr[v], src.begin() + row_ptr[(size_t)v + 1], v);
-            for (int32_t v : rid_vtx) {
-                const int32_t k0 = in_ptr[(size_t)v], k1 = in_ptr[(size_t)v + 1];
-                fnode.push_back(make_uint4((uint32_t)v, (uint32_t)fin16.size(), (uint32_t)(k1 - k0),
-                                           (uint32_t)(row_ptr[(size_t)v + 1] - row_ptr[v])));
-                for (int32_t k = k0; k < k1; ++k) {
-                    const size_t e = (size_t)in_edge[(size_t)k];
-                    const int32_t s = src[e], r = rid[(size_t)s];
-                    const uint32_t b = hthr[e];
-                    fin16.push_back(((b ? b - 1 : 0u) >> 8 << 16) | (r >= 0 ? (uint32_t)r : 0xFFFDu));
-                    fbound.push_back(b);
-                    fsrc.push_back(r >= 0 ? s : -1 - r);
+        nreach = nclaim;
+        for (int32_t v = 0; v < n; ++v)
+            if (in_ptr[(size_t)v + 1] - in_ptr[v] == 1) {
+                rid[v] = nreach;
+                vtx[nreach++] = v;
+            }
+        if (lt) {
+            // Linear-threshold model: the in-edges of v split [0, 2^24) into consecutive intervals,
+            // edge k of v (ascending id) getting [bound_{k-1}, bound_k) with
+            // bound_k = min(2^24, ceil(2^24 * (w_1 + ... + w_k))) from fp64 running sums.
+            uint32_t *const lo = host.data() + o_lo;
+            for (int32_t v = 0; v < n; ++v) {
+                double sum = 0.0;
+                uint32_t prev = 0;
+                for (int32_t k = in_ptr[v]; k < in_ptr[(size_t)v + 1]; ++k) {
+                    const int32_t e = in_edge[k];
+                    sum += (double)prob[e];
+                    const double bound = std::min(16777216.0, std::ceil(sum * 16777216.0));
+                    lo[e] = prev;
+                    thr[e] = (uint32_t)bound;
+                    prev = (uint32_t)bound;
+                }
+                if (sum > 1.0 + 1e-5) {
+                    delete g;
+                    return IMIN_EINVAL;
                 }
             }
-        } catch (...) {
-            delete g;
-            return IMIN_ENOMEM;
+            // Few enough reachable vertices: the in-edges by reach id (launch_forest_index)
+            forest = imin::forest_shape(nreach, nsrc, fshape);
+            if (forest) {
+                fnode.reserve((size_t)nreach);
+                uint32_t first = 0;
+                for (int32_t r = 0; r < nreach; ++r) {
+                    const int32_t v = vtx[r];
+                    const uint32_t deg = (uint32_t)(in_ptr[(size_t)v + 1] - in_ptr[v]);
+                    fnode.push_back(make_uint4((uint32_t)v, first, deg,
+                                               (uint32_t)(row_ptr[(size_t)v + 1] - row_ptr[v])));
+                    first += deg;
+                }
+            }
         }
+    } catch (...) {
+        delete g;
+        return IMIN_ENOMEM;
     }
     g->model = model;
     g->words = (n + 31) / 32;
     g->nclaim = nclaim;
-    g->nreach = (int32_t)rid_vtx.size();
+    g->nreach = nreach;
     g->tree = imin::tree_shape(tree_fit(g, 1, false), g->shape);
     g->forest = g->tree && forest;
     g->fshape = fshape;
     g->nsrc = nsrc;
-    int32_t *d_rid = nullptr;
-    bool good =
-        ok(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking)) &&
-        ok(hipEventCreate(&g->ev0)) && ok(hipEventCreate(&g->ev1)) &&
-        ok(hipMalloc(&g->d_row_ptr, (size_t)(n + 1) * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_col4, hcol.size() * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_thr4, hthr.size() * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_thr_orig, hthr.size() * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_in_ptr, in_ptr.size() * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_in_edge, in_edge.size() * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_inelig, (size_t)g->words * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_cand, (size_t)g->words * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_seeds, (size_t)n * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_list, 2 * (size_t)n * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_D, ((size_t)n + rid_vtx.size()) * sizeof(unsigned long long))) &&
-        ok(hipMalloc(&g->d_stats, kCallStats * sizeof(unsigned long long))) &&
-        ok(hipMalloc(&g->d_ctrl, imin::kCtrlWords * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_sctrl, 3 * sizeof(uint32_t))) &&
-        ok(hipMalloc(&g->d_inst, sizeof(imin::InstanceDesc))) &&
-        ok(hipMalloc(&g->d_part_d, (size_t)g->parts * sizeof(unsigned long long))) &&
-        ok(hipMalloc(&g->d_part_i, (size_t)g->parts * sizeof(int32_t))) &&
-        ok(hipMalloc(&g->d_x, sizeof(int32_t))) &&
-        (model != IMIN_LT || ok(hipMalloc(&g->d_lo4, hlo.size() * sizeof(uint32_t)))) &&
-        (model != IMIN_LT || ok(hipMalloc(&g->d_tl, 2 * hlo.size() * sizeof(uint32_t)))) &&
-        (model != IMIN_IC || ok(hipMalloc(&g->d_edge, hcol.size() * sizeof(uint4)))) &&
-        (!g->tree || ok(hipMalloc(&g->d_tedge, hcol.size() * sizeof(uint4)))) &&
-        (!g->tree || model != IMIN_IC || ok(hipMalloc(&g->d_code, hcol.size()))) &&
-        ok(hipMalloc(&g->d_rid_vtx, std::max<size_t>(rid_vtx.size(), 1) * sizeof(int32_t))) &&
-        ok(hipMalloc(&d_rid, (size_t)n * sizeof(int32_t))) &&
-        (!g->forest || (ok(hipMalloc(&g->d_fnode, fnode.size() * sizeof(uint4))) &&
-                        ok(hipMalloc(&g->d_fin16, fin16.size() * 4)) &&
-                        ok(hipMalloc(&g->d_fbound, fbound.size() * 4)) &&
-                        ok(hipMalloc(&g->d_fsrc, fsrc.size() * 4))));
-    if (!good) {
+    const size_t records = g->tree ? edges : 0, fedges = g->forest ? (size_t)m : 0;
+    auto carve = [&](unsigned char *base) {
+        uint32_t *const w = reinterpret_cast<uint32_t *>(base);
+        g->d_row_ptr = reinterpret_cast<int32_t *>(w + o_row);
+        g->d_col4 = reinterpret_cast<uint4 *>(w + o_col);
+        g->d_thr_orig = reinterpret_cast<uint4 *>(w + o_thr);
+        g->d_in_ptr = reinterpret_cast<int32_t *>(w + o_in);
+        g->d_in_edge = reinterpret_cast<int32_t *>(w + o_ine);
+        g->d_lo4 = lt ? reinterpret_cast<uint4 *>(w + o_lo) : nullptr;
+        g->d_rid_of = reinterpret_cast<int32_t *>(w + o_rid);
+        g->d_rid_vtx = reinterpret_cast<int32_t *>(w + o_vtx);
+        size_t at = staged * sizeof(uint32_t);
+        auto take = [&](auto *&p, size_t count) {
+            using T = typename std::remove_reference<decltype(*p)>::type;
+            p = count > 0 ? reinterpret_cast<T *>(base + at) : nullptr;
+            at += (count * sizeof(T) + 255) / 256 * 256;
+        };
+        take(g->d_thr4, quads);
+        take(g->d_inelig, (size_t)g->words);
+        take(g->d_cand, (size_t)g->words);
+        take(g->d_seeds, (size_t)n);
+        take(g->d_list, (size_t)n);
+        take(g->d_D, (size_t)n + (size_t)nreach);
+        take(g->d_stats, (size_t)kCallStats);
+        take(g->d_ctrl, (size_t)imin::kCtrlWords);
+        take(g->d_sctrl, (size_t)3);
+        take(g->d_inst, (size_t)1);
+        take(g->d_part_d, (size_t)g->parts);
+        take(g->d_part_i, (size_t)g->parts);
+        take(g->d_x, (size_t)1);
+        take(g->d_tl, lt ? 2 * quads : 0);
+        take(g->d_edge, lt ? 0 : edges);
+        take(g->d_tedge, records);
+        take(g->d_code, lt ? 0 : records / 4);
+        take(g->d_fnode, fedges ? (size_t)nreach : 0);
+        take(g->d_fin16, fedges);
+        take(g->d_fbound, fedges);
+        take(g->d_fsrc, fedges);
+        return at;
+    };
+    if (!ok(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking)) ||
+        !ok(hipEventCreate(&g->ev0)) || !ok(hipEventCreate(&g->ev1)) ||
+        !ok(hipMalloc(&g->block, carve(nullptr)))) {
         (void)hipGetLastError();
-        dfree(d_rid);
+        g->block = nullptr;
         destroy(g);
         return IMIN_ENOMEM;
     }
-    if (!ok(hipMemcpy(g->d_row_ptr, row_ptr, (size_t)(n + 1) * sizeof(int32_t),
-                      hipMemcpyHostToDevice)) ||
-        !ok(hipMemcpy(g->d_col4, hcol.data(), hcol.size() * sizeof(uint32_t),
-                      hipMemcpyHostToDevice)) ||
-        !ok(hipMemcpy(g->d_thr4, hthr.data(), hthr.size() * sizeof(uint32_t),
-                      hipMemcpyHostToDevice)) ||
-        !ok(hipMemcpy(g->d_thr_orig, hthr.data(), hthr.size() * sizeof(uint32_t),
-                      hipMemcpyHostToDevice)) ||
-        !ok(hipMemcpy(g->d_in_ptr, in_ptr.data(), in_ptr.size() * sizeof(int32_t),
-                      hipMemcpyHostToDevice)) ||
-        !ok(hipMemcpy(g->d_in_edge, in_edge.data(), in_edge.size() * sizeof(int32_t),
-                      hipMemcpyHostToDevice)) ||
-        (model == IMIN_LT && !ok(hipMemcpy(g->d_lo4, hlo.data(), hlo.size() * sizeof(uint32_t),
-                                           hipMemcpyHostToDevice))) ||
-        (!rid_vtx.empty() &&
-         !ok(hipMemcpy(g->d_rid_vtx, rid_vtx.data(), rid_vtx.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice))) ||
-        !ok(hipMemcpy(d_rid, rid.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice)) ||
-        (g->forest &&
-         (!ok(hipMemcpy(g->d_fnode, fnode.data(), fnode.size() * sizeof(uint4),
-                        hipMemcpyHostToDevice)) ||
-          !ok(hipMemcpy(g->d_fin16, fin16.data(), fin16.size() * 4, hipMemcpyHostToDevice)) ||
-          !ok(hipMemcpy(g->d_fbound, fbound.data(), fbound.size() * 4, hipMemcpyHostToDevice)) ||
-          !ok(hipMemcpy(g->d_fsrc, fsrc.data(), fsrc.size() * 4, hipMemcpyHostToDevice)))) ||
-        !ok(imin::launch_edge_records(reinterpret_cast<const uint32_t *>(g->d_col4), g->d_row_ptr,
-                                      d_rid, reinterpret_cast<const uint32_t *>(g->d_thr_orig), m,
+    carve(g->block);
+    const uint32_t *const orig = reinterpret_cast<const uint32_t *>(g->d_thr_orig);
+    const uint32_t *const targets = reinterpret_cast<const uint32_t *>(g->d_col4);
+    if (!ok(hipMemcpy(g->block, host.data(), staged * sizeof(uint32_t), hipMemcpyHostToDevice)) ||
+        (g->forest && !ok(hipMemcpy(g->d_fnode, fnode.data(), fnode.size() * sizeof(uint4),
+                                    hipMemcpyHostToDevice))) ||
+        !ok(imin::launch_edge_records(targets, g->d_row_ptr, g->d_rid_of, orig,
+                                      reinterpret_cast<const uint32_t *>(g->d_lo4), m, (int64_t)edges,
                                       g->d_tedge, reinterpret_cast<uint8_t *>(g->d_code), g->d_edge,
-                                      g->stream)) ||
+                                      reinterpret_cast<uint32_t *>(g->d_thr4),
+                                      reinterpret_cast<uint32_t *>(g->d_tl), g->stream)) ||
+        (g->forest &&
+         !ok(imin::launch_forest_index(g->d_in_ptr, g->d_in_edge, targets, g->d_row_ptr, n, m,
+                                       g->d_rid_of, orig, g->d_fnode, g->d_fin16, g->d_fbound,
+                                       g->d_fsrc, g->stream))) ||
         !ok(hipStreamSynchronize(g->stream))) {
-        dfree(d_rid);
         destroy(g);
         return IMIN_EDEVICE;
-    }
-    if (g->forest) g->d_rid_of = d_rid;
-    else dfree(d_rid);
-    if (model == IMIN_LT) {
-        // per quad: its 4 targets, then its 4 lower bounds
-        std::vector<uint32_t> htl;
-        try {
-            htl.assign(2 * hlo.size(), 0u);
-        } catch (...) {
-            destroy(g);
-            return IMIN_ENOMEM;
-        }
-        for (size_t q = 0; q < hlo.size() / 4; ++q)
-            for (int k = 0; k < 4; ++k) {
-                htl[8 * q + k] = hcol[4 * q + k];
-                htl[8 * q + 4 + k] = hlo[4 * q + k];
-            }
-        if (!ok(hipMemcpy(g->d_tl, htl.data(), htl.size() * sizeof(uint32_t),
-                          hipMemcpyHostToDevice))) {
-            destroy(g);
-            return IMIN_EDEVICE;
-        }
     }
     *out = g;
     return IMIN_OK;

@@ -389,6 +389,30 @@ void forest_kernel(ForestArgs a)
     if (!kMulti && tid == 0 && a.ws.words > 0) a.ws.used[slot] = counted;
 }
 
+// The in-edge words, one in-edge a thread; its source is the row it lies in. In a host loop this
+// took half of a graph's creation (131k vertices: 21.7 ms; 9.6 without the index).
+__global__ void forest_index_kernel(const int32_t *in_ptr, const int32_t *in_edge, const uint32_t *col,
+                                    const int32_t *row_ptr, int32_t n, int32_t m, const int32_t *rid,
+                                    const uint32_t *bound, const uint4 *node, uint32_t *in16,
+                                    uint32_t *exact, int32_t *src)
+{
+    for (int64_t k = blockIdx.x * 256ll + threadIdx.x; k < m; k += (int64_t)gridDim.x * 256) {
+        const int32_t e = in_edge[k];
+        const uint32_t v = col[e], b = bound[e];
+        int32_t lo = 0, hi = n - 1;  // the last row that starts at or before e
+        while (lo < hi) {
+            const int32_t mid = lo + (hi - lo + 1) / 2;
+            if (row_ptr[mid] <= e) lo = mid;
+            else hi = mid - 1;
+        }
+        const int32_t r = rid[lo];
+        const uint32_t at = node[rid[v]].y + (uint32_t)(k - in_ptr[v]);
+        in16[at] = ((b ? b - 1 : 0u) >> 8 << 16) | (r >= 0 ? (uint32_t)r : kNoRid);
+        exact[at] = b;
+        src[at] = r >= 0 ? lo : -1 - r;
+    }
+}
+
 template <int B, int KW>
 bool class_for(int64_t nreach, int64_t nsrc, ForestShape &out)
 {
@@ -419,6 +443,18 @@ bool forest_shape(int64_t nreach, int64_t nsrc, ForestShape &out)
     if (class_for<256, 32>(nreach, nsrc, out) && out.per_cu * out.block >= full) return true;
     if (class_for<512, 32>(nreach, nsrc, out) && out.per_cu * out.block >= full) return true;
     return class_for<1024, 32>(nreach, nsrc, out);
+}
+
+hipError_t launch_forest_index(const int32_t *in_ptr, const int32_t *in_edge, const uint32_t *col,
+                               const int32_t *row_ptr, int32_t n, int32_t m, const int32_t *rid,
+                               const uint32_t *bound, const uint4 *node, uint32_t *in16,
+                               uint32_t *exact, int32_t *src, hipStream_t stream)
+{
+    if (m <= 0) return hipSuccess;
+    const int grid = (int)std::min<int64_t>(4096, ((int64_t)m + 255) / 256);
+    hipLaunchKernelGGL(forest_index_kernel, dim3(grid), dim3(256), 0, stream, in_ptr, in_edge, col,
+                       row_ptr, n, m, rid, bound, node, in16, exact, src);
+    return hipGetLastError();
 }
 
 hipError_t launch_forest(const ForestArgs &a, const ForestShape &s, int slots, bool multi,

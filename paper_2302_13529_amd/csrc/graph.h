@@ -31,6 +31,8 @@ struct imin_graph {
     int num_cus = 1;
     std::vector<int32_t> row_ptr;  // host copies: out-neighbours of the seeds (GR)
     std::vector<int32_t> col;
+    unsigned char *block = nullptr;  // one allocation: every array below but the growing ones
+                                  // (d_sj, d_ovf, d_B and the kernels' scratch)
     int32_t *d_row_ptr = nullptr;
     uint4 *d_col4 = nullptr;      // edge targets, 4 per quad, padded to a whole quad
     uint4 *d_edge = nullptr;      // independent cascade: one record per edge slot of d_col4,
@@ -105,7 +107,7 @@ struct imin_graph {
     std::vector<int32_t> masked;       // vertices whose in-edges have threshold 0 in d_thr4
     std::vector<int32_t> mask_prev;    // the previous call's list
     bool mask_known = true;            // false while a call runs, and after one that failed
-    int32_t *d_list = nullptr;         // 2n: device copies of the two lists above
+    int32_t *d_list = nullptr;         // n: device copy of `masked`
     std::vector<hipEvent_t> kev;  // pairs around each decrease launch of the current call
     size_t kev_used = 0;
     imin::host::MultiScratch *batch_ms = nullptr;  // scratch of the batches this graph leads

@@ -231,6 +231,11 @@ struct ForestArgs {
     ForestWs ws;
 };
 bool forest_shape(int64_t nreach, int64_t nsrc, ForestShape &out);
+// InstanceDesc's in-edge words by reach id, from the in-edge index by vertex. node: filled.
+hipError_t launch_forest_index(const int32_t *in_ptr, const int32_t *in_edge, const uint32_t *col,
+                               const int32_t *row_ptr, int32_t n, int32_t m, const int32_t *rid,
+                               const uint32_t *bound, const uint4 *node, uint32_t *in16,
+                               uint32_t *exact, int32_t *src, hipStream_t stream);
 hipError_t launch_forest(const ForestArgs &a, const ForestShape &s, int slots, bool multi,
                          hipStream_t stream);
 
@@ -294,9 +299,12 @@ hipError_t launch_tree(const TreeArgs &a, const TreeShape &s, bool lt, hipStream
 hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *rid_vtx,
                                int32_t nreach, const unsigned long long *Dr, unsigned long long *D,
                                hipStream_t stream);
+// Per edge of a graph being created: its records and codes, the working thresholds, and under linear
+// threshold its quad's targets and lower bounds (padded to whole quads). Null outputs are left out.
 hipError_t launch_edge_records(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
-                               const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
-                               uint4 *plain, hipStream_t stream);
+                               const uint32_t *thr, const uint32_t *lo, int64_t m, int64_t padded,
+                               uint4 *edge, uint8_t *code, uint4 *plain, uint32_t *work, uint32_t *tl,
+                               hipStream_t stream);
 // The records' thresholds of all edges, as created.
 hipError_t launch_edge_restore(const uint32_t *thr, int64_t m, uint4 *edge, hipStream_t stream);
 

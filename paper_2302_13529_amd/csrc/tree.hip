@@ -1237,18 +1237,26 @@ __global__ __launch_bounds__(kDrainWords *kDrainRows) void drain_planes_kernel(
 }
 
 // Per edge: the target's row range, its reach id and the edge's threshold; the threshold's
-// code; and the record without a threshold (target, its row range) of the other kernels. Null
-// outputs are left out.
+// code; the record without a threshold (target, its row range) of the other kernels; the working
+// threshold; and, per quad, its targets and lower bounds. Null outputs are left out.
 __global__ void edge_records_kernel(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
-                                    const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
-                                    uint4 *plain)
+                                    const uint32_t *thr, const uint32_t *lo, int64_t m,
+                                    int64_t padded, uint4 *edge, uint8_t *code, uint4 *plain,
+                                    uint32_t *work, uint32_t *tl)
 {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < padded;
          e += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t v = col[e];
+        const uint32_t v = col[e], t = thr[e];
+        work[e] = t;
+        if (tl) {
+            uint32_t *const at = tl + (e >> 2) * 8 + (e & 3);
+            at[0] = v;
+            at[4] = lo[e];
+        }
+        if (e >= m) continue;
         const uint32_t r0 = (uint32_t)row_ptr[v], r1 = (uint32_t)row_ptr[v + 1];
-        if (edge) edge[e] = make_uint4(r0, r1, (uint32_t)rid[v], thr[e]);
-        if (code) code[e] = (uint8_t)threshold_code(thr[e]);
+        if (edge) edge[e] = make_uint4(r0, r1, (uint32_t)rid[v], t);
+        if (code) code[e] = (uint8_t)threshold_code(t);
         if (plain) plain[e] = make_uint4(v, r0, r1, 0u);
     }
 }
@@ -1436,13 +1444,13 @@ hipError_t launch_drain_planes(const TreeWs &ws, int32_t slots, const int32_t *r
 }
 
 hipError_t launch_edge_records(const uint32_t *col, const int32_t *row_ptr, const int32_t *rid,
-                               const uint32_t *thr, int64_t m, uint4 *edge, uint8_t *code,
-                               uint4 *plain, hipStream_t stream)
+                               const uint32_t *thr, const uint32_t *lo, int64_t m, int64_t padded,
+                               uint4 *edge, uint8_t *code, uint4 *plain, uint32_t *work, uint32_t *tl,
+                               hipStream_t stream)
 {
-    if (m <= 0) return hipSuccess;
-    const int grid = (int)std::min<int64_t>(8192, (m + 255) / 256);
+    const int grid = (int)std::min<int64_t>(8192, (padded + 255) / 256);
     hipLaunchKernelGGL(edge_records_kernel, dim3(grid), dim3(256), 0, stream, col, row_ptr, rid, thr,
-                       m, edge, code, plain);
+                       lo, m, padded, edge, code, plain, work, tl);
     return hipGetLastError();
 }
 
