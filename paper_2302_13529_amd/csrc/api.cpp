@@ -62,19 +62,17 @@ void free_ws(Workspace &ws)
     ws = Workspace();
 }
 
-size_t slot_bytes(int64_t n, int64_t lcap, int64_t xcap, bool rng = false)
+size_t slot_bytes(int64_t n, int64_t lcap, int64_t xcap)
 {
     return (size_t)n * sizeof(unsigned long long) + (size_t)lcap * sizeof(imin::LocalVtx) +
            (size_t)(lcap + 1) * sizeof(int32_t) + (size_t)xcap * sizeof(int2) + 2 * sizeof(uint32_t) +
-           (rng ? (size_t)lcap * sizeof(int2) : 0);
+           (size_t)lcap * sizeof(int2);
 }
 
 int alloc_ws(Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap,
-             hipStream_t stream, bool rng)
+             hipStream_t stream)
 {
-    if (ws.slots == slots && ws.n == n && ws.lcap == lcap && ws.xcap == xcap &&
-        (ws.rng != nullptr) == rng)
-        return IMIN_OK;
+    if (ws.slots == slots && ws.n == n && ws.lcap == lcap && ws.xcap == xcap) return IMIN_OK;
     free_ws(ws);
     // the map's local-id field holds lid + 1 <= lcap, and leaves at least one epoch bit
     int32_t lbits = 1;
@@ -85,7 +83,7 @@ int alloc_ws(Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap
                 ok(hipMalloc(&ws.loc, S * (size_t)lcap * sizeof(imin::LocalVtx))) &&
                 ok(hipMalloc(&ws.lvl, S * (size_t)(lcap + 1) * sizeof(int32_t))) &&
                 ok(hipMalloc(&ws.extra, S * (size_t)std::max<int64_t>(xcap, 1) * sizeof(int2))) &&
-                (!rng || ok(hipMalloc(&ws.rng, S * (size_t)lcap * sizeof(int2)))) &&
+                ok(hipMalloc(&ws.rng, S * (size_t)lcap * sizeof(int2))) &&
                 ok(hipMalloc(&ws.epoch, S * sizeof(uint32_t))) &&
                 ok(hipMalloc(&ws.dirty, S * sizeof(uint32_t)));
     if (!good) {
@@ -104,7 +102,7 @@ int alloc_ws(Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap
     ws.lcap = lcap;
     ws.xcap = xcap;
     ws.lbits = lbits;
-    ws.bytes = S * slot_bytes(n, lcap, xcap, rng);
+    ws.bytes = S * slot_bytes(n, lcap, xcap);
     return IMIN_OK;
 }
 
@@ -307,7 +305,7 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
         size_t free_b = 0, total_b = 0;
         if (!ok(hipMemGetInfo(&free_b, &total_b))) return IMIN_EDEVICE;
         free_b += g->main_ws.bytes;  // the current allocation is released before a new one
-        const size_t per = slot_bytes(g->n, lcap, xcap, g->model == IMIN_IC);
+        const size_t per = slot_bytes(g->n, lcap, xcap);
         const size_t by_mem = std::max<size_t>(1, (free_b / 2) / per);
         slots = (int32_t)std::min<size_t>((size_t)imin::kSlotsPerCu * g->num_cus, by_mem);
         if (max_slots > 0) slots = std::min(slots, max_slots);
@@ -318,12 +316,10 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
             (have >= slots || (max_slots == 0 && have > kSmallModeSlots)))
             slots = have;
     }
-    // independent cascade: slots keep each claimed vertex's row range (from its edge record)
-    const bool rng = g->model == IMIN_IC;
-    int rc = alloc_ws(g->main_ws, g->n, slots, lcap, xcap, g->stream, rng);
+    int rc = alloc_ws(g->main_ws, g->n, slots, lcap, xcap, g->stream);
     if (rc) return rc;
     if (xcap < xmax) {
-        rc = alloc_ws(g->big_ws, g->n, kSpillSlots, lcap, xmax, g->stream, rng);
+        rc = alloc_ws(g->big_ws, g->n, kSpillSlots, lcap, xmax, g->stream);
         if (rc) return rc;
     } else {
         free_ws(g->big_ws);
@@ -692,7 +688,6 @@ int launch_large_on(imin_graph *g, const LargeTarget &t, uint32_t theta, uint64_
     a.thr4 = t.thr4;
     a.lo4 = g->d_lo4;
     a.tl = g->d_tl;
-    a.lt = g->model == IMIN_LT ? 1 : 0;
     a.seeds = t.seeds;
     a.nseeds = t.nseeds;
     a.n = g->n;
@@ -824,14 +819,14 @@ int multi_slots(MultiScratch &ms, int num_cus, const MultiSize &size, hipStream_
     const int64_t lcap = max_n + 1;
     const int64_t xcap = extra_cap(max_n, max_m);
     free_b += ms.main_ws.bytes;
-    const size_t per = slot_bytes(max_n, lcap, xcap, true);
+    const size_t per = slot_bytes(max_n, lcap, xcap);
     const int32_t slots = (int32_t)std::max<size_t>(
         1, std::min<size_t>((size_t)imin::kMultiSlotsPerCu * std::max(1, num_cus),
                             (free_b / 4) / per));
-    int rc = alloc_ws(ms.main_ws, max_n, slots, lcap, xcap, stream, true);
+    int rc = alloc_ws(ms.main_ws, max_n, slots, lcap, xcap, stream);
     if (rc) return rc;
     if (xcap < xmax) {
-        rc = alloc_ws(ms.big_ws, max_n, (int32_t)kSpillSlots, lcap, xmax, stream, true);
+        rc = alloc_ws(ms.big_ws, max_n, (int32_t)kSpillSlots, lcap, xmax, stream);
         if (rc) return rc;
     } else {
         free_ws(ms.big_ws);
@@ -1239,7 +1234,10 @@ int decrease_round(imin_graph *g, int32_t nseeds, uint32_t theta, uint64_t seed,
                 // the host), the one after it without
                 g->probe = 1;
             }
-            if (drop || handed > (uint32_t)g->main_ws.slots) {
+            const int32_t slots = !tree_on(g)  ? g->main_ws.slots
+                                  : reach_only ? g->reach_tw.slots
+                                               : g->main_tw.slots;
+            if (drop || handed > (uint32_t)slots) {
                 rc = size_workspaces(g, 0, theta, reach_only);
                 if (rc) return rc;
             }

@@ -80,7 +80,7 @@ struct Call {
 };
 
 struct SlotView {
-    int2 *rng;  // row range of each local vertex (none in linear-threshold single calls)
+    int2 *rng;  // row range of each local vertex
     unsigned long long *map;
     LocalVtx *loc;
     int32_t *lvl;
@@ -124,9 +124,9 @@ struct Shared {
 // this sample is at least tag, every older one below it.
 // inc: 1 when the slot keeps reach counts in its map (the count word of w gains this
 // sample's reach), else 0.
-// kRng: w's row range r is kept with its local id, so that the next level starts from it
-// without a dependent row_ptr read.
-template <bool kRng, class Sh>
+// w's row range r is kept with its local id, so that the next level starts from it without a
+// dependent row_ptr read.
+template <class Sh>
 __device__ __forceinline__ void visit(const DecreaseArgs &a, const SlotView &sv, Sh &sh, int w,
                                       int src, uint32_t tag, uint32_t inc, int2 r)
 {
@@ -148,7 +148,7 @@ __device__ __forceinline__ void visit(const DecreaseArgs &a, const SlotView &sv,
             rec.tdom = src;
             rec.csz = 1;
             sv.loc[id] = rec;
-            if (kRng) sv.rng[id] = r;
+            sv.rng[id] = r;
         } else {
             // keep the slot's count (the sample is abandoned and re-run elsewhere)
             __hip_atomic_store(&sv.map[w], tag64 | (uint32_t)old, __ATOMIC_RELAXED,
@@ -176,9 +176,9 @@ __device__ __forceinline__ void locate(const Sh &sh, int cnt, int q, int &l, int
     quad = (sh.e0[lo] >> 2) + (q - sh.qpre[lo]);
 }
 
-// The live edges (mask) of one quad whose targets are in col. kRng: each target's row range
-// is read from row_ptr beside its claim.
-template <bool kRng, class Sh>
+// The live edges (mask) of one quad whose targets are in col. Each target's row range is read
+// from row_ptr beside its claim.
+template <class Sh>
 __device__ __forceinline__ void visit_mask(const DecreaseArgs &a, const SlotView &sv, Sh &sh,
                                            uint32_t mask, uint4 col, int src, uint32_t tag,
                                            uint32_t inc, uint32_t &live,
@@ -189,9 +189,7 @@ __device__ __forceinline__ void visit_mask(const DecreaseArgs &a, const SlotView
         const int i = __builtin_ctz(mask);
         mask &= mask - 1;
         const uint32_t c = i == 0 ? col.x : i == 1 ? col.y : i == 2 ? col.z : col.w;
-        int2 r = make_int2(0, 0);
-        if (kRng) r = make_int2(row_ptr[c], row_ptr[c + 1]);
-        visit<kRng>(a, sv, sh, (int)c, src, tag, inc, r);
+        visit(a, sv, sh, (int)c, src, tag, inc, make_int2(row_ptr[c], row_ptr[c + 1]));
     }
 }
 
@@ -209,7 +207,7 @@ __device__ __forceinline__ void visit_edges(const DecreaseArgs &a, const SlotVie
         mask &= mask - 1;
         const uint4 cur = h;
         if (mask) h = edge[((size_t)quad << 2) + __builtin_ctz(mask)];
-        visit<true>(a, sv, sh, (int)cur.x, src, tag, inc, make_int2((int)cur.y, (int)cur.z));
+        visit(a, sv, sh, (int)cur.x, src, tag, inc, make_int2((int)cur.y, (int)cur.z));
     }
 }
 
@@ -219,17 +217,14 @@ __device__ __forceinline__ void visit_edges(const DecreaseArgs &a, const SlotVie
 // the edge quads of a chunk are spread evenly over the workgroup, two independent quads in
 // flight per thread. A quad's thresholds are always read. Under IC only its live edges'
 // records (target and row range) are read; under LT its targets are read first, since the
-// coins depend on them, and a claimed target's row range comes from row_ptr in
-// many-instance launches. kMulti: many-instance launch. Row ranges of local vertices are
-// kept (kRng) except in linear-threshold single calls, which read row_ptr per frontier
-// vertex.
-template <int B, bool kLT, bool kMulti>
+// coins depend on them, and a claimed target's row range comes from row_ptr. Row ranges of
+// local vertices are kept.
+template <int B, bool kLT>
 __device__ void expand(const DecreaseArgs &a, const Call &c, const SlotView &sv, Shared<B> &sh,
                        bool from_seeds, int lo, int hi, uint32_t j, uint32_t tag,
                        uint32_t inc, uint32_t &scanned, uint32_t &live)
 {
     constexpr int kChunk = Shared<B>::kChunk;
-    constexpr bool kRng = kMulti || !kLT;
     const int tid = threadIdx.x;
     for (int base = lo; base < hi; base += kChunk) {
         const int first = tid * kPerThread;
@@ -241,14 +236,14 @@ __device__ void expand(const DecreaseArgs &a, const Call &c, const SlotView &sv,
             nq[i] = 0;
             if (k < hi) {
                 int e0, e1;
-                if (kRng && !from_seeds) {
+                if (from_seeds) {
+                    const int v = c.seeds[k];
+                    e0 = c.row_ptr[v];
+                    e1 = c.row_ptr[v + 1];
+                } else {
                     const int2 r = sv.rng[k];
                     e0 = r.x;
                     e1 = r.y;
-                } else {
-                    const int v = from_seeds ? c.seeds[k] : sv.loc[k].glob;
-                    e0 = c.row_ptr[v];
-                    e1 = c.row_ptr[v + 1];
                 }
                 scanned += (uint32_t)(e1 - e0);
                 nq[i] = (e1 > e0) ? (((e1 - 1) >> 2) - (e0 >> 2) + 1) : 0;
@@ -286,10 +281,8 @@ __device__ void expand(const DecreaseArgs &a, const Call &c, const SlotView &sv,
                 const uint32_t m2 = has2 ? live_mask_lt(quad2, j, c.key_lo, c.key_hi, sh.e0[l2],
                                                         sh.e1[l2], b2, t2, c2)
                                          : 0u;
-                visit_mask<kRng>(a, sv, sh, m1, c1, from_seeds ? 0 : base + l1, tag, inc, live,
-                                 c.row_ptr);
-                visit_mask<kRng>(a, sv, sh, m2, c2, from_seeds ? 0 : base + l2, tag, inc, live,
-                                 c.row_ptr);
+                visit_mask(a, sv, sh, m1, c1, from_seeds ? 0 : base + l1, tag, inc, live, c.row_ptr);
+                visit_mask(a, sv, sh, m2, c2, from_seeds ? 0 : base + l2, tag, inc, live, c.row_ptr);
             } else {
                 const uint32_t m1 =
                     live_mask(quad1, j, c.key_lo, c.key_hi, sh.e0[l1], sh.e1[l1], t1);
@@ -350,7 +343,7 @@ void decrease_kernel(DecreaseArgs a)
     sv.loc = a.ws.loc + slot * (size_t)a.ws.lcap;
     sv.lvl = a.ws.lvl + slot * (size_t)(a.ws.lcap + 1);
     sv.extra = a.ws.extra + slot * (size_t)a.ws.xcap;
-    sv.rng = (kMulti || !kLT) ? a.ws.rng + slot * (size_t)a.ws.lcap : nullptr;
+    sv.rng = a.ws.rng + slot * (size_t)a.ws.lcap;
     uint32_t epoch = a.ws.epoch[slot];
     const uint32_t emax = 0xFFFFFFFFu >> a.ws.lbits;  // largest epoch the map entries hold
     const uint32_t count = a.sample_list ? *a.sample_count : a.theta;
@@ -409,14 +402,14 @@ void decrease_kernel(DecreaseArgs a)
 
         uint32_t p_scanned = 0, p_live = 0;
         const uint32_t inc = cnt_on ? 1u : 0u;
-        expand<B, kLT, kMulti>(a, c, sv, sh, true, 0, c.nseeds, j, tag, inc, p_scanned, p_live);
+        expand<B, kLT>(a, c, sv, sh, true, 0, c.nseeds, j, tag, inc, p_scanned, p_live);
         int L = 1, lo = 1;
         int hi = sh.tail;
         __syncthreads();
         while (lo < hi) {
             if (sh.ovf) break;
             if (tid == 0) sv.lvl[L + 1] = hi;
-            expand<B, kLT, kMulti>(a, c, sv, sh, false, lo, hi, j, tag, inc, p_scanned, p_live);
+            expand<B, kLT>(a, c, sv, sh, false, lo, hi, j, tag, inc, p_scanned, p_live);
             lo = hi;
             hi = sh.tail;
             ++L;
@@ -714,7 +707,7 @@ hipError_t launch_decrease(const DecreaseArgs &a, hipStream_t stream)
     else if (a.inst)
         hipLaunchKernelGGL((decrease_kernel<true, false>), grid, dim3(kMultiBlock), 0, stream, a);
     else if (a.lt)
-        hipLaunchKernelGGL((decrease_kernel<false, true>), grid, dim3(kBlock), 0, stream, a);
+        return hipErrorInvalidValue;  // single calls under linear threshold: the other kernels
     else
         hipLaunchKernelGGL((decrease_kernel<false, false>), grid, dim3(kBlock), 0, stream, a);
     return hipGetLastError();

@@ -57,9 +57,8 @@ struct Workspace {
     LocalVtx *loc = nullptr;   // slots * lcap
     int32_t *lvl = nullptr;    // slots * (lcap + 1): first local id of each BFS level
     int2 *extra = nullptr;     // slots * xcap: (source local id, target vertex -> local id)
-    int2 *rng = nullptr;       // slots * lcap, except for linear-threshold single calls: the
-                               // row range (row_ptr pair) of each local vertex, known when it
-                               // is claimed
+    int2 *rng = nullptr;       // slots * lcap: the row range (row_ptr pair) of each local
+                               // vertex, known when it is claimed
     uint32_t *epoch = nullptr; // slots: epoch of the slot's last sample
     uint32_t *dirty = nullptr; // slots: 1 when the slot's last counting launch left reach
                                // counts in its map (launch_flush_counts reads only those)
@@ -80,7 +79,8 @@ struct DecreaseArgs {
     const uint4 *lo4;        // linear-threshold model: interval lower bounds (thr4 = upper)
     const uint4 *tl;         // linear-threshold model: 2 * ceil(m / 4) quads, quad q's targets
                              // at 2q and its lower bounds at 2q + 1
-    int32_t lt;              // 1: linear-threshold model, 0: independent cascade
+    int32_t lt;              // 1: linear-threshold model (many-instance launches alone), 0:
+                             // independent cascade
     const int32_t *seeds;    // distinct seeds
     int32_t nseeds;
     int32_t n;

@@ -176,8 +176,7 @@ bool carve_tree_call(Carve &c, const imin_graph *g, uint32_t theta, imin::TreeSh
 }
 
 // Slot-major workgroup-kernel scratch of `slots` slots in the carve.
-bool carve_ws(Carve &c, imin::Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap,
-              bool rng)
+bool carve_ws(Carve &c, imin::Workspace &ws, int64_t n, int32_t slots, int64_t lcap, int64_t xcap)
 {
     int32_t lbits = 1;
     while (lbits < 32 && (int64_t(1) << lbits) <= lcap) ++lbits;
@@ -189,7 +188,7 @@ bool carve_ws(Carve &c, imin::Workspace &ws, int64_t n, int32_t slots, int64_t l
     ws.extra = c.take<int2>(S * (size_t)std::max<int64_t>(xcap, 1));
     ws.epoch = c.take<uint32_t>(S);
     ws.dirty = c.take<uint32_t>(S);
-    ws.rng = rng ? c.take<int2>(S * (size_t)lcap) : nullptr;
+    ws.rng = c.take<int2>(S * (size_t)lcap);
     ws.slots = slots;
     ws.n = n;
     ws.lcap = lcap;
@@ -232,26 +231,24 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
     uint8_t *marks = blocked ? c.take<uint8_t>((size_t)n) : nullptr;
     uint32_t *sj = c.take<uint32_t>(theta);
     uint32_t *ovf = c.take<uint32_t>(theta);
-    // independent cascade: slots keep each claimed vertex's row range
-    const bool rng = g->model == IMIN_IC;
     imin::Workspace main_ws, big_ws;
     imin::TreeWs main_tw, big_tw;
     const bool tree = tree_on(g);
     if (tree) {
         if (!c.fits || !carve_tree_call(c, g, theta, g->shape, main_tw, big_tw)) return IMIN_ERANGE;
     } else {
-        if (xcap < xmax && !carve_ws(c, big_ws, n, 2, lcap, xmax, rng)) return IMIN_ERANGE;
+        if (xcap < xmax && !carve_ws(c, big_ws, n, 2, lcap, xmax)) return IMIN_ERANGE;
         if (!c.fits) return IMIN_ERANGE;
         const size_t fixed = c.used;
         // as many workgroup slots as the rest holds, up to the usual count
         Carve probe{base, fixed};
         imin::Workspace one;
-        if (!carve_ws(probe, one, n, 1, lcap, xcap, rng)) return IMIN_ERANGE;
+        if (!carve_ws(probe, one, n, 1, lcap, xcap)) return IMIN_ERANGE;
         const size_t per_slot = probe.used - fixed + 7 * 256;
         const int32_t slots = (int32_t)std::max<size_t>(
             1, std::min<size_t>((size_t)imin::kSlotsPerCu * g->num_cus,
                                 (kScratchBytes - fixed) / per_slot));
-        if (!carve_ws(c, main_ws, n, slots, lcap, xcap, rng)) return IMIN_ERANGE;
+        if (!carve_ws(c, main_ws, n, slots, lcap, xcap)) return IMIN_ERANGE;
         if (xcap >= xmax) big_ws = imin::Workspace();
     }
 

@@ -1427,7 +1427,9 @@ hipError_t launch_tree(const TreeArgs &args, const TreeShape &s, bool lt, hipStr
     TreeArgs a = args;
     a.lds_bytes = s.lds;
     a.bm_words = s.bm_words;
-    if (a.inst) return lt ? launch_shape<true, true>(a, s, stream) : launch_shape<true, false>(a, s, stream);
+    // many-instance launches: independent cascade (the forest kernel and the kernel of
+    // decrease.hip take linear threshold)
+    if (a.inst) return lt ? hipErrorInvalidValue : launch_shape<true, false>(a, s, stream);
     return lt ? launch_shape<false, true>(a, s, stream) : launch_shape<false, false>(a, s, stream);
 }
 

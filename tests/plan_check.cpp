@@ -22,13 +22,21 @@ Carve call_arrays(const imin_graph &g, uint32_t theta, int32_t nS, bool blocked)
     return c;
 }
 
+// The layout of the kernel that claims in device memory (linear threshold: without row ranges).
 bool device_claims_fit(Carve c, const imin_graph &g)
 {
     const int64_t n = g.n, lcap = n + 1, xmax = (int64_t)g.m + 1, xcap = extra_cap(n, g.m);
-    const bool rng = g.model == IMIN_IC;
-    imin::Workspace ws;
-    if (xcap < xmax && !carve_ws(c, ws, n, 2, lcap, xmax, rng)) return false;
-    return c.fits && carve_ws(c, ws, n, 1, lcap, xcap, rng);
+    auto slots = [&](size_t count, int64_t extra) {
+        c.take<unsigned long long>(count * (size_t)n);
+        c.take<imin::LocalVtx>(count * (size_t)lcap);
+        c.take<int32_t>(count * (size_t)(lcap + 1));
+        c.take<int2>(count * (size_t)std::max<int64_t>(extra, 1));
+        c.take<uint32_t>(count);
+        c.take<uint32_t>(count);
+        if (g.model == IMIN_IC) c.take<int2>(count * (size_t)lcap);
+        return c.fits;
+    };
+    return (xcap >= xmax || slots(2, xmax)) && slots(1, xcap);
 }
 
 }  // namespace
