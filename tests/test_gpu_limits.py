@@ -156,3 +156,22 @@ def test_spread_scratch_is_row_ranges(gpu, lt):
     D3, _ = h.decrease(seeds, None, 5000, 3)
     assert np.array_equal(D, D3)
     h.close()
+
+
+def test_forced_wave_kernel_keeps_few_slots(gpu):
+    """Ten hand-overs need no more than the 64 slots that go with the wave kernel."""
+    import torch
+    n = 200_000
+    src, dst = np.arange(n), (np.arange(n) + 1) % n
+    p = np.where(src < 300, 1.0, 0.0)
+    twice = np.concatenate([src, src]), np.concatenate([dst, dst]), np.concatenate([p, 0 * p])
+    g = gpu.Graph(*csr(n, *twice))
+    g.set_small(1)
+    print("[case] forced wave kernel", flush=True)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    D, st = g.decrease([0], None, 10, 3)
+    held = before - torch.cuda.mem_get_info()[0]
+    assert st["wave_samples"] == 0 and st["reached"] == 10 * 300
+    assert held <= 64 * (26 * n + 16 * (n // 4)) + (64 << 20), held
+    g.close()
