@@ -82,8 +82,11 @@ typedef struct {
                                seed nor blocked, leaving a seed or a vertex of R_j */
     uint64_t spilled;       /* samples re-run in large-capacity scratch after overflow */
     double device_ms;       /* GPU time of the whole call, measured with HIP events */
-    double kernel_ms;       /* GPU time of the sampling/dominator kernel launches alone,
-                               summed over the call (HIP events around each launch) */
+    double kernel_ms;       /* GPU time of the rounds' sampling and dominator kernels, summed
+                               over the call: HIP events around each round's launches, or in
+                               single calls of the LDS-claim and the forest kernel the device's
+                               clock, from the clearing of a round's counters (some us of it
+                               included) to the kernel that follows the round */
     uint64_t wave_samples;  /* samples finished by a wavefront-level kernel (one sample per
                                wave, or several per wave); the rest ran one workgroup per
                                sample */
@@ -226,13 +229,13 @@ typedef struct {
  * more than 255 vertices, keeps more than 256 non-tree live edges, or meets a frontier
  * chunk over the quad limit is left, with nothing accumulated, to the one-workgroup-per-
  * sample kernel in the same call.
- *   enable  -1 automatic (the default: off for graphs that the LDS-claim kernel or the forest
- *           kernel takes, which run small samples as well; else on for the first round of
- *           every call, and off for
- *           the call's later rounds when fewer than half of the first round's samples
- *           finished in the wave kernel; otherwise the second round is timed with it, the
- *           third runs without it as a timed trial, and later rounds keep whichever of the
- *           two was faster), 0 off, 1 on.
+ *   enable  -1 automatic (the default), 0 off, 1 on. Automatic: off for graphs that the forest
+ *           kernel takes, and for those of the LDS-claim kernel unless a call has very many
+ *           samples for its slots; on for the first round of a call on other graphs. Off for a
+ *           call's later rounds when fewer than half of the first round's samples finished in
+ *           the wave kernel. Otherwise, on the other graphs, the second round is timed with it,
+ *           the third runs without it as a timed trial, and later rounds keep whichever of the
+ *           two was faster.
  *   launch  the wave kernel's launch shape (NULL: defaults).
  * Results never depend on these values. Errors: IMIN_EINVAL for NULL g, enable outside
  * [-1, 1], or negative launch values.

@@ -767,10 +767,14 @@ void MultiSize::add(const imin_graph *g)
 }
 
 // Many-instance rounds on graphs with more reach ids than this hand their larger samples to the
-// LDS-claim kernels: a workgroup of 512 threads pays where samples of 10^4 vertices carry the
-// round. 48 queries on a 1M-vertex graph: 211 ms without, 153 with. On smaller graphs the 2048
-// smaller slots of the other kernel keep more of the short samples in flight: 96 graphs of at
+// LDS-claim kernels. What decides is the number and size of the hand-overs, for which the reach
+// ids only stand in. Where samples of 10^4 vertices carry the round, a workgroup of 512 threads
+// pays: 48 queries on a 1M-vertex graph 211 ms without, 153 with. Where hand-overs are few, the
+// 2048 smaller slots of the other kernel keep more of them in flight: 96 trivalency graphs of at
 // most 100,000 vertices 13.2 ms against 13.6, 32 queries on an 8k-vertex graph 10.8 against 12.7.
+// Below the line the other kernel is also kept where it loses: 48 weighted-cascade graphs of at
+// most 100,000 vertices take 54.6 ms, and would take 51.0 with 512 threads and 46.2 with 256; a
+// weighted-cascade GreedyReplace batch 27.1, 22.2 and 19.5; a 131k-vertex server 21.0, 20.1, 20.4.
 constexpr int64_t kMultiTreeReach = 1 << 17;
 
 // The workgroup kernel's slots for many-instance rounds: as many as a compute unit holds,

@@ -28,7 +28,9 @@
 //      above 1 into D, consecutive lanes to consecutive counters.
 // LDS holds one array of 16-bit entries, ancestors and sums in turn, beside the bitmaps.
 // The sizes pass keeps its ancestors and sizes in registers: kept in memory they were read and
-// written every round, beyond the L2 with all slots at work, and a launch took 7.2 ms for 4.4.
+// written every round, beyond the L2 with all slots at work, and a launch took 7.2 ms for 4.4. In
+// the forms of 32 words a thread they do not all fit beside what else lives: the compiler spills 11
+// registers in single calls (17 with 1,024 threads) and 8 in many-instance launches of 1,024.
 //
 // What bounds it is the random reads of the choices (L2) and of the doubling rounds (LDS).
 // Measured with 5,000 samples of a 131k-vertex R-MAT graph that reach 35,300 vertices each:

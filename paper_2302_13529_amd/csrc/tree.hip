@@ -1338,11 +1338,14 @@ hipError_t launch_shape(const TreeArgs &a, const TreeShape &s, hipStream_t strea
 {
     const dim3 grid(a.ws.slots);
     void (*k)(TreeArgs) = nullptr;
-    if (s.block == 64) k = tree_kernel<kMulti, kLT, 64>;
-    else if (s.block == 128) k = tree_kernel<kMulti, kLT, 128>;
-    else if (s.block == 256) k = tree_kernel<kMulti, kLT, 256>;
-    else if (s.block == 512) k = tree_kernel<kMulti, kLT, 512>;
-    else k = tree_kernel<kMulti, kLT, 1024>;
+    if (s.block == 512) k = tree_kernel<kMulti, kLT, 512>;
+    else if (s.block == 1024) k = tree_kernel<kMulti, kLT, 1024>;
+    if constexpr (!kMulti) {  // many-instance launches prefer 512, and take 1024 where that is more
+        if (s.block == 64) k = tree_kernel<kMulti, kLT, 64>;
+        else if (s.block == 128) k = tree_kernel<kMulti, kLT, 128>;
+        else if (s.block == 256) k = tree_kernel<kMulti, kLT, 256>;
+    }
+    if (!k) return hipErrorInvalidValue;
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)s.lds);

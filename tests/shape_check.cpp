@@ -29,6 +29,10 @@ int main()
                         continue;
                     }
                     ++taken;
+                    // many-instance launches, whose kernel has two sizes
+                    if (seed_edges < 0 && !reach_only && !block && theta == 1000000 &&
+                        f.nreach > (1 << 17) && s.block != 512 && s.block != 1024)
+                        return std::printf("nclaim %ld: %d threads\n", (long)nclaim, s.block), 1;
                     const size_t head = s.block == 64    ? head_bytes<64>()
                                         : s.block == 128 ? head_bytes<128>()
                                         : s.block == 256 ? head_bytes<256>()
