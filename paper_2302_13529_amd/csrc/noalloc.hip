@@ -346,13 +346,15 @@ int imin_decrease_noalloc(imin_graph *g, const int32_t *S, int32_t nS, const uin
         !ok(hipMemcpyAsync(g->d_inst, &I, sizeof(I), hipMemcpyHostToDevice, st)))
         return IMIN_EDEVICE;
     // The LDS-claim kernel takes every sample itself, unless there are very many, or 16 and more a
-    // slot on graphs whose slots in the array are fewer than the compute units (where the wave
-    // kernel alone fills the chip: 10,000 samples of a 131k-vertex trivalency graph, 67 slots, 1.80 ms
-    // without it and 0.37 with it; 2,000 from one seed of a 524k-vertex graph, 9 slots, 2.33 and
-    // 0.54; with 8 a slot, 500 from one seed of a 131k-vertex R-MAT graph, 0.18 and 0.30). The
-    // kernel of large claim sets takes those that the wave kernel leaves.
+    // slot (32 where the seeds have hardly any out-edges) on graphs whose slots in the array are
+    // fewer than the compute units, where the wave kernel alone fills the chip. 10,000 samples of a
+    // 131k-vertex trivalency graph, 67 slots, 1.80 ms without it and 0.37 with it; 2,000 from one
+    // seed of a 524k-vertex graph, 9 slots, 2.33 and 0.54; but 2,000 from one of a 131k-vertex R-MAT
+    // graph, some 90 slots, 0.56 and 0.65, and 500 0.18 and 0.30. The kernel of large claim sets
+    // takes those that the wave kernel leaves.
     const uint32_t *list = nullptr, *list_count = nullptr;
-    const bool few = main_tw.slots < g->num_cus && theta / 16 >= (uint32_t)main_tw.slots;
+    const bool few = main_tw.slots < g->num_cus &&
+                     (int64_t)theta >= (g->seed_edges >= 32 ? 16 : 32) * (int64_t)main_tw.slots;
     if (!tree || few || many_small(g, theta, main_tw.slots, false)) {
         imin::SmallArgs s;
         std::memset(&s, 0, sizeof(s));
