@@ -1493,17 +1493,27 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     const bool lt = model == IMIN_LT;
     const size_t quads = (size_t)std::max<int64_t>(((int64_t)m + 3) / 4, 1);
     const size_t edges = quads * 4;
-    // What the host fills lies in one block, laid out as on the device, and goes there in one copy:
-    // an allocation, a copy or a free costs a small graph 10 us each.
-    size_t staged = 0;
-    auto stage = [&](size_t words) {
-        const size_t at = staged;
-        staged += (words + 63) / 64 * 64;
-        return at;
+    // What the host fills lies in one block. Small graphs' arrays lie on the device as they do
+    // there and go in one copy: an allocation, a copy or a free costs a graph 10 us each. Larger
+    // arrays start where pages of memory do, as allocations of their own would: an 8k-vertex
+    // linear-threshold graph's 9,422 samples take 1.08 ms so, and 1.22 packed.
+    struct Filled {
+        size_t at, words;  // in the block
     };
-    const size_t o_row = stage((size_t)n + 1), o_col = stage(edges), o_thr = stage(edges);
-    const size_t o_in = stage((size_t)n + 1), o_ine = stage((size_t)std::max(m, 1));
-    const size_t o_lo = lt ? stage(edges) : 0, o_rid = stage((size_t)n), o_vtx = stage((size_t)n);
+    size_t staged = 0;
+    auto page = [](size_t bytes) {
+        return bytes >= (size_t)2 << 20 ? (size_t)2 << 20 : bytes >= (32 << 10) ? (size_t)64 << 10 : 256;
+    };
+    auto stage = [&](size_t words) {
+        const size_t to = std::min<size_t>(page(words * 4), 64 << 10) / 4;
+        const size_t at = (staged + to - 1) / to * to;
+        staged = at + words;
+        return Filled{at, words};
+    };
+    const Filled f_row = stage((size_t)n + 1), f_col = stage(edges), f_thr = stage(edges);
+    const Filled f_in = stage((size_t)n + 1), f_ine = stage((size_t)std::max(m, 1));
+    const Filled f_lo = stage(lt ? edges : 0), f_rid = stage((size_t)n), f_vtx = stage((size_t)n);
+    const bool one_copy = staged * 4 <= (1 << 20);
     std::vector<uint32_t> host;
     std::vector<int32_t> fill;
     std::vector<uint4> fnode;
@@ -1512,11 +1522,11 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     bool forest = false;
     try {
         host.assign(staged, 0u);  // padding edges have threshold 0: never live
-        std::copy(row_ptr, row_ptr + n + 1, host.begin() + o_row);
-        if (m > 0) std::copy(col, col + m, host.begin() + o_col);
-        uint32_t *const thr = host.data() + o_thr;
-        int32_t *const in_ptr = reinterpret_cast<int32_t *>(host.data() + o_in);
-        int32_t *const in_edge = reinterpret_cast<int32_t *>(host.data() + o_ine);
+        std::copy(row_ptr, row_ptr + n + 1, host.begin() + f_row.at);
+        if (m > 0) std::copy(col, col + m, host.begin() + f_col.at);
+        uint32_t *const thr = host.data() + f_thr.at;
+        int32_t *const in_ptr = reinterpret_cast<int32_t *>(host.data() + f_in.at);
+        int32_t *const in_edge = reinterpret_cast<int32_t *>(host.data() + f_ine.at);
         if (!lt)
             for (int32_t e = 0; e < m; ++e) thr[e] = live_threshold(prob[e]);
         // in-edge index: edge ids grouped by target, ascending (counting sort)
@@ -1526,8 +1536,8 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
         for (int32_t e = 0; e < m; ++e) in_edge[fill[(size_t)col[e]]++] = e;
         // Reach ids: the vertices that need a claim (two or more in-edges), then those with one;
         // the vertices without are numbered below -1.
-        int32_t *const rid = reinterpret_cast<int32_t *>(host.data() + o_rid);
-        int32_t *const vtx = reinterpret_cast<int32_t *>(host.data() + o_vtx);
+        int32_t *const rid = reinterpret_cast<int32_t *>(host.data() + f_rid.at);
+        int32_t *const vtx = reinterpret_cast<int32_t *>(host.data() + f_vtx.at);
         for (int32_t v = 0; v < n; ++v) {
             const int32_t deg = in_ptr[(size_t)v + 1] - in_ptr[v];
             if (deg > 1) {
@@ -1547,7 +1557,7 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
             // Linear-threshold model: the in-edges of v split [0, 2^24) into consecutive intervals,
             // edge k of v (ascending id) getting [bound_{k-1}, bound_k) with
             // bound_k = min(2^24, ceil(2^24 * (w_1 + ... + w_k))) from fp64 running sums.
-            uint32_t *const lo = host.data() + o_lo;
+            uint32_t *const lo = host.data() + f_lo.at;
             for (int32_t v = 0; v < n; ++v) {
                 double sum = 0.0;
                 uint32_t prev = 0;
@@ -1592,21 +1602,27 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     g->nsrc = nsrc;
     const size_t records = g->tree ? edges : 0, fedges = g->forest ? (size_t)m : 0;
     auto carve = [&](unsigned char *base) {
-        uint32_t *const w = reinterpret_cast<uint32_t *>(base);
-        g->d_row_ptr = reinterpret_cast<int32_t *>(w + o_row);
-        g->d_col4 = reinterpret_cast<uint4 *>(w + o_col);
-        g->d_thr_orig = reinterpret_cast<uint4 *>(w + o_thr);
-        g->d_in_ptr = reinterpret_cast<int32_t *>(w + o_in);
-        g->d_in_edge = reinterpret_cast<int32_t *>(w + o_ine);
-        g->d_lo4 = lt ? reinterpret_cast<uint4 *>(w + o_lo) : nullptr;
-        g->d_rid_of = reinterpret_cast<int32_t *>(w + o_rid);
-        g->d_rid_vtx = reinterpret_cast<int32_t *>(w + o_vtx);
-        size_t at = staged * sizeof(uint32_t);
+        size_t at = one_copy ? (staged * 4 + 255) / 256 * 256 : 0;
         auto take = [&](auto *&p, size_t count) {
             using T = typename std::remove_reference<decltype(*p)>::type;
+            const size_t to = page(count * sizeof(T));
+            at = (at + to - 1) / to * to;
             p = count > 0 ? reinterpret_cast<T *>(base + at) : nullptr;
-            at += (count * sizeof(T) + 255) / 256 * 256;
+            at += count * sizeof(T);
         };
+        auto place = [&](auto *&p, Filled f) {
+            using T = typename std::remove_reference<decltype(*p)>::type;
+            if (one_copy) p = f.words ? reinterpret_cast<T *>(base + f.at * 4) : nullptr;
+            else take(p, f.words * 4 / sizeof(T));
+        };
+        place(g->d_row_ptr, f_row);
+        place(g->d_col4, f_col);
+        place(g->d_thr_orig, f_thr);
+        place(g->d_in_ptr, f_in);
+        place(g->d_in_edge, f_ine);
+        place(g->d_lo4, f_lo);
+        place(g->d_rid_of, f_rid);
+        place(g->d_rid_vtx, f_vtx);
         take(g->d_thr4, quads);
         take(g->d_inelig, (size_t)g->words);
         take(g->d_cand, (size_t)g->words);
@@ -1641,7 +1657,17 @@ int imin_graph_create_model(int32_t n, int32_t m, const int32_t *row_ptr, const 
     carve(g->block);
     const uint32_t *const orig = reinterpret_cast<const uint32_t *>(g->d_thr_orig);
     const uint32_t *const targets = reinterpret_cast<const uint32_t *>(g->d_col4);
-    if (!ok(hipMemcpy(g->block, host.data(), staged * sizeof(uint32_t), hipMemcpyHostToDevice)) ||
+    auto send = [&](void *to, Filled f) {
+        return f.words == 0 ||
+               ok(hipMemcpy(to, host.data() + f.at, f.words * 4, hipMemcpyHostToDevice));
+    };
+    const bool sent = one_copy
+                          ? send(g->block, Filled{0, staged})
+                          : send(g->d_row_ptr, f_row) && send(g->d_col4, f_col) &&
+                                send(g->d_thr_orig, f_thr) && send(g->d_in_ptr, f_in) &&
+                                send(g->d_in_edge, f_ine) && send(g->d_lo4, f_lo) &&
+                                send(g->d_rid_of, f_rid) && send(g->d_rid_vtx, f_vtx);
+    if (!sent ||
         (g->forest && !ok(hipMemcpy(g->d_fnode, fnode.data(), fnode.size() * sizeof(uint4),
                                     hipMemcpyHostToDevice))) ||
         !ok(imin::launch_edge_records(targets, g->d_row_ptr, g->d_rid_of, orig,
