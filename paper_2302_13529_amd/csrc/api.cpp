@@ -245,11 +245,12 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
         const int32_t most = (int32_t)std::min<int64_t>((int64_t)g->shape.per_cu * g->num_cus, filled);
         const imin::TreeWs &have = g->main_tw;
         if (reach_only) {
-            // The row ranges are all that reachability needs: a slot takes 8 bytes a reach id
-            // where dominators take 25, and the many small workgroups share the space of the
-            // fewer large ones of the other calls. More than two a compute unit take a sixteenth
-            // of the device's memory at most.
-            const size_t per = (size_t)lcap * sizeof(int2);
+            // Row ranges and level starts are all that reachability writes: a slot takes 12 bytes a
+            // reach id where dominators take 25, and the many small workgroups share the space of
+            // the fewer large ones of the other calls. More than two a compute unit take a
+            // sixteenth of the device's memory at most. (8 bytes, with the level starts left out by
+            // a test in the kernel, cost the dominators' calls 0.8 %: 22.6 ms for 22.4.)
+            const size_t per = (size_t)lcap * sizeof(int2) + (size_t)(lcap + 1) * sizeof(int32_t);
             const int64_t there =
                 have.base ? (int64_t)((size_t)(have.base + have.bytes -
                                                reinterpret_cast<unsigned char *>(have.rng)) / per) : 0;
@@ -271,6 +272,7 @@ int size_workspaces(imin_graph *g, int32_t max_slots, uint32_t theta, bool reach
             g->reach_tw.slots = (int32_t)want;
             g->reach_tw.lcap = lcap;
             g->reach_tw.rng = g->main_tw.rng;
+            g->reach_tw.lvl = reinterpret_cast<int32_t *>(g->reach_tw.rng + want * lcap);
             return IMIN_OK;
         }
         int32_t slots = g->force_slots;

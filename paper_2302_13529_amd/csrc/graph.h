@@ -101,7 +101,7 @@ struct imin_graph {
     int32_t *d_x = nullptr;
     imin::Workspace main_ws, big_ws;
     imin::TreeWs main_tw, big_tw;
-    imin::TreeWs reach_tw;             // main_tw's space as slots of row ranges alone
+    imin::TreeWs reach_tw;             // main_tw's space as slots of row ranges and level starts
     unsigned char *leaf = nullptr;     // the wave-per-sample form's scratch
     imin::ForestWs fws;
     std::vector<int32_t> masked;       // vertices whose in-edges have threshold 0 in d_thr4

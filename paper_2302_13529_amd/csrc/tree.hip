@@ -620,7 +620,7 @@ void tree_kernel(TreeArgs a)
         }
         const int cwords = kLT ? 0 : (c.nclaim + 31) >> 5;
         for (int w = tid; w < cwords; w += B) bm[w] = 0u;
-        if (tid == 0 && !a.reach_only) {
+        if (tid == 0) {
             sv.lvl[0] = 0;
             sv.lvl[1] = 1;
         }
@@ -629,7 +629,7 @@ void tree_kernel(TreeArgs a)
         uint32_t p_scanned = 0, p_live = 0;
         int L = 0, lo = 0, hi = c.nseeds, base = 1, lset = 0;
         do {
-            if (tid == 0 && L > 0 && !a.reach_only) sv.lvl[L + 1] = hi;
+            if (tid == 0 && L > 0) sv.lvl[L + 1] = hi;
             GroupSink<kLT> sink{c, sv, a.ws.xcap, a.reach_only != 0, bm, &sh.nextra, base,
                                 &sh.grown[lset], false};
             const int grown = expand_level<B, kLT>(c, sv.rng, sh, sink, L == 0, lo, hi, lset, j,
