@@ -82,6 +82,18 @@ def traffic_from_profile(path: str, kernel_source: str):
         return None
 
 
+RMAT22_PROFILE = os.path.join("profiles", "tree_kernel_rmat22_pmc.txt")
+
+
+def rmat22_traffic(model: str):
+    """The headline launch's HBM bytes. The counters are of the independent-cascade launch: a
+    linear-threshold launch reaches three times as many vertices and has no summary."""
+    if model != "ic":
+        return None
+    return traffic_from_profile(os.path.join(ROOT, RMAT22_PROFILE),
+                                os.path.join(ROOT, "paper_2302_13529_amd", "csrc", "tree.hip"))
+
+
 def cpu_workers() -> int:
     """Host cores the CPU oracle runs on: this process's CPU affinity, at most 16."""
     try:
@@ -378,9 +390,7 @@ def bench_headline(args) -> dict:
     alg = algorithmic_bytes(st, len(inst.seeds))
     kernel_s = st["kernel_ms"] / 1e3
     achieved = alg / kernel_s / 1e9
-    prof = os.path.join("profiles", "tree_kernel_rmat22_pmc.txt")
-    src = os.path.join("paper_2302_13529_amd", "csrc", "tree.hip")
-    traffic = traffic_from_profile(os.path.join(ROOT, prof), os.path.join(ROOT, src))
+    traffic = rmat22_traffic(args.model)
     out = line(samples / dt, "samples/s", args.steps, args.warmup, dt * 1e3 / args.steps,
                {"workload": inst.name + ("_lt" if args.model == "lt" else ""),
                 "model": args.model.upper(), "n": inst.n, "m": inst.m,
@@ -392,7 +402,7 @@ def bench_headline(args) -> dict:
         "blockers": [int(x) for x in B],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "traffic_source": (f"{prof} (rocprofv3 FETCH_SIZE/WRITE_SIZE of this "
+                     "traffic_source": (f"{RMAT22_PROFILE} (rocprofv3 FETCH_SIZE/WRITE_SIZE of this "
                                         f"kernel source, sha256 match)") if traffic else None,
                      "kernel": "tree_kernel",
                      "algorithmic_bytes_per_launch": alg / launches,

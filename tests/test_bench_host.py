@@ -47,6 +47,12 @@ def test_committed_profile_names_a_source_hash_and_traffic():
     assert fields["kernel_source_sha256"] == hashlib.sha256(open(src, "rb").read()).hexdigest()
 
 
+def test_headline_traffic_is_of_the_independent_cascade_launch():
+    # the counters belong to the committed kernel, and to no launch under linear threshold
+    assert bench.rmat22_traffic("ic") > 0
+    assert bench.rmat22_traffic("lt") is None
+
+
 def test_more_than_one_gpu_is_refused():
     root = os.path.dirname(os.path.abspath(bench.__file__))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"],
